@@ -111,9 +111,10 @@ WsLayout ws_layout(const specdec_model_desc* d, int max_rows, int max_ctx) {
   const size_t R = (size_t)max_rows;
   const int hd = d->head_dim, H = d->n_heads, G = d->n_kv_heads;
   // (passes of up to max_rows rows: the skinny and, above kMaxGemmRows, the wide partial counts)
-  w.ss_parts = std::max(1, gemm_row_blocks(d->dtype, EPI_RESID, d->d_model, std::min(max_rows, kMaxGemmRows)));
+  w.ss_parts = std::max(1, gemm_row_blocks(d->dtype, EPI_RESID, d->d_model, std::min(max_rows, kMaxGemmRows), true));
   const bool wide = gemm_wide(d->dtype, max_rows);
-  if (wide) w.ss_parts = std::max(w.ss_parts, gemm_row_blocks(d->dtype, EPI_RESID, d->d_model, max_rows));
+  if (d->dtype == SPECDEC_BF16)
+    w.ss_parts = std::max(w.ss_parts, gemm_row_blocks(d->dtype, EPI_RESID, d->d_model, max_rows, false));
   w.chunk = attention_chunk(d->dtype, hd);
   w.n_split = (max_ctx + w.chunk - 1) / w.chunk;
   size_t off = 0;
@@ -131,10 +132,14 @@ WsLayout ws_layout(const specdec_model_desc* d, int max_rows, int max_ctx) {
   w.u = take(R * d->ffn_dim * 4);
   w.logits = take(R * d->vocab * 4);
   w.samp = take(sampling_scratch_bytes(max_rows, 1, d->vocab));
-  // (stacked operands: two 1 KB fragments per 32 columns)
-  w.xs_d = take(d->dtype == SPECDEC_BF16 ? (size_t)(d->d_model + 31) / 32 * 2048 : 0);
-  w.xs_f = take(d->dtype == SPECDEC_BF16 ? (size_t)(std::max(d->ffn_dim, H * hd) + 31) / 32 * 2048 : 0);
-  w.ypart = take(wide ? wide_ypart_floats(d->d_model) * 4 : 0);
+  // (stacked operands: two 1 KB fragments per 32 columns and 16 rows)
+  const bool bf16 = d->dtype == SPECDEC_BF16;
+  const size_t stk_tile = bf16 ? (size_t)(std::min(max_rows, kMaxGemmRows) + 15) / 16 * 2048 : 0;
+  w.xs_d = take((size_t)(d->d_model + 31) / 32 * stk_tile);
+  w.xs_f = take((size_t)(std::max(d->ffn_dim, H * hd) + 31) / 32 * stk_tile);
+  const size_t rows_part = bf16 && max_rows > kSkinnyRows
+                               ? (size_t)kRowsSplitMax * std::min(max_rows, kMaxGemmRows) * d->d_model : 0;
+  w.ypart = take(std::max(rows_part, wide ? wide_ypart_floats(d->d_model) : 0) * 4);
   w.ctr = take(d->dtype == SPECDEC_BF16 ? attention_counter_count(H, G, max_rows) * 4 : 0);
   w.cnt = take(d->dtype == SPECDEC_BF16 ? attention_counter_count(H, G, max_rows) * 4 : 0);
   w.ll = take(d->dtype == SPECDEC_BF16 ? attention_ll_words(H, hd, max_rows, w.n_split) * 8 : 0);
@@ -296,12 +301,13 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   ra.rope_cs = m->rope_cs;
   ra.h = m->h;
   ra.ss = m->ss;
-  // Passes of at most 16 rows on bf16 weights hand x from kernel to kernel also
-  // as a stacked operand (put_stacked): the skinny GEMMs then read one 16-byte
-  // fragment per k-step (two when M > 8) instead of two float32 loads per row
-  // tile.
-  const bool stk = dt == SPECDEC_BF16 && m->wfmt != SPECDEC_WEIGHTS_INT4 && M <= 16 && m->xs_d;
-  const int stt = M <= 8 ? 1 : 2;
+  // Passes of at most 64 rows on bf16 weights hand x from kernel to kernel as a
+  // stacked operand (put_stacked): the GEMMs then read 16-byte fragments (one
+  // per k-step over at most 8 rows, two per 16 rows above) instead of float32
+  // rows which each would convert again.
+  const bool q4 = m->wfmt == SPECDEC_WEIGHTS_INT4;
+  const bool stk = dt == SPECDEC_BF16 && !q4 && M <= kMaxGemmRows && m->xs_d;
+  const int stt = M <= 8 ? 1 : 2 * ((M + 15) / 16);
   ra.xs = stk ? m->xs_d : nullptr;
   ra.stt = stt;
   {
@@ -325,7 +331,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   base.ypart = m->ypart;
   base.stt = stt;
   int n_ss = 1;
-  const int n_resid_blocks = gemm_row_blocks(dt, EPI_RESID, d.d_model, M);
+  const int n_resid_blocks = gemm_row_blocks(dt, EPI_RESID, d.d_model, M, q4);
 
   AttnArgs at{};
   at.rows = m->rows;
@@ -371,7 +377,6 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
       q.rows = m->rows; q.rope_cs = m->rope_cs; q.qr = m->qr; q.kv = kv_layout(kv); q.layer = l;
       q.n_heads = H; q.n_kv_heads = G; q.head_dim = hd;
     }
-    const bool q4 = m->wfmt == SPECDEC_WEIGHTS_INT4;
     if (q4) { q.q4 = 1; q.wscale[0] = m->sq[l]; q.wscale[1] = m->sk[l]; q.wscale[2] = m->sv[l]; }
     if (stk) q.xs = m->xs_d;
     {
@@ -623,7 +628,7 @@ specdec_status specdec_model_create_fmt(const specdec_model_desc* desc, const sp
   m->samp = base + L.samp;
   m->xs_d = desc->dtype == SPECDEC_BF16 ? (uint16_t*)(base + L.xs_d) : nullptr;
   m->xs_f = desc->dtype == SPECDEC_BF16 ? (uint16_t*)(base + L.xs_f) : nullptr;
-  m->ypart = gemm_wide(desc->dtype, max_rows) ? (float*)(base + L.ypart) : nullptr;
+  m->ypart = bf16 && max_rows > kSkinnyRows ? (float*)(base + L.ypart) : nullptr;
   m->attn_ctr = desc->dtype == SPECDEC_BF16 ? (uint32_t*)(base + L.ctr) : nullptr;
   m->attn_cnt = desc->dtype == SPECDEC_BF16 ? (uint32_t*)(base + L.cnt) : nullptr;
   m->attn_ll = desc->dtype == SPECDEC_BF16 ? (uint64_t*)(base + L.ll) : nullptr;

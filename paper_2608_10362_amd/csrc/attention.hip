@@ -171,11 +171,11 @@ __device__ __forceinline__ void split_hilo(const float* v, bf16x8& hi, bf16x8& l
   }
 }
 
-// One element of the attention output o[row][head * hd + d], also into the
-// stacked operand of the O projection when the pass hands x over stacked.
+// One element of the attention output o[row][head * hd + d], into the stacked
+// operand of the O projection where the pass hands x over stacked.
 __device__ __forceinline__ void put_o(const AttnArgs& a, float* o, int row, int head, int d, float v) {
-  o[d] = v;
   if (a.xs) put_stacked(a.xs, a.stt, row, head * a.head_dim + d, v);
+  else o[d] = v;
 }
 
 // Reductions over the 16 lanes of a row of the wave (lanes 16k .. 16k+15)

@@ -13,6 +13,8 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));  // (callers' buffers: float alignment)
+typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------ storage types
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) {
@@ -26,19 +28,35 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// Stacked bf16 operand of at most 16 activation rows, the x operand of the
-// skinny GEMMs written by the kernels that produce x: per 32-column k-step,
-// stt fragments of 1 KB in MFMA operand order (lane 16*(k%32/8) + row,
-// element k%8).  stt = 1 (at most 8 rows): row m's hi part in fragment row m
-// and its lo part in row 8 + m, so one product gives both; stt = 2 (at most
-// 16 rows): the hi parts in fragment 0, the lo parts in fragment 1.  hi =
-// bf16(v), lo = bf16(v - hi) (round to nearest even, as the GEMMs' own split).
+// Stacked bf16 operand: activation rows as the x operand of the GEMMs,
+// written by the kernels that produce x: per 32-column k-step, stt fragments
+// of 1 KB in MFMA operand order (lane 16*(k%32/8) + row%16, element k%8).
+// stt = 1 (at most 8 rows): row m's hi part in fragment row m and its lo part
+// in row 8 + m, so one product gives both; stt = 2 MT (MT = ceil(rows / 16)):
+// the hi parts of row tile m/16 in fragment 2(m/16), its lo parts in the next
+// one.  hi = bf16(v), lo = bf16(v - hi) (round to nearest even).
+__device__ __forceinline__ size_t stacked_at(int stt, int m, int k) {
+  return ((size_t)(k >> 5) * stt + 2 * (m >> 4)) * 512 + (size_t)(16 * ((k & 31) >> 3) + (m & 15)) * 8 + (k & 7);
+}
 __device__ __forceinline__ void put_stacked(uint16_t* xs, int stt, int m, int k, float v) {
   const __bf16 h = (__bf16)v;
   const __bf16 l = (__bf16)(v - (float)h);
-  const size_t at = (size_t)(k >> 5) * stt * 512 + (size_t)(16 * ((k & 31) >> 3) + m) * 8 + (k & 7);
+  const size_t at = stacked_at(stt, m, k);
   xs[at] = __builtin_bit_cast(uint16_t, h);
   xs[at + (stt == 1 ? 64 : 512)] = __builtin_bit_cast(uint16_t, l);
+}
+// Columns k .. k+3 (k % 4 == 0) of row m.
+__device__ __forceinline__ void put_stacked4(uint16_t* xs, int stt, int m, int k, f32x4 v) {
+  u16x4 h, l;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const __bf16 hb = (__bf16)v[e];
+    h[e] = __builtin_bit_cast(uint16_t, hb);
+    l[e] = __builtin_bit_cast(uint16_t, (__bf16)(v[e] - (float)hb));
+  }
+  const size_t at = stacked_at(stt, m, k);
+  *(u16x4*)(xs + at) = h;
+  *(u16x4*)(xs + at + (stt == 1 ? 64 : 512)) = l;
 }
 
 template <typename T> struct Storage;

@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "gemm_common.h"
 #include "internal.h"
 
 namespace specdec {
@@ -23,16 +24,6 @@ namespace {
 
 constexpr int kMfmaThreads = 1024;  // 16 waves split K
 constexpr int kMfmaWaves = kMfmaThreads / kWave;
-
-__device__ __forceinline__ float silu_f(float z) { return z / (1.0f + expf(-z)); }
-
-// Raw buffer descriptor over `bytes` bytes at `base` (dword 3: the gfx9 raw
-// buffer format); loads past `bytes` return zeros.
-constexpr uint32_t kOutOfRange = 0x80000000u;
-constexpr int kNonTemporal = 2;  // cache-policy bit of a streamed (read-once) load
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
-}
 
 __device__ __forceinline__ float load_gain(const void* g, int bf16, int n) {
   return bf16 ? bf16_bits_to_f32(((const uint16_t*)g)[n]) : ((const float*)g)[n];
@@ -161,47 +152,6 @@ __device__ __forceinline__ const WT* weight_row(const GemmArgs& a, int kind, int
   if (n < b1) return (const WT*)a.w[0] + (size_t)n * a.K;
   if (n < b2) return (const WT*)a.w[1] + (size_t)(n - b1) * a.K;
   return (const WT*)a.w[2] + (size_t)(n - b2) * a.K;
-}
-
-// Base of the packed 16-row tile `t` (t < NC/16) of block `blk`.  Packed
-// matrices are sequences of 16-row tiles of ceil(K/32) 1 KB fragments.
-__device__ __forceinline__ const uint16_t* weight_tile(const GemmArgs& a, int kind, int blk, int NC, int t,
-                                                       int KS, bool& ok) {
-  int seg, n;
-  if (kind == EPI_SWIGLU) {
-    const int H = NC / 2;
-    seg = 16 * t >= H;
-    n = blk * H + 16 * t - seg * H;
-    ok = n < a.n_rows;
-    if (!ok) n = 0;
-  } else {
-    n = blk * NC + 16 * t;
-    ok = n < a.n_rows;
-    if (!ok) n = 0;
-    const int b1 = a.n_seg[0], b2 = b1 + a.n_seg[1];
-    seg = n < b1 ? 0 : (n < b2 ? 1 : 2);
-    n -= seg == 0 ? 0 : (seg == 1 ? b1 : b2);
-  }
-  return (const uint16_t*)a.w[seg] + (size_t)(n / 16) * KS * 512;
-}
-
-// Segment and local row of row tile t of block blk (as weight_tile).
-__device__ __forceinline__ void tile_segment(const GemmArgs& a, int kind, int blk, int NC, int t, int& seg, int& n,
-                                             bool& ok) {
-  if (kind == EPI_SWIGLU) {
-    const int H = NC / 2;
-    seg = 16 * t >= H;
-    n = blk * H + 16 * t - seg * H;
-    ok = n < a.n_rows;
-    if (!ok) n = 0;
-  } else {
-    n = blk * NC + 16 * t;
-    ok = n < a.n_rows;
-    if (!ok) n = 0;
-    const int b1 = a.n_seg[0], b2 = b1 + a.n_seg[1];
-    seg = n < b1 ? 0 : (n < b2 ? 1 : 2);
-    n -= seg == 0 ? 0 : (seg == 1 ? b1 : b2);
-  }
 }
 
 // INT4 image of W [N, K]: per 16-row tile and group of 128 columns a 1 KB
@@ -1417,9 +1367,10 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(GemmArgs a, int n_spl
     const f32x4 h = *(const f32x4*)hp + y;
     *(f32x4*)hp = h;
     const uint16_t* g = (const uint16_t*)a.gain_out + n;
-    *(f32x4*)(a.xg_out + (size_t)m * a.ldo + n) =
-        f32x4{h[0] * bf16_bits_to_f32(g[0]), h[1] * bf16_bits_to_f32(g[1]), h[2] * bf16_bits_to_f32(g[2]),
-              h[3] * bf16_bits_to_f32(g[3])};
+    const f32x4 x = f32x4{h[0] * bf16_bits_to_f32(g[0]), h[1] * bf16_bits_to_f32(g[1]), h[2] * bf16_bits_to_f32(g[2]),
+                          h[3] * bf16_bits_to_f32(g[3])};
+    if (a.xs_out) put_stacked4(a.xs_out, a.stt, m, n, x);
+    else *(f32x4*)(a.xg_out + (size_t)m * a.ldo + n) = x;
     t = h[0] * h[0] + h[1] * h[1] + h[2] * h[2] + h[3] * h[3];
   }
 #pragma unroll
@@ -1472,30 +1423,7 @@ __global__ __launch_bounds__(256) void qkv_reduce_kernel(GemmArgs a, int n_split
     y[e] *= sc;
     z[e] = __shfl_xor(y[e], 2, kWave);
   }
-  if (!live) return;
-  const int H = a.n_heads, hd = a.head_dim, half = hd >> 1, cap = a.kv.capacity;
-  const int nq = a.n_seg[0], nqk = nq + a.n_seg[1];
-  const RowDesc rd = a.rows[m];
-  if (n >= nqk) {  // values: natural order
-    if (!rd.valid) return;
-    const int r = n - nqk, head = r / hd, w = r % hd;
-    uint16_t* kvb = k_block<uint16_t>(a.kv, a.layer, rd.b, head);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) Storage<uint16_t>::store(kvb + KvIndex<uint16_t>::v(rd.pos, w + e, hd, cap), y[e]);
-    return;
-  }
-  const bool is_q = n < nq;
-  const int r = n - (is_q ? 0 : nq), head = r / hd, w = r % hd, tq = w >> 4;
-  const float* cs = a.rope_cs + (size_t)m * hd;
-  uint16_t* kvb = is_q || !rd.valid ? nullptr : k_block<uint16_t>(a.kv, a.layer, rd.b, head);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int ec = (w & 15) + e, j = 8 * tq + (ec & 7), d = ec < 8 ? j : half + j;
-    const float c = cs[j], sn = cs[half + j];
-    const float out = ec < 8 ? y[e] * c - z[e] * sn : y[e] * c + z[e] * sn;
-    if (is_q) a.qr[((size_t)m * H + head) * hd + d] = out;
-    else if (kvb) Storage<uint16_t>::store(kvb + KvIndex<uint16_t>::k(rd.pos, d, hd, cap), out);
-  }
+  if (live) qkv_store4(a, m, n, y, z);
 }
 
 // ---------------------------------------------------------------- tile MFMA kernel (bf16 weights, 129+ rows)
@@ -1937,8 +1865,14 @@ size_t wide_ypart_floats(int n_rows) {
   return (size_t)std::max(kWideSplitMax * kWideRows, kTilePartialRows) * n_rows;
 }
 
-int gemm_row_blocks(int dtype, int kind, int n_rows, int M) {
-  if (gemm_wide(dtype, M) && kind == EPI_RESID) return (n_rows + kWideCols - 1) / kWideCols;
+hipError_t launch_resid_reduce(const GemmArgs& a, int n_split, hipStream_t s) {
+  hipLaunchKernelGGL(resid_reduce_kernel, dim3((a.n_rows + kWideCols - 1) / kWideCols, (a.M + 7) / 8), dim3(256), 0, s,
+                     a, n_split);
+  return hipGetLastError();
+}
+
+int gemm_row_blocks(int dtype, int kind, int n_rows, int M, bool q4) {
+  if (kind == EPI_RESID && (gemm_wide(dtype, M) || (dtype == SPECDEC_BF16 && !q4 && M > kSkinnyRows))) return (n_rows + kWideCols - 1) / kWideCols;
   if (dtype == SPECDEC_BF16) {
     int nc = 16 * mfma_tiles(kind, n_rows);
     int per = kind == EPI_SWIGLU ? nc / 2 : nc;
@@ -2154,7 +2088,8 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
     return launch_wide(a, s);
   }
   if (a.M > kMaxGemmRows) return hipErrorInvalidValue;
-  const int blocks = gemm_row_blocks(dtype, a.kind, a.n_rows, a.M);
+  if (a.xs && a.M > kSkinnyRows) return dtype == SPECDEC_BF16 && !a.q4 ? launch_gemm_rows(a, s) : hipErrorInvalidValue;
+  const int blocks = gemm_row_blocks(dtype, a.kind, a.n_rows, a.M, a.q4 != 0);
   if (a.q4) {  // INT4 layer weights (passes of at most 64 rows)
     if (dtype != SPECDEC_BF16 || (a.K % 32) != 0) return hipErrorInvalidValue;
     if (a.kind == EPI_RESID && !a.gain_bf16) return hipErrorInvalidValue;

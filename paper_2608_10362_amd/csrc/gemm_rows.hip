@@ -1,0 +1,278 @@
+// Weight-streaming GEMMs of passes of 17 to 128 rows (the verify blocks of
+// several sequences, draft steps of many, catch-up and prefill chunks):
+//   y[m, n] = s_m * sum_k W[n, k] x[m, k]
+// with bf16 weights from the packed image and x handed over by its producer
+// as the stacked bf16 operand (put_stacked: hi and lo parts, x = hi + lo +
+// O(2^-17 |x|)), so two products per weight fragment give a float32-accuracy
+// result and no kernel converts x again.
+#include <algorithm>
+
+#include "device_common.h"
+#include "gemm_common.h"
+#include "internal.h"
+
+namespace specdec {
+
+namespace {
+
+// Block = NW waves, a work unit = T tiles of 16 weight rows over a range of
+// k-steps; the unit's k-steps are dealt out to the waves (wave w: w, w + NW,
+// ...) and every wave holds the whole unit's T x MT accumulator tiles in
+// registers.  So each x fragment is read once per block, straight into the
+// registers of the one wave that multiplies it: no staging, no barrier in the
+// loop, and 2 MT / T bytes of x (from L2) per weight byte.  Two register
+// buffers of UB k-steps keep the next loads, including the next unit's, in
+// flight during the products and the epilogue.  Then the waves' sums are added
+// in wave order through LDS, each wave finishing whole fragments.
+// The weights are the A operand: D[4 (l/16) + r][l % 16] is weight row 4
+// (l/16) + r, x row l % 16, so a lane ends with four consecutive columns of
+// one row and stores them at once; a RoPE partner (column ^ 8) is lane ^ 32.
+template <int T, int MT, int NW, int UB, int KIND>
+__global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_units, int n_split, int ks_per_split) {
+  constexpr int NTH = 64 * NW, NC = 16 * T, MP = 16 * MT, NF = T * MT, XF = 2 * MT;
+  constexpr bool SCALE = KIND != EPI_RESID, SWIGLU = KIND == EPI_SWIGLU;
+  // fragments per reduction round (a SwiGLU round holds whole gate / up pairs)
+  constexpr int RMAX = 128 / NW;
+  constexpr int RT = T * MT <= RMAX ? MT : (RMAX / T > 0 ? RMAX / T : 1);  // row tiles per round
+  __shared__ f32x4 red[RT * T][NW][kWave];
+  __shared__ float scale[MP];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int K = a.K, KS = K / 32, M = a.M;
+  const int split = (int)blockIdx.x % n_split, u0 = (int)blockIdx.x / n_split, us = (int)gridDim.x / n_split;
+  const int ks_begin = split * ks_per_split, n_k = min(KS, ks_begin + ks_per_split) - ks_begin;
+  const int my_ks = n_k > wave ? (n_k - wave + NW - 1) / NW : 0;
+  const int nbat = max(1, (my_ks + UB - 1) / UB);
+  const int my_units = (n_units - u0 + us - 1) / us;
+  const int total = my_units * nbat;
+
+  floatx4 acc[MT][T];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int t = 0; t < T; ++t) acc[mt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  u32x4 wA[UB][T], wB[UB][T], xA[UB][XF], xB[UB][XF];
+
+  // (the lanes of rows past M read nothing and hold zeros)
+  const uint32_t xlast = (uint32_t)(16 * (MT - 1) + (lane & 15) >= M) << 31;
+  const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.xs, (uint32_t)KS * XF * 1024u);
+  int lu = u0, lb = 0;  // load cursor: unit, batch
+  auto load = [&](u32x4 (&wv)[UB][T], u32x4 (&xv)[UB][XF]) {
+    __amdgpu_buffer_rsrc_t wr[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      bool ok;
+      const uint16_t* base = weight_tile(a, KIND, lu, NC, t, KS, ok);
+      wr[t] = make_rsrc(base, ok ? (uint32_t)KS * 1024u : 0u);
+    }
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int i = lb * UB + u;
+      const uint32_t ks = (uint32_t)(ks_begin + wave + i * NW);
+      const uint32_t bad = (uint32_t)(i >= my_ks) << 31;
+      const uint32_t woff = (ks * 1024u + lane * 16u) | bad;
+#pragma unroll
+      for (int t = 0; t < T; ++t) wv[u][t] = __builtin_amdgcn_raw_buffer_load_b128(wr[t], woff, 0, kNonTemporal);
+#pragma unroll
+      for (int f = 0; f < XF; ++f) {
+        const uint32_t xoff = ((ks * XF + f) * 1024u + lane * 16u) | bad | (f >= XF - 2 ? xlast : 0u);
+        xv[u][f] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff, 0, 0);
+      }
+    }
+    if (++lb == nbat) { lb = 0; lu += us; }
+  };
+  auto compute = [&](const u32x4 (&wv)[UB][T], const u32x4 (&xv)[UB][XF]) {
+#pragma unroll
+    for (int u = 0; u < UB; ++u)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int t = 0; t < T; ++t)
+            acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[u][t]),
+                                                                 __builtin_bit_cast(bf16x8, xv[u][2 * mt + h]),
+                                                                 acc[mt][t], 0, 0, 0);
+  };
+
+  // One finished fragment: y[r] = column n + r of row m (sums over all waves).
+  const int cl = lane & 15, rg = lane >> 4;
+  auto emit = [&](int unit, int mt, int t, f32x4 y, f32x4 yu) {
+    const int m = mt * 16 + cl;
+    if constexpr (KIND == EPI_RESID) {
+      const int n = unit * NC + 16 * t + 4 * rg;
+      if (m < M && n < a.n_rows) *(f32x4*)(a.ypart + ((size_t)split * M + m) * a.n_rows + n) = y;
+    } else if constexpr (KIND == EPI_STORE) {
+      const int n = unit * NC + 16 * t + 4 * rg;
+      if (m < M && n < a.n_rows) *(f32x4_a4*)(a.out + (size_t)m * a.ldo + n) = y * scale[m];
+    } else if constexpr (SWIGLU) {
+      const int n = unit * (NC / 2) + 16 * t + 4 * rg;
+      if (m < M && n < a.n_rows) {
+        const float sc = scale[m];
+        f32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = silu_f(y[e] * sc) * (yu[e] * sc);
+        put_stacked4(a.xs_out, a.stt, m, n, o);
+      }
+    } else {
+      const int n = unit * NC + 16 * t + 4 * rg;
+      y *= m < M ? scale[m] : 0.f;
+      f32x4 z;  // (every lane takes part in the shuffles)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[e] = __shfl_xor(y[e], 32, kWave);
+      if (m < M && n < a.n_rows) qkv_store4(a, m, n, y, z);
+    }
+  };
+  auto finish = [&](int unit) {
+#pragma unroll
+    for (int m0 = 0; m0 < MT; m0 += RT) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+          if (m0 + i < MT) red[i * T + t][wave][lane] = acc[m0 + i][t];
+      __syncthreads();
+      constexpr int PF = SWIGLU ? T / 2 : T;  // outputs (or pairs) per row tile
+      for (int f = wave; f < RT * PF; f += NW) {
+        const int i = f / PF, t = f % PF;
+        if (m0 + i < MT) {
+          f32x4 y = red[i * T + t][0][lane], yu = y;
+#pragma unroll
+          for (int w = 1; w < NW; ++w) y += red[i * T + t][w][lane];
+          if constexpr (SWIGLU) {
+            yu = red[i * T + T / 2 + t][0][lane];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) yu += red[i * T + T / 2 + t][w][lane];
+          }
+          emit(unit, m0 + i, t, y, yu);
+        }
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int t = 0; t < T; ++t) acc[mt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  };
+
+  // Prologue: the row-scale partial sums are requested before the weights
+  // (loads complete in order), then both buffers.
+  constexpr int RS = (MP + NW - 1) / NW;  // scale rows per wave
+  float rs[SCALE ? RS : 1];
+  if constexpr (SCALE) {
+    const __amdgpu_buffer_rsrc_t sr = make_rsrc(a.ss_in, a.ss_in ? (uint32_t)a.n_ss * a.ss_ld * 4u : 0u);
+#pragma unroll
+    for (int r = 0; r < RS; ++r) {
+      const int m = wave + r * NW;
+      const uint32_t off = ((uint32_t)lane * a.ss_ld + m) * 4u | ((uint32_t)(m >= M || lane >= a.n_ss) << 31);
+      rs[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, off, 0, 0));
+    }
+  }
+  load(wA, xA);
+  if (total > 1) load(wB, xB);
+  if constexpr (SCALE) {
+    // s_m = 1/sqrt(sum_p ss[p][m] / K + eps): partial p in lane p % 64, fixed shuffle tree
+    for (int p0 = kWave; p0 < a.n_ss; p0 += kWave)
+#pragma unroll
+      for (int r = 0; r < RS; ++r) {
+        const int m = wave + r * NW, p = p0 + lane;
+        if (a.ss_in && m < M && p < a.n_ss) rs[r] += a.ss_in[(size_t)p * a.ss_ld + m];
+      }
+    wave_sum_n(rs);
+#pragma unroll
+    for (int r = 0; r < RS; ++r) {
+      const int m = wave + r * NW;
+      if (lane == 0 && m < MP) scale[m] = (a.ss_in && m < M) ? 1.0f / sqrtf(rs[r] / (float)K + a.eps) : 1.0f;
+    }
+  }
+
+  int q = 0, cu = u0, cb = 0;  // compute cursor
+  while (true) {
+    compute(wA, xA);
+    if (q + 2 < total) load(wA, xA);
+    if (++cb == nbat) { finish(cu); cb = 0; cu += us; }
+    if (++q >= total) break;
+    compute(wB, xB);
+    if (q + 2 < total) load(wB, xB);
+    if (++cb == nbat) { finish(cu); cb = 0; cu += us; }
+    if (++q >= total) break;
+  }
+}
+
+template <int T, int MT, int NW, int UB, int KIND>
+void launch_mt(const GemmArgs& a, int n_split, int ks_per_split, hipStream_t s) {
+  constexpr int NU = KIND == EPI_SWIGLU ? 8 * T : 16 * T;  // output columns per unit
+  const int units = (a.n_rows + NU - 1) / NU;
+  const int grid = std::min(units, std::max(1, device_compute_units() / n_split)) * n_split;
+  hipLaunchKernelGGL((gemm_bf16_rows<T, MT, NW, UB, KIND>), dim3(grid), dim3(64 * NW), 0, s, a, units, n_split,
+                     ks_per_split);
+}
+template <int T, int NW, int UB, int KIND>
+void launch_t(const GemmArgs& a, int n_split, int ks_per_split, hipStream_t s) {
+  const int MT = (a.M + 15) / 16;
+  if (MT == 2) launch_mt<T, 2, NW, UB, KIND>(a, n_split, ks_per_split, s);
+  else if (MT == 3) launch_mt<T, 3, NW, UB, KIND>(a, n_split, ks_per_split, s);
+  else launch_mt<T, 4, NW, UB, KIND>(a, n_split, ks_per_split, s);
+}
+
+// Rounds of the persistent grid that units of T tiles take, in tiles (plus
+// one for what a round costs besides its weights).
+int unit_cost(int n_tiles, int T) {
+  const int units = (n_tiles + T - 1) / T, cus = device_compute_units();
+  return (units + cus - 1) / cus * (T + 1);
+}
+
+}  // namespace
+
+hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
+  if (a.M <= kSkinnyRows || a.M > kMaxGemmRows || !a.xs || a.stt != 2 * ((a.M + 15) / 16) || a.K % 32 || a.n_rows % 16)
+    return hipErrorInvalidValue;
+  const int KS = a.K / 32, tiles = a.n_rows / 16;
+  switch (a.kind) {
+    case EPI_STORE:
+      // Larger units read x fewer times: 8 tiles unless 4 fill the CUs' rounds
+      // better (7B LM head, 40 rows: 52.6 us in 250 units of 8, 54.7 in 500 of
+      // 4) or the k loop is too short to cover a unit's reduction (K = 2048, 20
+      // rows: 31.8 us against 26.4).
+      if (KS >= 128 && unit_cost(tiles, 8) <= unit_cost(tiles, 4)) launch_t<8, 4, 1, EPI_STORE>(a, 1, KS, s);
+      else launch_t<4, 8, 1, EPI_STORE>(a, 1, KS, s);
+      break;
+    case EPI_QKV: {
+      if (a.kv.dtype != SPECDEC_BF16 || a.head_dim % 16 || a.n_seg[0] % a.head_dim || a.n_seg[1] % a.head_dim)
+        return hipErrorInvalidValue;
+      const int c1 = unit_cost(tiles, 1), c2 = unit_cost(tiles, 2), c3 = unit_cost(tiles, 3);
+      if (c3 <= c2 && c3 <= c1) launch_t<3, 8, 1, EPI_QKV>(a, 1, KS, s);
+      else if (c2 <= c1) launch_t<2, 8, 1, EPI_QKV>(a, 1, KS, s);
+      else launch_t<1, 8, 1, EPI_QKV>(a, 1, KS, s);
+      break;
+    }
+    case EPI_SWIGLU:
+      // (pairs of a gate and an up tile: 6 tiles cover three of them; the 7B
+      // shape over 40 rows: 38.1 us in 230 units of 6 tiles, 49.5 in 344 of 4)
+      if (!a.xs_out) return hipErrorInvalidValue;
+      if (unit_cost(2 * tiles, 6) <= unit_cost(2 * tiles, 4)) launch_t<6, 4, 2, EPI_SWIGLU>(a, 1, KS, s);
+      else launch_t<4, 8, 1, EPI_SWIGLU>(a, 1, KS, s);
+      break;
+    case EPI_RESID: {
+      // Few tiles (7B O and down: 256): units of 4 tiles with K split over the
+      // grid, as far as every wave of a split keeps two k-steps; else units of
+      // 2.  7B O over 40 rows: 9.8 us in 64 units x 4 splits, 11.2 in 128 x 2.
+      if (!a.ypart || !a.xs_out || !a.gain_bf16) return hipErrorInvalidValue;
+      const int cus = device_compute_units();
+      auto splits = [&](int T) {
+        return std::min({kRowsSplitMax, KS, std::max(1, cus / ((tiles + T - 1) / T))});
+      };
+      const bool four = splits(4) * 16 <= KS;
+      int n_split = four ? splits(4) : splits(2);
+      const int per = (KS + n_split - 1) / n_split;
+      n_split = (KS + per - 1) / per;
+      if (four) launch_t<4, 8, 1, EPI_RESID>(a, n_split, per, s);
+      else launch_t<2, 8, 1, EPI_RESID>(a, n_split, per, s);
+      return launch_resid_reduce(a, n_split, s);
+    }
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace specdec

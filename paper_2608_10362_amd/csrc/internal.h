@@ -58,6 +58,8 @@ template <> struct KvIndex<uint16_t> {
 // same 16-row tile, which the packed image provides (see launch_pack).
 enum EpiKind { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
 constexpr int kMaxGemmRows = 64;  // rows of x per launch of the skinny kernels (callers split larger M)
+constexpr int kSkinnyRows = 16;   // bf16 weights: passes of more rows run launch_gemm_rows (to kMaxGemmRows)
+constexpr int kRowsSplitMax = 8;  // K splits of its residual GEMMs (partials in ypart: kRowsSplitMax * M * n_rows)
 // Passes of more than kMaxGemmRows bf16 rows run the wide kernel in launches of
 // up to gemm_launch_rows() rows; residual GEMMs there split K over the grid
 // and need ypart = wide_ypart_floats(n_rows) floats.
@@ -91,9 +93,10 @@ struct GemmArgs {
   // wide passes
   int wide;               // 1: the whole pass has more than kMaxGemmRows rows (set by the caller for every launch)
   float* ypart;           // RESID: split-K partial sums, wide_ypart_floats(n_rows) floats
-  // Passes of at most 16 rows, bf16 weights: x also as a stacked operand
-  // (put_stacked, stt fragments per k-step), read instead of x when xs is set;
-  // RESID and SwiGLU epilogues also write their output stacked into xs_out.
+  // Passes of at most kMaxGemmRows rows, bf16 weights: x also as a stacked
+  // operand (put_stacked, stt fragments per k-step), read instead of x when xs
+  // is set; RESID and SwiGLU epilogues write their output stacked into xs_out
+  // (over more than kSkinnyRows rows in place of xg_out and out).
   const uint16_t* xs;
   uint16_t* xs_out;
   int stt;
@@ -118,7 +121,11 @@ size_t packed_int4_scale_bytes(int N, int K);
 hipError_t launch_pack_int4(const void* src, void* frag, void* scale, int N, int K, int rope_hd, hipStream_t s);
 // Number of row blocks the launcher uses for this GEMM (for ss partial counts)
 // in a pass of M rows.
-int gemm_row_blocks(int dtype, int kind, int n_rows, int M);
+int gemm_row_blocks(int dtype, int kind, int n_rows, int M, bool q4);
+// bf16 GEMMs of 17 to 64 rows over the stacked operand (gemm_rows.hip).
+hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s);
+// Ordered sum of a residual GEMM's split-K partials (ypart), residual add, next RMSNorm input and its sums of squares.
+hipError_t launch_resid_reduce(const GemmArgs& a, int n_split, hipStream_t s);
 hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);
 
 // ------------------------------------------------------------------ rows / embedding
@@ -142,7 +149,7 @@ struct RowsArgs {
   float* h;               // out [M, d]
   float* xg;              // out [M, d] h * gain
   float* ss;              // out [M] sum of squares of h rows
-  uint16_t* xs;           // out (or null): xg as a stacked operand (put_stacked), stt fragments per k-step
+  uint16_t* xs;           // or null: xg goes out as the stacked operand (put_stacked, stt fragments per k-step) only
   int stt;
 };
 hipError_t launch_rows_embed(int dtype, const RowsArgs& a, hipStream_t s);
@@ -162,7 +169,7 @@ struct AttnArgs {
   float* o_part;         // [M, h, n_split, hd]
   float* ml_part;        // [M, h, n_split, 2]
   float* o;              // [M, h hd]
-  uint16_t* xs;          // or null: o also as a stacked operand (put_stacked), stt fragments per k-step
+  uint16_t* xs;          // or null: o goes out as the stacked operand (put_stacked, stt fragments per k-step) only
   int stt;
   int32_t* status;
   int seq_bound;         // 1: bound each sequence's keys by its own last row (batches of several sequences)

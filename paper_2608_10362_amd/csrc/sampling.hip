@@ -165,8 +165,8 @@ __global__ __launch_bounds__(256) void rows_embed_kernel(RowsArgs a) {
     const float v = Storage<ET>::load(e + k);
     h[k] = v;
     const float xv = v * Storage<ET>::load(gn + k);
-    xg[k] = xv;
     if (a.xs) put_stacked(a.xs, a.stt, r, k, xv);
+    else xg[k] = xv;
     ss += v * v;
   }
   ss = block_sum(ss, red);

@@ -1,0 +1,35 @@
+"""Passes of 17 to 128 rows (the streaming GEMMs over the stacked operand)
+against the float64 oracle, at the edges of their row tiles, on shapes whose
+tile counts leave remainders in every unit size and fewer k-steps than waves,
+and at the 7B widths that take the large units."""
+import numpy as np
+import pytest
+
+from paper_2608_10362_amd import synth
+from tests.gpu_util import log
+from tests.test_gpu_model import _bf16_case
+
+pytestmark = pytest.mark.gpu
+
+# 20 Q|K|V tiles, 12 residual tiles, 22 gate / up pairs, 31 head tiles; K of 192 (6 k-steps) and 352 (11)
+ODD = synth.ModelShape(2, 192, 6, 2, 32, 352, 496)
+# float32-accuracy products (2^-17 per product) behind keys and values stored in bf16: single values one
+# bf16 unit apart (2^-8) move the logits by 1e-5 to 5e-5 of their norm
+REL = 2e-4
+
+
+def _rows_case(shape, n_layers, lengths, g, seed):
+    got, ref, _ = _bf16_case(shape, n_layers, lengths, g, seed=seed, return_logits=True)
+    rel = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    log(f"rows {len(lengths) * (g + 1)}: relative error {rel:.3g}")
+    assert rel < REL
+
+
+@pytest.mark.parametrize("B,g", [(17, 0), (4, 7), (11, 2), (6, 7), (7, 6), (8, 7)])
+def test_odd_shape_rows(B, g):
+    _rows_case(ODD, 2, [1 + (37 * b) % 90 for b in range(B)], g, seed=B)
+
+
+@pytest.mark.parametrize("B,g", [(3, 5), (8, 4), (8, 6), (16, 3)])
+def test_7b_width_rows(B, g):
+    _rows_case(synth.LLAMA_7B, 1, [40 + 13 * b for b in range(B)], g, seed=B)
