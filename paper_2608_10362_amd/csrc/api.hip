@@ -111,10 +111,10 @@ WsLayout ws_layout(const specdec_model_desc* d, int max_rows, int max_ctx) {
   const size_t R = (size_t)max_rows;
   const int hd = d->head_dim, H = d->n_heads, G = d->n_kv_heads;
   // (passes of up to max_rows rows: the skinny and, above kMaxGemmRows, the wide partial counts)
-  w.ss_parts = std::max(1, gemm_row_blocks(d->dtype, EPI_RESID, d->d_model, std::min(max_rows, kMaxGemmRows), true));
+  w.ss_parts = std::max(1, gemm_row_blocks(d->dtype, EPI_RESID, d->d_model, std::min(max_rows, kSkinnyRows)));
   const bool wide = gemm_wide(d->dtype, max_rows);
   if (d->dtype == SPECDEC_BF16)
-    w.ss_parts = std::max(w.ss_parts, gemm_row_blocks(d->dtype, EPI_RESID, d->d_model, max_rows, false));
+    w.ss_parts = std::max(w.ss_parts, gemm_row_blocks(d->dtype, EPI_RESID, d->d_model, max_rows));
   w.chunk = attention_chunk(d->dtype, hd);
   w.n_split = (max_ctx + w.chunk - 1) / w.chunk;
   size_t off = 0;
@@ -301,13 +301,14 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   ra.rope_cs = m->rope_cs;
   ra.h = m->h;
   ra.ss = m->ss;
-  // Passes of at most 64 rows on bf16 weights hand x from kernel to kernel as a
+  // Passes of at most 64 rows (INT4 weights: of 17 to 64) hand x from kernel to kernel as a
   // stacked operand (put_stacked): the GEMMs then read 16-byte fragments (one
   // per k-step over at most 8 rows, two per 16 rows above) instead of float32
   // rows which each would convert again.
   const bool q4 = m->wfmt == SPECDEC_WEIGHTS_INT4;
-  const bool stk = dt == SPECDEC_BF16 && !q4 && M <= kMaxGemmRows && m->xs_d;
+  const bool stk = dt == SPECDEC_BF16 && M <= kMaxGemmRows && (!q4 || M > kSkinnyRows) && m->xs_d;
   const int stt = M <= 8 ? 1 : 2 * ((M + 15) / 16);
+  const bool head_stk = q4 && M <= kSkinnyRows;  // (INT4 layers convert float32 x themselves; the bf16 LM head does not)
   ra.xs = stk ? m->xs_d : nullptr;
   ra.stt = stt;
   {
@@ -331,7 +332,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   base.ypart = m->ypart;
   base.stt = stt;
   int n_ss = 1;
-  const int n_resid_blocks = gemm_row_blocks(dt, EPI_RESID, d.d_model, M, q4);
+  const int n_resid_blocks = gemm_row_blocks(dt, EPI_RESID, d.d_model, M);
 
   AttnArgs at{};
   at.rows = m->rows;
@@ -438,6 +439,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
     dn.gain_out = l + 1 < m->n_layers ? m->attn_norm[l + 1] : m->final_norm;
     if (q4) { dn.q4 = 1; dn.wscale[0] = m->sd[l]; }
     if (stk) { dn.xs = m->xs_f; dn.xs_out = m->xs_d; }
+    else if (head_stk && l + 1 == m->n_layers) dn.xs_out = m->xs_d;
     {
       Timed t(SPECDEC_KERNEL_DOWN, s);
       SD_TRY(gemm_rows(dt, dn, M, s));
@@ -449,7 +451,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   hd_.x = m->xg; hd_.ldx = d.d_model; hd_.ss_in = m->ss; hd_.n_ss = n_ss;
   hd_.K = d.d_model; hd_.w[0] = m->lm_head; hd_.n_seg[0] = d.vocab; hd_.n_rows = d.vocab;
   hd_.kind = EPI_STORE; hd_.out = logits; hd_.ldo = d.vocab;
-  if (stk) hd_.xs = m->xs_d;
+  if (stk || head_stk) hd_.xs = m->xs_d;
   {
     Timed t(SPECDEC_KERNEL_LM_HEAD, s);
     SD_TRY(gemm_rows(dt, hd_, M, s));

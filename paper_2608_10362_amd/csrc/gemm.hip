@@ -174,7 +174,7 @@ struct Q4Frag {
 // MFMA operand layout (16x16x32): lane l holds A[l%16][8(l/16)+j] (x rows),
 // B[8(l/16)+j][l%16] (= W[n0 + l%16][k0 + 8(l/16) + j]: 16 bytes at lane*16 of
 // the packed 1 KB fragment), D[4(l/16)+r][l%16].
-template <int T, int MT, int UB, bool PIPE, int KIND, bool Q4 = false, int XS = 0>
+template <int T, int UB, int KIND, bool Q4 = false, int XS = 0>
 __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n_tiles) {
   // Q4: INT4 weights (Q4Frag).  A code q is fed to the MFMA as the bf16 value
   // 136 + q (bits 0x4300 | (q + 8): two byte permutes and an OR per four
@@ -190,7 +190,8 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
   // cross-wave sums, the same arithmetic for either count of fragments.
   // XS = 3: XS = 1 with each wave's x fragments (at most 8 k-steps, K <= 4096)
   // fetched once into LDS and read from there for every unit of the block.
-  static_assert(XS == 0 || (MT == 1 && !Q4), "stacked x: bf16 weights, one row tile");
+  static_assert(XS == 0 || !Q4, "stacked x: bf16 weights");
+  constexpr int MT = 1;  // (at most kSkinnyRows rows)
   using WReg = std::conditional_t<Q4, Q4Frag, u32x4>;
   constexpr bool XL = XS == 3;
   constexpr int XF = XL ? 1 : XS;   // stacked fragments per k-step
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
   constexpr int NF = T * MT;              // accumulator fragments per wave
   constexpr int RR = XL ? 1 : (NF <= 2 ? NF : 2);  // fragments reduced per LDS round (XL: LDS goes to x)
   constexpr bool QKV = KIND == EPI_QKV;
-  constexpr int E = (MP * NC + kMfmaThreads - 1) / kMfmaThreads;  // epilogue elements per thread
+  static_assert(MP * NC <= kMfmaThreads, "one epilogue element per thread");
   __shared__ float red[RR][kMfmaWaves][kWave][4];
   __shared__ u32x4 s_xl[XL ? kMfmaWaves : 1][XL ? 8 : 1][kWave];  // XL: wave w's x fragments, k-steps w + 16j
   __shared__ float yfin[MP][NC + 1];
@@ -243,12 +244,10 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
   f32x4 xA[UB][MA][2], xB[UB][MA][2];  // (stacked x: [u][fragment][0] holds the fragment's 16 bytes)
   // Residual epilogue inputs (old h and the next RMSNorm gain) of the tile whose
   // last batch sits in the matching register buffer, fetched with that batch.
-  // (Only when every thread has at most one epilogue element; larger row
-  // counts read them in the epilogue, keeping the registers for the loads.)
-  constexpr bool PRE = KIND == EPI_RESID && E == 1;
+  constexpr bool PRE = KIND == EPI_RESID;
   struct Pre {
-    float h[E];
-    uint32_t g[E];  // bf16 bits of the gain (bf16 models only run this kernel)
+    float h;
+    uint32_t g;  // bf16 bits of the gain (bf16 models only run this kernel)
   } pA, pB;
   auto epi_fetch = [&](int q, Pre& p) {
     if constexpr (PRE) {
@@ -257,14 +256,11 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
       const int tile = blockIdx.x + (q / nbat) * gridDim.x;
       const __amdgpu_buffer_rsrc_t hr = make_rsrc(a.out, (uint32_t)a.M * a.ldo * 4u);
       const __amdgpu_buffer_rsrc_t gr = make_rsrc(a.gain_out, (uint32_t)a.n_rows * 2u);
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const int i = tid + e * kMfmaThreads, m = i / NC, n = tile * NC + i % NC;
-        const uint32_t bad = (uint32_t)(n >= a.n_rows) << 31;  // (rows m >= M fall outside hr)
-        p.h[e] = __builtin_bit_cast(
-            float, __builtin_amdgcn_raw_buffer_load_b32(hr, (((uint32_t)m * a.ldo + n) * 4u) | bad, 0, 0));
-        p.g[e] = __builtin_amdgcn_raw_buffer_load_b16(gr, ((uint32_t)n * 2u) | bad, 0, 0);
-      }
+      const int m = tid / NC, n = tile * NC + tid % NC;
+      const uint32_t bad = (uint32_t)(n >= a.n_rows) << 31;  // (rows m >= M fall outside hr)
+      p.h = __builtin_bit_cast(
+          float, __builtin_amdgcn_raw_buffer_load_b32(hr, (((uint32_t)m * a.ldo + n) * 4u) | bad, 0, 0));
+      p.g = __builtin_amdgcn_raw_buffer_load_b16(gr, ((uint32_t)n * 2u) | bad, 0, 0);
     }
   };
   // Loads go through buffer descriptors: an offset past the descriptor's range
@@ -415,9 +411,9 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
       if (m < M) {
         float hv = 0.f;
         if (n < a.n_rows) {
-          hv = p.h[0] + yfin[m][c];
+          hv = p.h + yfin[m][c];
           a.out[(size_t)m * a.ldo + n] = hv;
-          const float xv = hv * bf16_bits_to_f32((uint16_t)p.g[0]);
+          const float xv = hv * bf16_bits_to_f32((uint16_t)p.g);
           a.xg_out[(size_t)m * a.ldo + n] = xv;
           if (a.xs_out) put_stacked(a.xs_out, a.stt, m, n, xv);
         }
@@ -501,11 +497,10 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
       }
     }
   }
-  constexpr bool HOIST = QKV && MT <= 2;  // (the 64-row tables would cost spills)
-  constexpr int CS_E = HOIST ? MP * 128 / kMfmaThreads : 1;  // table entries per thread
+  constexpr int CS_E = QKV ? MP * 128 / kMfmaThreads : 1;  // table entries per thread
   float cs_v[CS_E];
   RowDesc rd_v{0, 0, 0, 0};
-  if constexpr (HOIST) {
+  if constexpr (QKV) {
     const __amdgpu_buffer_rsrc_t cr = make_rsrc(a.rope_cs, (uint32_t)a.M * a.head_dim * 4u);
 #pragma unroll
     for (int e = 0; e < CS_E; ++e) {
@@ -531,7 +526,7 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
     load(0, wA, xA);
     epi_fetch(0, pA);
   }
-  if (PIPE && total > 1) {
+  if (total > 1) {
     load(1, wB, xB);
     epi_fetch(1, pB);
   }
@@ -559,51 +554,29 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
       if (lane == 0 && m < MP) scale[m] = (a.ss_in && m < a.M) ? 1.0f / sqrtf(t[r] / (float)a.K + a.eps) : 1.0f;
     }
   }
-  if constexpr (HOIST) {
+  if constexpr (QKV) {
 #pragma unroll
     for (int e = 0; e < CS_E; ++e) {
       const int i = tid + e * kMfmaThreads;
       s_cs[i / 128][i % 128] = cs_v[e];
     }
     if (tid < MP) s_rows[tid] = rd_v;
-  } else if constexpr (QKV) {
-    for (int i = tid; i < MP; i += kMfmaThreads) s_rows[i] = i < a.M ? a.rows[i] : RowDesc{0, 0, 0, 0};
-    for (int i = tid; i < MP * 128; i += kMfmaThreads) {
-      const int m = i / 128, j = i % 128;
-      s_cs[m][j] = (m < a.M && j < a.head_dim) ? a.rope_cs[(size_t)m * a.head_dim + j] : 0.f;
-    }
   }
-  if (PIPE) {
-    // A buffer is refilled as soon as its batch has been multiplied, before the
-    // tile's reduction and epilogue (which use only the accumulators, LDS and
-    // the epilogue inputs fetched with that batch): two batches stay in flight
-    // across tile boundaries.
-    // (Not for the INT4 three-tile kernels over more than 16 rows: the longer
-    // live ranges there cost spills.)
-    constexpr bool EARLY = !(Q4 && MT >= 2);
-    while (q < total) {
-      compute(wA, xA, q);
-      if (EARLY && q + 2 < total) load(q + 2, wA, xA);
-      finish(q, pA);
-      if (!EARLY && q + 2 < total) load(q + 2, wA, xA);
-      if (q + 2 < total) epi_fetch(q + 2, pA);
-      if (++q >= total) break;
-      compute(wB, xB, q);
-      if (EARLY && q + 2 < total) load(q + 2, wB, xB);
-      finish(q, pB);
-      if (!EARLY && q + 2 < total) load(q + 2, wB, xB);
-      if (q + 2 < total) epi_fetch(q + 2, pB);
-      ++q;
-    }
-  } else {
-    for (; q < total; ++q) {
-      if (q > 0) {
-        load(q, wA, xA);
-        epi_fetch(q, pA);
-      }
-      compute(wA, xA, q);
-      finish(q, pA);
-    }
+  // A buffer is refilled as soon as its batch has been multiplied, before the
+  // tile's reduction and epilogue (which use only the accumulators, LDS and
+  // the epilogue inputs fetched with that batch): two batches stay in flight
+  // across tile boundaries.
+  while (q < total) {
+    compute(wA, xA, q);
+    if (q + 2 < total) load(q + 2, wA, xA);
+    finish(q, pA);
+    if (q + 2 < total) epi_fetch(q + 2, pA);
+    if (++q >= total) break;
+    compute(wB, xB, q);
+    if (q + 2 < total) load(q + 2, wB, xB);
+    finish(q, pB);
+    if (q + 2 < total) epi_fetch(q + 2, pB);
+    ++q;
   }
 }
 
@@ -941,7 +914,9 @@ __global__ __launch_bounds__(kQ4Threads) void gemm_q4_lds(GemmArgs a, int n_unit
       if (n < a.n_rows) {
         hv = pre_h + yfin[0][m][c];
         a.out[(size_t)m * a.ldo + n] = hv;
-        a.xg_out[(size_t)m * a.ldo + n] = hv * bf16_bits_to_f32((uint16_t)pre_g);
+        const float xv = hv * bf16_bits_to_f32((uint16_t)pre_g);
+        if (a.xs_out) put_stacked(a.xs_out, a.stt, m, n, xv);
+        else a.xg_out[(size_t)m * a.ldo + n] = xv;
       }
       yfin[0][m][c] = hv;
     }
@@ -1663,20 +1638,6 @@ __global__ __launch_bounds__(256) void gemm_f32_vector(GemmArgs a) {
   epilogue<NC, KIND, 256>(a, blk, yfin, scale);
 }
 
-// k-steps per register buffer and whether two buffers are kept (the next
-// batch's loads in flight while the current one is multiplied): chosen so W
-// and x fragments stay within the 128 VGPRs a wave of a 16-wave block may use.
-template <int T, int MT> struct Batch;
-template <> struct Batch<1, 1> { static constexpr int UB = 3; static constexpr bool PIPE = true; };
-template <> struct Batch<1, 2> { static constexpr int UB = 2; static constexpr bool PIPE = true; };
-template <> struct Batch<1, 4> { static constexpr int UB = 2; static constexpr bool PIPE = false; };
-template <> struct Batch<2, 1> { static constexpr int UB = 2; static constexpr bool PIPE = true; };
-template <> struct Batch<2, 2> { static constexpr int UB = 1; static constexpr bool PIPE = true; };
-template <> struct Batch<2, 4> { static constexpr int UB = 1; static constexpr bool PIPE = false; };
-template <> struct Batch<3, 1> { static constexpr int UB = 1; static constexpr bool PIPE = true; };
-template <> struct Batch<3, 2> { static constexpr int UB = 1; static constexpr bool PIPE = true; };
-template <> struct Batch<3, 4> { static constexpr int UB = 1; static constexpr bool PIPE = false; };
-
 int compute_units() {
   static int cus = [] {
     int dev = 0, n = 0;
@@ -1688,58 +1649,43 @@ int compute_units() {
   return cus;
 }
 
-// The residual and QKV epilogues keep more live registers: one k-step per
-// buffer for single-tile units over more than 16 rows.
-template <int T, int MT, int KIND> struct BatchK {
-  static constexpr bool tight = (KIND == EPI_RESID || KIND == EPI_QKV) && T == 1 && MT >= 2;
-  static constexpr int UB = tight ? 1 : Batch<T, MT>::UB;
-  static constexpr bool PIPE = Batch<T, MT>::PIPE;
+// k-steps per register buffer: two buffers' W and x fragments stay within the
+// 128 VGPRs a wave of a 16-wave block may use.  (INT4 weights: as many, with a
+// k-step's fragment a quarter of the bf16 one.  Single-tile units reading one
+// stacked x fragment per k-step, from memory or LDS, have the registers for
+// four: measured 9.9 -> 9.2 us for the 7B O projection; two fragments per
+// k-step or float32 x would spill.)
+template <int T, bool Q4, int XS> struct Batch {
+  static constexpr int UB = T == 1 ? (!Q4 && (XS == 1 || XS == 3) ? 4 : 3) : (T == 2 ? 2 : 1);
 };
 
-// (INT4 weights: a k-step's fragment is a quarter of the bf16 one, so a buffer
-// holds more k-steps to keep as many weight bytes in flight.)
-template <int T, int MT, int KIND, bool Q4> struct BatchQ {
-  static constexpr int UB = Q4 ? (MT == 1 ? (T == 1 ? 3 : (T == 2 ? 2 : 1)) : 1) : BatchK<T, MT, KIND>::UB;
-  static constexpr bool PIPE_Q = !(Q4 && T == 3 && MT == 4);
-  static constexpr bool PIPE = BatchK<T, MT, KIND>::PIPE && PIPE_Q;
-};
-
-// (Single-tile units reading one stacked x fragment per k-step, from memory or
-// LDS, have the registers for four k-steps per buffer: measured 9.9 -> 9.2 us
-// for the 7B O projection.  Two fragments per k-step or float32 x would spill.)
-template <int T, int MT, int KIND, bool Q4, int XS> struct BatchX {
-  static constexpr int UB = (!Q4 && T == 1 && MT == 1 && (XS == 1 || XS == 3)) ? 4 : BatchQ<T, MT, KIND, Q4>::UB;
-  static constexpr bool PIPE = BatchQ<T, MT, KIND, Q4>::PIPE;
-};
-
-template <int T, int MT, int KIND, bool Q4 = false, int XS = 0>
-void launch_mfma_mt(const GemmArgs& a, int tiles, hipStream_t s) {
+template <int T, int KIND, bool Q4 = false, int XS = 0>
+void launch_mfma_x(const GemmArgs& a, int tiles, hipStream_t s) {
   const int grid = tiles < compute_units() ? tiles : compute_units();
-  hipLaunchKernelGGL(
-      (gemm_bf16_mfma<T, MT, BatchX<T, MT, KIND, Q4, XS>::UB, BatchX<T, MT, KIND, Q4, XS>::PIPE, KIND, Q4, XS>),
-      dim3(grid), dim3(kMfmaThreads), 0, s, a, tiles);
+  hipLaunchKernelGGL((gemm_bf16_mfma<T, Batch<T, Q4, XS>::UB, KIND, Q4, XS>), dim3(grid), dim3(kMfmaThreads), 0, s, a,
+                     tiles);
 }
 
 template <int T, int KIND, bool Q4 = false>
 hipError_t launch_mfma_t(const GemmArgs& a, int blocks, hipStream_t s) {
-  const int MT = (a.M + 15) / 16;
+  if (a.M > kSkinnyRows) return hipErrorInvalidValue;
   if constexpr (!Q4) {
-    if (a.xs) {  // stacked x (passes of at most 16 rows)
-      if (a.stt != (a.M <= 8 ? 1 : 2) || a.M > 16) return hipErrorInvalidValue;
+    if (a.xs) {
+      if (a.stt != (a.M <= 8 ? 1 : 2)) return hipErrorInvalidValue;
       // (x held in LDS: measured faster for the store, SwiGLU and residual GEMMs, slower for Q|K|V, whose
       // epilogue tables then leave room for one reduction fragment per round only)
       if (KIND != EPI_QKV && a.stt == 1 && (a.K + 31) / 32 <= 8 * kMfmaWaves)
-        launch_mfma_mt<T, 1, KIND, false, 3>(a, blocks, s);
-      else if (a.stt == 1) launch_mfma_mt<T, 1, KIND, false, 1>(a, blocks, s);
-      else launch_mfma_mt<T, 1, KIND, false, 2>(a, blocks, s);
+        launch_mfma_x<T, KIND, false, 3>(a, blocks, s);
+      else if (a.stt == 1) launch_mfma_x<T, KIND, false, 1>(a, blocks, s);
+      else launch_mfma_x<T, KIND, false, 2>(a, blocks, s);
       return hipGetLastError();
     }
   }
-  if (MT <= 1) launch_mfma_mt<T, 1, KIND, Q4>(a, blocks, s);
-  else if (MT <= 2) launch_mfma_mt<T, 2, KIND, Q4>(a, blocks, s);
-  else if (MT <= 4) launch_mfma_mt<T, 4, KIND, Q4>(a, blocks, s);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  if constexpr (Q4 || KIND == EPI_STORE) {  // (float32 x: INT4 layers, and the LM head behind them)
+    launch_mfma_x<T, KIND, Q4>(a, blocks, s);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 }
 
 // 16-row tiles per work unit of the bf16 kernel.  More tiles per unit mean
@@ -1871,8 +1817,8 @@ hipError_t launch_resid_reduce(const GemmArgs& a, int n_split, hipStream_t s) {
   return hipGetLastError();
 }
 
-int gemm_row_blocks(int dtype, int kind, int n_rows, int M, bool q4) {
-  if (kind == EPI_RESID && (gemm_wide(dtype, M) || (dtype == SPECDEC_BF16 && !q4 && M > kSkinnyRows))) return (n_rows + kWideCols - 1) / kWideCols;
+int gemm_row_blocks(int dtype, int kind, int n_rows, int M) {
+  if (kind == EPI_RESID && dtype == SPECDEC_BF16 && M > kSkinnyRows) return (n_rows + kWideCols - 1) / kWideCols;
   if (dtype == SPECDEC_BF16) {
     int nc = 16 * mfma_tiles(kind, n_rows);
     int per = kind == EPI_SWIGLU ? nc / 2 : nc;
@@ -2088,8 +2034,8 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
     return launch_wide(a, s);
   }
   if (a.M > kMaxGemmRows) return hipErrorInvalidValue;
-  if (a.xs && a.M > kSkinnyRows) return dtype == SPECDEC_BF16 && !a.q4 ? launch_gemm_rows(a, s) : hipErrorInvalidValue;
-  const int blocks = gemm_row_blocks(dtype, a.kind, a.n_rows, a.M, a.q4 != 0);
+  if (dtype == SPECDEC_BF16 && a.M > kSkinnyRows) return launch_gemm_rows(a, s);
+  const int blocks = gemm_row_blocks(dtype, a.kind, a.n_rows, a.M);
   if (a.q4) {  // INT4 layer weights (passes of at most 64 rows)
     if (dtype != SPECDEC_BF16 || (a.K % 32) != 0) return hipErrorInvalidValue;
     if (a.kind == EPI_RESID && !a.gain_bf16) return hipErrorInvalidValue;
@@ -2098,11 +2044,7 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
       return hipErrorInvalidValue;
     const hipError_t e = launch_q4_lds(a, s);
     if (e != hipErrorNotSupported) return e;
-    // (Q|K|V over more than 32 rows: one tile per unit, the registers going to
-    // the row tiles; the residual GEMMs keep mfma_tiles' count, which their
-    // RMSNorm partials follow)
-    const int T = a.M > 32 && a.kind == EPI_QKV ? 1 : mfma_tiles(a.kind, a.n_rows);
-    const int units = a.kind == EPI_QKV ? (a.n_rows + 16 * T - 1) / (16 * T) : blocks;
+    const int T = mfma_tiles(a.kind, a.n_rows);
     switch (a.kind) {
       case EPI_RESID:
         if (!a.gain_bf16) return hipErrorInvalidValue;
@@ -2113,9 +2055,9 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
       case EPI_QKV:
         if (a.kv.dtype != SPECDEC_BF16 || a.head_dim % 16 || a.n_seg[0] % a.head_dim || a.n_seg[1] % a.head_dim)
           return hipErrorInvalidValue;
-        return T == 1 ? launch_mfma_t<1, EPI_QKV, true>(a, units, s)
-                      : (T == 2 ? launch_mfma_t<2, EPI_QKV, true>(a, units, s)
-                                : launch_mfma_t<3, EPI_QKV, true>(a, units, s));
+        return T == 1 ? launch_mfma_t<1, EPI_QKV, true>(a, blocks, s)
+                      : (T == 2 ? launch_mfma_t<2, EPI_QKV, true>(a, blocks, s)
+                                : launch_mfma_t<3, EPI_QKV, true>(a, blocks, s));
       default: return hipErrorInvalidValue;
     }
   }

@@ -15,6 +15,20 @@ namespace specdec {
 
 namespace {
 
+// One k-step's INT4 code word (8 columns of the lane's row, column e in bits
+// 4e..4e+3) as bf16 operands 24 + q in column order: the sign bit flipped makes
+// a nibble q + 8, which as the top mantissa bits of 16.0 (0x4180 | (q + 8) << 3)
+// is 16 + (q + 8).
+__device__ __forceinline__ bf16x8 q4_operand24(uint32_t w) {
+  const uint32_t c = w ^ 0x88888888u, lo = c << 3, hi = c >> 1;  // even / odd columns' nibbles at bits 3..6 of their byte
+  u32x4 v;
+  v[0] = (__builtin_amdgcn_perm(hi, lo, 0x0c040c00u) & 0x00780078u) | 0x41804180u;
+  v[1] = (__builtin_amdgcn_perm(hi, lo, 0x0c050c01u) & 0x00780078u) | 0x41804180u;
+  v[2] = (__builtin_amdgcn_perm(hi, lo, 0x0c060c02u) & 0x00780078u) | 0x41804180u;
+  v[3] = (__builtin_amdgcn_perm(hi, lo, 0x0c070c03u) & 0x00780078u) | 0x41804180u;
+  return __builtin_bit_cast(bf16x8, v);
+}
+
 // Block = NW waves, a work unit = T tiles of 16 weight rows over a range of
 // k-steps; the unit's k-steps are dealt out to the waves (wave w: w, w + NW,
 // ...) and every wave holds the whole unit's T x MT accumulator tiles in
@@ -27,7 +41,12 @@ namespace {
 // The weights are the A operand: D[4 (l/16) + r][l % 16] is weight row 4
 // (l/16) + r, x row l % 16, so a lane ends with four consecutive columns of
 // one row and stores them at once; a RoPE partner (column ^ 8) is lane ^ 32.
-template <int T, int MT, int NW, int UB, int KIND>
+// Q4 (INT4 weights): a batch is one group of 128 columns, its codes one 1 KB
+// block per tile and its x the fragments of four k-steps (UB = 4).  A code q
+// is fed to the products as the bf16 value 24 + q (q4_operand24), the bias is
+// cancelled by the product of the same x with -24, shared by the unit's tiles,
+// and a group's sum is multiplied by the row's group scale in float32.
+template <int T, int MT, int NW, int UB, int KIND, bool Q4 = false>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_units, int n_split, int ks_per_split) {
   constexpr int NTH = 64 * NW, NC = 16 * T, MP = 16 * MT, NF = T * MT, XF = 2 * MT;
   constexpr bool SCALE = KIND != EPI_RESID, SWIGLU = KIND == EPI_SWIGLU;
@@ -39,10 +58,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int K = a.K, KS = K / 32, M = a.M;
+  const int KG = (K + 127) / 128;  // (Q4: groups)
   const int split = (int)blockIdx.x % n_split, u0 = (int)blockIdx.x / n_split, us = (int)gridDim.x / n_split;
-  const int ks_begin = split * ks_per_split, n_k = min(KS, ks_begin + ks_per_split) - ks_begin;
+  const int ks_begin = split * ks_per_split, n_k = min(Q4 ? KG : KS, ks_begin + ks_per_split) - ks_begin;
   const int my_ks = n_k > wave ? (n_k - wave + NW - 1) / NW : 0;
-  const int nbat = max(1, (my_ks + UB - 1) / UB);
+  const int nbat = Q4 ? max(1, my_ks) : max(1, (my_ks + UB - 1) / UB);  // (Q4: "k-steps" of the range are groups)
   const int my_units = (n_units - u0 + us - 1) / us;
   const int total = my_units * nbat;
 
@@ -51,48 +71,111 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int t = 0; t < T; ++t) acc[mt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-  u32x4 wA[UB][T], wB[UB][T], xA[UB][XF], xB[UB][XF];
+  constexpr int WB = Q4 ? 1 : UB;  // weight pieces per tile and batch
+  u32x4 wA[WB][T], wB[WB][T], xA[UB][XF], xB[UB][XF];
+  u32x2 sA[Q4 ? T : 1], sB[Q4 ? T : 1];  // Q4: bf16 scales of the lane's four weight rows
 
   // (the lanes of rows past M read nothing and hold zeros)
   const uint32_t xlast = (uint32_t)(16 * (MT - 1) + (lane & 15) >= M) << 31;
   const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.xs, (uint32_t)KS * XF * 1024u);
   int lu = u0, lb = 0;  // load cursor: unit, batch
-  auto load = [&](u32x4 (&wv)[UB][T], u32x4 (&xv)[UB][XF]) {
-    __amdgpu_buffer_rsrc_t wr[T];
+  auto load = [&](u32x4 (&wv)[WB][T], u32x4 (&xv)[UB][XF], u32x2 (&sv)[Q4 ? T : 1]) {
+    if constexpr (Q4) {
+      const int i = min(lb, max(my_ks - 1, 0));
+      const uint32_t gr = (uint32_t)(ks_begin + wave + i * NW);
+      const uint32_t bad = (uint32_t)(lb >= my_ks) << 31;
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      bool ok;
-      const uint16_t* base = weight_tile(a, KIND, lu, NC, t, KS, ok);
-      wr[t] = make_rsrc(base, ok ? (uint32_t)KS * 1024u : 0u);
-    }
+      for (int t = 0; t < T; ++t) {
+        int seg, n;
+        bool ok;
+        tile_segment(a, KIND, lu, NC, t, seg, n, ok);
+        const __amdgpu_buffer_rsrc_t wr =
+            make_rsrc((const char*)a.w[seg] + (size_t)(n / 16) * KG * 1024, ok ? (uint32_t)KG * 1024u : 0u);
+        wv[0][t] = __builtin_amdgcn_raw_buffer_load_b128(wr, (gr * 1024u + lane * 16u) | bad, 0, kNonTemporal);
+        // (a tile or group past the end reads the scales of a valid one; its x or its columns are not used)
+        sv[t] = *(const u32x2*)(a.wscale[seg] + ((size_t)(n / 16) * KG + min(gr, (uint32_t)KG - 1u)) * 16 + 4 * (lane >> 4));
+      }
 #pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      const int i = lb * UB + u;
-      const uint32_t ks = (uint32_t)(ks_begin + wave + i * NW);
-      const uint32_t bad = (uint32_t)(i >= my_ks) << 31;
-      const uint32_t woff = (ks * 1024u + lane * 16u) | bad;
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int t = 0; t < T; ++t) wv[u][t] = __builtin_amdgcn_raw_buffer_load_b128(wr[t], woff, 0, kNonTemporal);
+        for (int f = 0; f < XF; ++f) {
+          const uint32_t xoff = (((4 * gr + u) * XF + f) * 1024u + lane * 16u) | bad | (f >= XF - 2 ? xlast : 0u);
+          xv[u][f] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff, 0, 0);
+        }
+    } else {
+      __amdgpu_buffer_rsrc_t wr[T];
 #pragma unroll
-      for (int f = 0; f < XF; ++f) {
-        const uint32_t xoff = ((ks * XF + f) * 1024u + lane * 16u) | bad | (f >= XF - 2 ? xlast : 0u);
-        xv[u][f] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff, 0, 0);
+      for (int t = 0; t < T; ++t) {
+        bool ok;
+        const uint16_t* base = weight_tile(a, KIND, lu, NC, t, KS, ok);
+        wr[t] = make_rsrc(base, ok ? (uint32_t)KS * 1024u : 0u);
+      }
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int i = lb * UB + u;
+        const uint32_t ks = (uint32_t)(ks_begin + wave + i * NW);
+        const uint32_t bad = (uint32_t)(i >= my_ks) << 31;
+        const uint32_t woff = (ks * 1024u + lane * 16u) | bad;
+#pragma unroll
+        for (int t = 0; t < T; ++t) wv[u][t] = __builtin_amdgcn_raw_buffer_load_b128(wr[t], woff, 0, kNonTemporal);
+#pragma unroll
+        for (int f = 0; f < XF; ++f) {
+          const uint32_t xoff = ((ks * XF + f) * 1024u + lane * 16u) | bad | (f >= XF - 2 ? xlast : 0u);
+          xv[u][f] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff, 0, 0);
+        }
       }
     }
     if (++lb == nbat) { lb = 0; lu += us; }
   };
-  auto compute = [&](const u32x4 (&wv)[UB][T], const u32x4 (&xv)[UB][XF]) {
+  auto compute = [&](const u32x4 (&wv)[WB][T], const u32x4 (&xv)[UB][XF], const u32x2 (&sv)[Q4 ? T : 1]) {
+    if constexpr (Q4) {
+      const bf16x8 m24 = __builtin_bit_cast(bf16x8, u32x4{0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u, 0xC1C0C1C0u});
+      floatx4 pb[MT];
 #pragma unroll
-    for (int u = 0; u < UB; ++u)
+      for (int mt = 0; mt < MT; ++mt) pb[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+            pb[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m24, __builtin_bit_cast(bf16x8, xv[u][2 * mt + h]), pb[mt],
+                                                             0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        floatx4 p[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) p[mt] = pb[mt];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const bf16x8 w = q4_operand24(wv[0][t][u]);
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+              p[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, __builtin_bit_cast(bf16x8, xv[u][2 * mt + h]), p[mt], 0,
+                                                              0, 0);
+        }
+        const float s4[4] = {__uint_as_float(sv[t][0] << 16), __uint_as_float(sv[t][0] & 0xffff0000u),
+                             __uint_as_float(sv[t][1] << 16), __uint_as_float(sv[t][1] & 0xffff0000u)};
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-          for (int t = 0; t < T; ++t)
-            acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[u][t]),
-                                                                 __builtin_bit_cast(bf16x8, xv[u][2 * mt + h]),
-                                                                 acc[mt][t], 0, 0, 0);
+          for (int r = 0; r < 4; ++r) acc[mt][t][r] = fmaf(s4[r], p[mt][r], acc[mt][t][r]);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < UB; ++u)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+              acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[u][t]),
+                                                                   __builtin_bit_cast(bf16x8, xv[u][2 * mt + h]),
+                                                                   acc[mt][t], 0, 0, 0);
+    }
   };
 
   // One finished fragment: y[r] = column n + r of row m (sums over all waves).
@@ -168,8 +251,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
       rs[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, off, 0, 0));
     }
   }
-  load(wA, xA);
-  if (total > 1) load(wB, xB);
+  load(wA, xA, sA);
+  if (total > 1) load(wB, xB, sB);
   if constexpr (SCALE) {
     // s_m = 1/sqrt(sum_p ss[p][m] / K + eps): partial p in lane p % 64, fixed shuffle tree
     for (int p0 = kWave; p0 < a.n_ss; p0 += kWave)
@@ -188,31 +271,31 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
 
   int q = 0, cu = u0, cb = 0;  // compute cursor
   while (true) {
-    compute(wA, xA);
-    if (q + 2 < total) load(wA, xA);
+    compute(wA, xA, sA);
+    if (q + 2 < total) load(wA, xA, sA);
     if (++cb == nbat) { finish(cu); cb = 0; cu += us; }
     if (++q >= total) break;
-    compute(wB, xB);
-    if (q + 2 < total) load(wB, xB);
+    compute(wB, xB, sB);
+    if (q + 2 < total) load(wB, xB, sB);
     if (++cb == nbat) { finish(cu); cb = 0; cu += us; }
     if (++q >= total) break;
   }
 }
 
-template <int T, int MT, int NW, int UB, int KIND>
-void launch_mt(const GemmArgs& a, int n_split, int ks_per_split, hipStream_t s) {
+template <int T, int MT, int NW, int UB, int KIND, bool Q4>
+void launch_mt(const GemmArgs& a, int n_split, int per_split, hipStream_t s) {
   constexpr int NU = KIND == EPI_SWIGLU ? 8 * T : 16 * T;  // output columns per unit
   const int units = (a.n_rows + NU - 1) / NU;
   const int grid = std::min(units, std::max(1, device_compute_units() / n_split)) * n_split;
-  hipLaunchKernelGGL((gemm_bf16_rows<T, MT, NW, UB, KIND>), dim3(grid), dim3(64 * NW), 0, s, a, units, n_split,
-                     ks_per_split);
+  hipLaunchKernelGGL((gemm_bf16_rows<T, MT, NW, UB, KIND, Q4>), dim3(grid), dim3(64 * NW), 0, s, a, units, n_split,
+                     per_split);
 }
-template <int T, int NW, int UB, int KIND>
-void launch_t(const GemmArgs& a, int n_split, int ks_per_split, hipStream_t s) {
+template <int T, int NW, int UB, int KIND, bool Q4 = false>
+void launch_t(const GemmArgs& a, int n_split, int per_split, hipStream_t s) {
   const int MT = (a.M + 15) / 16;
-  if (MT == 2) launch_mt<T, 2, NW, UB, KIND>(a, n_split, ks_per_split, s);
-  else if (MT == 3) launch_mt<T, 3, NW, UB, KIND>(a, n_split, ks_per_split, s);
-  else launch_mt<T, 4, NW, UB, KIND>(a, n_split, ks_per_split, s);
+  if (MT == 2) launch_mt<T, 2, NW, UB, KIND, Q4>(a, n_split, per_split, s);
+  else if (MT == 3) launch_mt<T, 3, NW, UB, KIND, Q4>(a, n_split, per_split, s);
+  else launch_mt<T, 4, NW, UB, KIND, Q4>(a, n_split, per_split, s);
 }
 
 // Rounds of the persistent grid that units of T tiles take, in tiles (plus
@@ -222,11 +305,51 @@ int unit_cost(int n_tiles, int T) {
   return (units + cus - 1) / cus * (T + 1);
 }
 
+// INT4 weights: 4-wave blocks (a wave holds two groups' x and codes).
+hipError_t launch_q4(const GemmArgs& a, hipStream_t s) {
+  const int KG = (a.K + 127) / 128, tiles = a.n_rows / 16;
+  switch (a.kind) {
+    case EPI_QKV: {
+      const int c1 = unit_cost(tiles, 1), c3 = unit_cost(tiles, 3);
+      if (c3 <= c1) launch_t<3, 4, 4, EPI_QKV, true>(a, 1, KG, s);
+      else launch_t<1, 4, 4, EPI_QKV, true>(a, 1, KG, s);
+      break;
+    }
+    case EPI_SWIGLU:
+      // (6 tiles over more than 48 rows spill: 101 us against 65 for the 7B shape over 64 rows)
+      if (a.M <= 48 && unit_cost(2 * tiles, 6) <= unit_cost(2 * tiles, 4))
+        launch_t<6, 4, 4, EPI_SWIGLU, true>(a, 1, KG, s);
+      else launch_t<4, 4, 4, EPI_SWIGLU, true>(a, 1, KG, s);
+      break;
+    case EPI_RESID: {
+      const int cus = device_compute_units();
+      auto splits = [&](int T) {
+        return std::min({kRowsSplitMax, KG, std::max(1, cus / ((tiles + T - 1) / T))});
+      };
+      const bool four = splits(4) * 4 <= KG;  // (a group for each wave of a split)
+      int n_split = four ? splits(4) : splits(2);
+      const int per = (KG + n_split - 1) / n_split;
+      n_split = (KG + per - 1) / per;
+      if (four) launch_t<4, 4, 4, EPI_RESID, true>(a, n_split, per, s);
+      else launch_t<2, 4, 4, EPI_RESID, true>(a, n_split, per, s);
+      return launch_resid_reduce(a, n_split, s);
+    }
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
   if (a.M <= kSkinnyRows || a.M > kMaxGemmRows || !a.xs || a.stt != 2 * ((a.M + 15) / 16) || a.K % 32 || a.n_rows % 16)
     return hipErrorInvalidValue;
+  if (a.kind == EPI_QKV && (a.kv.dtype != SPECDEC_BF16 || a.head_dim % 16 || a.n_seg[0] % a.head_dim ||
+                            a.n_seg[1] % a.head_dim))
+    return hipErrorInvalidValue;
+  if (a.kind == EPI_SWIGLU && !a.xs_out) return hipErrorInvalidValue;
+  if (a.kind == EPI_RESID && (!a.ypart || !a.xs_out || !a.gain_bf16)) return hipErrorInvalidValue;
+  if (a.q4) return launch_q4(a, s);
   const int KS = a.K / 32, tiles = a.n_rows / 16;
   switch (a.kind) {
     case EPI_STORE:
@@ -238,8 +361,6 @@ hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
       else launch_t<4, 8, 1, EPI_STORE>(a, 1, KS, s);
       break;
     case EPI_QKV: {
-      if (a.kv.dtype != SPECDEC_BF16 || a.head_dim % 16 || a.n_seg[0] % a.head_dim || a.n_seg[1] % a.head_dim)
-        return hipErrorInvalidValue;
       const int c1 = unit_cost(tiles, 1), c2 = unit_cost(tiles, 2), c3 = unit_cost(tiles, 3);
       if (c3 <= c2 && c3 <= c1) launch_t<3, 8, 1, EPI_QKV>(a, 1, KS, s);
       else if (c2 <= c1) launch_t<2, 8, 1, EPI_QKV>(a, 1, KS, s);
@@ -249,7 +370,6 @@ hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
     case EPI_SWIGLU:
       // (pairs of a gate and an up tile: 6 tiles cover three of them; the 7B
       // shape over 40 rows: 38.1 us in 230 units of 6 tiles, 49.5 in 344 of 4)
-      if (!a.xs_out) return hipErrorInvalidValue;
       if (unit_cost(2 * tiles, 6) <= unit_cost(2 * tiles, 4)) launch_t<6, 4, 2, EPI_SWIGLU>(a, 1, KS, s);
       else launch_t<4, 8, 1, EPI_SWIGLU>(a, 1, KS, s);
       break;
@@ -257,7 +377,6 @@ hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
       // Few tiles (7B O and down: 256): units of 4 tiles with K split over the
       // grid, as far as every wave of a split keeps two k-steps; else units of
       // 2.  7B O over 40 rows: 9.8 us in 64 units x 4 splits, 11.2 in 128 x 2.
-      if (!a.ypart || !a.xs_out || !a.gain_bf16) return hipErrorInvalidValue;
       const int cus = device_compute_units();
       auto splits = [&](int T) {
         return std::min({kRowsSplitMax, KS, std::max(1, cus / ((tiles + T - 1) / T))});

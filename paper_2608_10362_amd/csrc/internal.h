@@ -121,8 +121,8 @@ size_t packed_int4_scale_bytes(int N, int K);
 hipError_t launch_pack_int4(const void* src, void* frag, void* scale, int N, int K, int rope_hd, hipStream_t s);
 // Number of row blocks the launcher uses for this GEMM (for ss partial counts)
 // in a pass of M rows.
-int gemm_row_blocks(int dtype, int kind, int n_rows, int M, bool q4);
-// bf16 GEMMs of 17 to 64 rows over the stacked operand (gemm_rows.hip).
+int gemm_row_blocks(int dtype, int kind, int n_rows, int M);
+// GEMMs of 17 to 64 rows over the stacked operand, bf16 or INT4 weights (gemm_rows.hip).
 hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s);
 // Ordered sum of a residual GEMM's split-K partials (ypart), residual add, next RMSNorm input and its sums of squares.
 hipError_t launch_resid_reduce(const GemmArgs& a, int n_split, hipStream_t s);

@@ -7,6 +7,7 @@ import pytest
 
 from paper_2608_10362_amd import synth
 from tests.gpu_util import log
+from tests.test_gpu_int4 import _int4_case
 from tests.test_gpu_model import _bf16_case
 
 pytestmark = pytest.mark.gpu
@@ -33,3 +34,14 @@ def test_odd_shape_rows(B, g):
 @pytest.mark.parametrize("B,g", [(3, 5), (8, 4), (8, 6), (16, 3)])
 def test_7b_width_rows(B, g):
     _rows_case(synth.LLAMA_7B, 1, [40 + 13 * b for b in range(B)], g, seed=B)
+
+
+# (INT4 groups of 128 columns: 192 and 352 leave a partial group, and a split or a wave without one)
+@pytest.mark.parametrize("B,g", [(17, 0), (4, 7), (11, 2), (6, 7), (7, 6), (8, 7)])
+def test_int4_odd_shape_rows(B, g):
+    _int4_case(ODD, 2, [1 + (37 * b) % 90 for b in range(B)], g, seed=B)
+
+
+@pytest.mark.parametrize("B,g", [(3, 5), (8, 4), (16, 3)])
+def test_int4_7b_width_rows(B, g):
+    _int4_case(synth.LLAMA_7B, 1, [40 + 13 * b for b in range(B)], g, seed=B)
