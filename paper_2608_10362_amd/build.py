@@ -10,7 +10,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libspecdec.so")
-SOURCES = ["api.hip", "gemm.hip", "gemm_rows.hip", "attention.hip", "sampling.hip", "stream.hip"]
+SOURCES = ["api.hip", "gemm.hip", "gemm_rows.hip", "gemm_tile.hip", "attention.hip", "sampling.hip", "stream.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -21,7 +21,7 @@ FLAGS = [
 ]
 
 
-def build(verbose: bool = False, jobs: int = 4) -> str:
+def build(verbose: bool = False, jobs: int = 6) -> str:
     """Compile every HIP source (in parallel) and link libspecdec.so; returns its path."""
     objdir = os.path.join(PKG, "_build")
     os.makedirs(objdir, exist_ok=True)

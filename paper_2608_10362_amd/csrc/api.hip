@@ -38,7 +38,8 @@ struct specdec_model {
   void* samp;  // scratch of the draft's softmax / draw kernels
   uint16_t* xs_d = nullptr;  // bf16: the stacked x operand of the d_model-column GEMMs (passes of <= 16 rows)
   uint16_t* xs_f = nullptr;  // bf16: the stacked attention output (the O projection's x), then SwiGLU output
-  float* ypart = nullptr;  // split-K partials of the wide residual GEMMs (passes of more than 64 rows)
+  float* ypart = nullptr;  // split-K partials (passes of more than 16 rows)
+  size_t ypart_floats = 0;
   uint32_t* attn_ctr = nullptr;           // bf16: the attention combine's epochs
   uint32_t* attn_cnt = nullptr;           // bf16: the one-round attention combine's arrival counters
   uint64_t* attn_ll = nullptr;            // bf16: the attention combine's tagged partial words
@@ -104,6 +105,7 @@ int elem_bytes(int dtype) { return dtype == SPECDEC_BF16 ? 2 : 4; }
 struct WsLayout {
   size_t rows, rope, h, xg, ss, qkv, qr, o_part, ml_part, o, u, logits, samp, xs_d, xs_f, ypart, ctr, cnt, ll, total;
   int ss_parts, chunk, n_split;
+  size_t ypart_floats;
 };
 
 WsLayout ws_layout(const specdec_model_desc* d, int max_rows, int max_ctx) {
@@ -122,24 +124,27 @@ WsLayout ws_layout(const specdec_model_desc* d, int max_rows, int max_ctx) {
   w.rows = take(R * sizeof(RowDesc));
   w.rope = take(R * hd * 4);
   w.h = take(R * d->d_model * 4);
-  w.xg = take(R * d->d_model * 4);
+  // (bf16 passes of more than 16 rows hand x over in the stacked operands only)
+  const bool bf16 = d->dtype == SPECDEC_BF16;
+  const size_t RF = bf16 ? std::min(R, (size_t)kSkinnyRows) : R;
+  w.xg = take(RF * d->d_model * 4);
   w.ss = take((size_t)w.ss_parts * R * 4);
-  w.qkv = take(R * (H + 2 * G) * hd * 4);
+  w.qkv = take(bf16 ? 0 : R * (H + 2 * G) * hd * 4);
   w.qr = take(R * H * hd * 4);
   w.o_part = take(R * H * (size_t)w.n_split * hd * 4);
   w.ml_part = take(R * H * (size_t)w.n_split * 2 * 4);
-  w.o = take(R * H * hd * 4);
-  w.u = take(R * d->ffn_dim * 4);
+  w.o = take(RF * H * hd * 4);
+  w.u = take(RF * d->ffn_dim * 4);
   w.logits = take(R * d->vocab * 4);
   w.samp = take(sampling_scratch_bytes(max_rows, 1, d->vocab));
   // (stacked operands: two 1 KB fragments per 32 columns and 16 rows)
-  const bool bf16 = d->dtype == SPECDEC_BF16;
-  const size_t stk_tile = bf16 ? (size_t)(std::min(max_rows, kMaxGemmRows) + 15) / 16 * 2048 : 0;
+  const size_t stk_tile = bf16 ? (R + 15) / 16 * 2048 : 0;
   w.xs_d = take((size_t)(d->d_model + 31) / 32 * stk_tile);
   w.xs_f = take((size_t)(std::max(d->ffn_dim, H * hd) + 31) / 32 * stk_tile);
   const size_t rows_part = bf16 && max_rows > kSkinnyRows
                                ? (size_t)kRowsSplitMax * std::min(max_rows, kMaxGemmRows) * d->d_model : 0;
-  w.ypart = take(std::max(rows_part, wide ? wide_ypart_floats(d->d_model) : 0) * 4);
+  w.ypart_floats = std::max(rows_part, wide ? tile_ypart_floats(d->d_model) : 0);
+  w.ypart = take(w.ypart_floats * 4);
   w.ctr = take(d->dtype == SPECDEC_BF16 ? attention_counter_count(H, G, max_rows) * 4 : 0);
   w.cnt = take(d->dtype == SPECDEC_BF16 ? attention_counter_count(H, G, max_rows) * 4 : 0);
   w.ll = take(d->dtype == SPECDEC_BF16 ? attention_ll_words(H, hd, max_rows, w.n_split) * 8 : 0);
@@ -260,6 +265,8 @@ hipError_t gemm_rows(int dtype, GemmArgs g, int M, hipStream_t s) {
     GemmArgs c = g;
     c.M = std::min(step, M - m0);
     c.x = g.x + (size_t)m0 * g.ldx;
+    if (g.xs) c.xs = g.xs + (size_t)(m0 / 16) * 1024;  // (launches of a stacked pass start at whole row tiles)
+    if (g.xs_out) c.xs_out = g.xs_out + (size_t)(m0 / 16) * 1024;
     if (g.out) c.out = g.out + (size_t)m0 * g.ldo;
     if (g.rows) c.rows = g.rows + m0;
     if (g.rope_cs) c.rope_cs = g.rope_cs + (size_t)m0 * g.head_dim;
@@ -301,12 +308,12 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   ra.rope_cs = m->rope_cs;
   ra.h = m->h;
   ra.ss = m->ss;
-  // Passes of at most 64 rows (INT4 weights: of 17 to 64) hand x from kernel to kernel as a
+  // bf16 passes (INT4 weights: of more than 16 rows) hand x from kernel to kernel as a
   // stacked operand (put_stacked): the GEMMs then read 16-byte fragments (one
   // per k-step over at most 8 rows, two per 16 rows above) instead of float32
   // rows which each would convert again.
   const bool q4 = m->wfmt == SPECDEC_WEIGHTS_INT4;
-  const bool stk = dt == SPECDEC_BF16 && M <= kMaxGemmRows && (!q4 || M > kSkinnyRows) && m->xs_d;
+  const bool stk = dt == SPECDEC_BF16 && (!q4 || M > kSkinnyRows);
   const int stt = M <= 8 ? 1 : 2 * ((M + 15) / 16);
   const bool head_stk = q4 && M <= kSkinnyRows;  // (INT4 layers convert float32 x themselves; the bf16 LM head does not)
   ra.xs = stk ? m->xs_d : nullptr;
@@ -330,6 +337,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   base.ss_ld = m->ss_ld;
   base.gain_bf16 = dt == SPECDEC_BF16;
   base.ypart = m->ypart;
+  base.ypart_floats = m->ypart_floats;
   base.stt = stt;
   int n_ss = 1;
   const int n_resid_blocks = gemm_row_blocks(dt, EPI_RESID, d.d_model, M);
@@ -373,8 +381,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
     q.n_seg[0] = H * hd; q.n_seg[1] = G * hd; q.n_seg[2] = G * hd;
     q.n_rows = (H + 2 * G) * hd; q.kind = EPI_STORE; q.out = m->qkv; q.ldo = (H + 2 * G) * hd;
     if (dt == SPECDEC_BF16) {  // RoPE, the query store and the KV append run in the GEMM epilogue
-      q.kind = EPI_QKV;  // (q.out stays the qkv scratch: passes of more than 128 rows store the projections there
-                         // and apply RoPE and the KV append in rope_append_kernel)
+      q.kind = EPI_QKV;
       q.rows = m->rows; q.rope_cs = m->rope_cs; q.qr = m->qr; q.kv = kv_layout(kv); q.layer = l;
       q.n_heads = H; q.n_kv_heads = G; q.head_dim = hd;
     }
@@ -630,6 +637,7 @@ specdec_status specdec_model_create_fmt(const specdec_model_desc* desc, const sp
   m->samp = base + L.samp;
   m->xs_d = desc->dtype == SPECDEC_BF16 ? (uint16_t*)(base + L.xs_d) : nullptr;
   m->xs_f = desc->dtype == SPECDEC_BF16 ? (uint16_t*)(base + L.xs_f) : nullptr;
+  m->ypart_floats = L.ypart_floats;
   m->ypart = bf16 && max_rows > kSkinnyRows ? (float*)(base + L.ypart) : nullptr;
   m->attn_ctr = desc->dtype == SPECDEC_BF16 ? (uint32_t*)(base + L.ctr) : nullptr;
   m->attn_cnt = desc->dtype == SPECDEC_BF16 ? (uint32_t*)(base + L.cnt) : nullptr;

@@ -937,670 +937,6 @@ __global__ __launch_bounds__(kQ4Threads) void gemm_q4_lds(GemmArgs a, int n_unit
   }
 }
 
-// ---------------------------------------------------------------- wide-M MFMA kernel (bf16 weights)
-// Passes of more than 64 rows (the verify blocks of many sequences, prefill
-// and catch-up chunks) in launches of up to 128 rows.  A block covers NC =
-// 64*T weight rows and a range of k-steps with G k-groups of 4 waves: group g
-// takes every G-th k-step of the range and wave w of a group owns tiles
-// wT..wT+T-1.  Each k-step's x slab (MP rows x 32 columns) is converted once
-// by its group into hi + lo bf16 A fragments in LDS (two buffers per group)
-// and shared by the group's four waves, so activation traffic per weight
-// byte falls by the 4T tiles sharing it.  Grids are about one block per CU,
-// so the G groups are what keeps more than one wave per SIMD busy; each wave
-// also keeps x slabs XR = 4 k-steps ahead and weight fragments D k-steps ahead
-// in register rings.  The groups' sums are added in group order in LDS; the
-// epilogues (store, SwiGLU, QKV with RoPE) then read the accumulators in
-// place.  Residual GEMMs (O, down: few row tiles) split K over the grid and
-// write partial sums, which resid_reduce_kernel adds in a fixed order; Q|K|V
-// and gate|up do the same with three tiles per wave, their partial sums added
-// by qkv_reduce_kernel (with RoPE, the query store and the KV append) and
-// swiglu_reduce_kernel.  (With three tiles per wave the x ring holds two slabs,
-// and the groups' sums go through the slab buffers one tile at a time.)
-constexpr int kWideGroups = 2;
-constexpr int kWideThreads = 256 * kWideGroups;
-constexpr int kWideRows = 128;  // rows per launch of the wide kernel
-constexpr int kWideCols = 128;  // columns per block of the split-K reduction (and per ss partial)
-constexpr int kWideMaxSs = 64;  // ss partials a wide launch sums (one per lane)
-constexpr int kWideSplitMax = 12;  // K splits of a wide launch's partial sums
-
-template <int MT, int T, int KIND>
-__global__ __launch_bounds__(kWideThreads) void gemm_bf16_wide(GemmArgs a, int ks_per_split, int n_split) {
-  constexpr int G = kWideGroups;
-  constexpr int MP = 16 * MT, NC = 64 * T;
-  constexpr int D = T == 1 ? 8 : 4;                  // weight k-steps in flight per wave
-  constexpr int XR = T >= 3 ? 2 : 4;                 // x slabs in flight per group (registers: T >= 3)
-  constexpr int PJ = (MP * 4 + 255) / 256;           // 32-byte x pieces per thread per slab
-  constexpr int MTP = PJ * 256 / 64;                 // m tiles the pieces cover (>= MT; extra rows read zeros)
-  constexpr bool QKV = KIND == EPI_QKV, SCALE = KIND != EPI_RESID;
-  constexpr int RSR = MP / (4 * G);                  // row-scale rows per wave
-  constexpr int CSL = QKV ? MP / 16 : 1;             // 16-byte cos/sin pieces per lane (8 columns x MP rows x 2)
-  static_assert(KIND != EPI_SWIGLU || T == 2, "SwiGLU pairs one gate and one up tile per wave");
-  static_assert(!QKV || T == 1, "the QKV epilogue tables cover one tile per wave");
-  static_assert(D % XR == 0, "the unrolled step loop indexes both rings statically");
-  static_assert(MP % (4 * G) == 0, "row-scale rows split evenly over the waves");
-  static_assert(4 * MT <= G * 2 * MTP * 2, "one tile's group sums fit in the slab buffers");
-  __shared__ u32x4 s_a[G][2][MTP][2][kWave];  // [group][buffer][m tile][hi, lo][lane]
-  __shared__ float scale[MP];
-  __shared__ f32x4 s_cs[QKV ? 4 : 1][QKV ? MP : 1][4];  // per tile wave, per row: cos of its 8 dims, then sin
-  __shared__ RowDesc s_rows[QKV ? MP : 1];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int grp = wave >> 2, wl = wave & 3, gtid = tid & 255;  // k-group, wave in group, thread in group
-  const int K = a.K, KS = (K + 31) / 32;
-  const int split = (int)blockIdx.x % n_split, blk = (int)blockIdx.x / n_split;
-  const int ks_begin = split * ks_per_split;
-  const int ks_end = min(KS, ks_begin + ks_per_split);
-  const int n_k = ks_end - ks_begin;
-  const int n_steps = (n_k + G - 1) / G;  // steps of every group (a group's last ones may be past the range)
-
-  // Weight tiles of this wave (SwiGLU: gate tile w and the up tile of the same columns).
-  __amdgpu_buffer_rsrc_t wr[T];
-#pragma unroll
-  for (int t = 0; t < T; ++t) {
-    const int lt = KIND == EPI_SWIGLU ? (t == 0 ? wl : 4 + wl) : wl * T + t;
-    bool ok;
-    const uint16_t* base = weight_tile(a, KIND, blk, NC, lt, KS, ok);
-    wr[t] = make_rsrc(base, ok ? (uint32_t)KS * 1024u : 0u);
-  }
-  const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, (uint32_t)a.M * a.ldx * 4u);
-
-  floatx4 acc[T][MT];
-#pragma unroll
-  for (int t = 0; t < T; ++t)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[t][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-  u32x4 wv[D][T];
-  f32x4 xv[XR][PJ][2];
-
-  // Step j of group g is k-step ks_begin + j*G + g.
-  auto load_w = [&](int j, u32x4 (&w)[T]) {
-    const int i = j * G + grp;
-    const uint32_t bad = (uint32_t)(i >= n_k) << 31;
-    const uint32_t off = ((uint32_t)(ks_begin + i) * 1024u + lane * 16u) | bad;
-#pragma unroll
-    for (int t = 0; t < T; ++t) w[t] = __builtin_amdgcn_raw_buffer_load_b128(wr[t], off, 0, kNonTemporal);
-  };
-  // Piece p = lane p%64 of the A fragment of m tile p/64: 8 consecutive floats
-  // of row 16*(p/64) + p%16 at column 8*(p%64/16) of the k-step (a wave moves
-  // whole fragments: contiguous LDS stores, 16 rows x 128 bytes per load).
-  auto load_x = [&](int j, f32x4 (&xs)[PJ][2]) {
-    const int i = j * G + grp;
-    const uint32_t bad = (uint32_t)(i >= n_k) << 31;
-#pragma unroll
-    for (int q = 0; q < PJ; ++q) {
-      const int p = gtid + q * 256, m = (p >> 6) * 16 + (p & 15), k = (ks_begin + i) * 32 + ((p >> 4) & 3) * 8;
-      const uint32_t off = (((uint32_t)m * a.ldx + k) * 4u) | bad | ((uint32_t)(k >= K) << 31);
-      xs[q][0] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
-      xs[q][1] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off + 16u, 0, 0));
-    }
-  };
-  // A fragment lane 16*(k/8) + m%16 holds row m, columns 8*(k/8)..+7
-  auto store_x = [&](int buf, const f32x4 (&xs)[PJ][2]) {
-#pragma unroll
-    for (int q = 0; q < PJ; ++q) {
-      const int p = gtid + q * 256;
-      const int mt = p >> 6, ln = p & 63;
-      bf16x8 hi, lo;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float v = xs[q][e >> 2][e & 3];
-        const __bf16 h = (__bf16)v;
-        hi[e] = h;
-        lo[e] = (__bf16)(v - (float)h);
-      }
-      s_a[grp][buf][mt][0][ln] = __builtin_bit_cast(u32x4, hi);
-      s_a[grp][buf][mt][1][ln] = __builtin_bit_cast(u32x4, lo);
-    }
-  };
-  // All fragment reads first, then the hi products of every tile, then the lo
-  // ones (a product's accumulator is not the previous product's).
-  auto compute = [&](int buf, const u32x4 (&w)[T]) {
-    bf16x8 av[MT][2];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      av[mt][0] = __builtin_bit_cast(bf16x8, s_a[grp][buf][mt][0][lane]);
-      av[mt][1] = __builtin_bit_cast(bf16x8, s_a[grp][buf][mt][1][lane]);
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-          acc[t][mt] =
-              __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mt][h], __builtin_bit_cast(bf16x8, w[t]), acc[t][mt], 0, 0, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * MT, 0);     // LDS reads
-    __builtin_amdgcn_sched_group_barrier(0x008, 2 * MT * T, 0);  // then MFMAs
-  };
-
-  // QKV epilogue geometry of this wave's tile: rotation dims 8*tq + e (e < 8)
-  // of its head for Q and K columns.
-  const int hd = a.head_dim, half = hd >> 1;
-  const int nq = a.n_seg[0], nqk = nq + a.n_seg[1];
-  const int n0 = blk * NC + wl * 16;  // (QKV: T == 1)
-  const int r0 = n0 >= nqk ? n0 - nqk : (n0 >= nq ? n0 - nq : n0);
-  const int tq = (r0 % hd) >> 4;
-
-  // Prologue.  Loads in order: the epilogue's small operands (row-scale
-  // partial sums; QKV: cos/sin of the tile's 8 dims and the row descriptors,
-  // fetched by group 0), XR x slabs, D weight k-steps.  Loads complete in
-  // order, so storing the small operands waits for them alone.
-  float rsv[SCALE ? RSR : 1];
-  if constexpr (SCALE) {
-    const __amdgpu_buffer_rsrc_t sr = make_rsrc(a.ss_in, a.ss_in ? (uint32_t)a.n_ss * a.ss_ld * 4u : 0u);
-#pragma unroll
-    for (int i = 0; i < RSR; ++i) {
-      const int m = wave + 4 * G * i;
-      const uint32_t off = ((uint32_t)lane * a.ss_ld + m) * 4u | ((uint32_t)(m >= a.M || lane >= a.n_ss) << 31);
-      rsv[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, off, 0, 0));
-    }
-  }
-  f32x4 csv[CSL];
-  u32x4 rdv = u32x4{0u, 0u, 0u, 0u};
-  if constexpr (QKV) {
-    const __amdgpu_buffer_rsrc_t cr = make_rsrc(a.rope_cs, (uint32_t)a.M * hd * 4u);
-#pragma unroll
-    for (int q = 0; q < CSL; ++q) {  // piece v = lane + 64q: row v/4, (cos, sin) = (v/2)%2, half (v%2)
-      const int v = lane + 64 * q, m = v >> 2, sn = (v >> 1) & 1, hf = v & 1;
-      const uint32_t off = ((uint32_t)m * hd + sn * half + 8 * tq + 4 * hf) * 4u |
-                           ((uint32_t)(n0 >= nqk || grp != 0) << 31);
-      csv[q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(cr, off, 0, 0));
-    }
-    const __amdgpu_buffer_rsrc_t rr = make_rsrc(a.rows, (uint32_t)a.M * (uint32_t)sizeof(RowDesc));
-    rdv = __builtin_amdgcn_raw_buffer_load_b128(
-        rr, (uint32_t)tid * (uint32_t)sizeof(RowDesc) | ((uint32_t)(tid >= MP) << 31), 0, 0);
-  }
-#pragma unroll
-  for (int r = 0; r < XR; ++r) load_x(r, xv[r]);
-#pragma unroll
-  for (int u = 0; u < D; ++u) load_w(u, wv[u]);
-  if constexpr (SCALE) {
-    // s_m = 1/sqrt(sum_p ss[p][m] / K + eps): partial p in lane p, fixed shuffle tree
-    wave_sum_n(rsv);  // (n_ss <= 64: checked by the launcher)
-#pragma unroll
-    for (int i = 0; i < RSR; ++i) {
-      const int m = wave + 4 * G * i;
-      if (lane == 0) scale[m] = (a.ss_in && m < a.M) ? 1.0f / sqrtf(rsv[i] / (float)a.K + a.eps) : 1.0f;
-    }
-  }
-  if constexpr (QKV) {
-    if (grp == 0) {
-#pragma unroll
-      for (int q = 0; q < CSL; ++q) {
-        const int v = lane + 64 * q;
-        s_cs[wl][v >> 2][v & 3] = csv[q];
-      }
-    }
-    if (tid < MP) s_rows[tid] = __builtin_bit_cast(RowDesc, rdv);
-  }
-  store_x(0, xv[0]);
-  load_x(XR, xv[0]);
-  __syncthreads();
-
-  // Step j: multiply the group's slab j (LDS buffer j%2) by weight slot j%D,
-  // refill the slot with step j+D, move slab j+1 (register slot (j+1)%XR) into
-  // the other buffer and fetch slab j+1+XR into its slot.  The step count is
-  // rounded up to a multiple of D: steps past the range multiply zeros (their
-  // loads are out of range), which keeps the loop free of early exits (an exit
-  // edge into the loop makes the compiler wait for every load in flight at the
-  // top of the loop).  (Scheduling barriers keep each step's conversions after
-  // its multiplies: hoisted above them, the conversions of a later slab would
-  // wait for the weight loads issued after it.)
-  for (int j0 = 0; j0 < n_steps; j0 += D) {
-#pragma unroll
-    for (int u = 0; u < D; ++u) {
-      const int j = j0 + u;
-      __builtin_amdgcn_sched_barrier(0);
-      compute(u & 1, wv[u]);
-      __builtin_amdgcn_sched_barrier(0);
-      load_w(j + D, wv[u]);
-      store_x((u + 1) & 1, xv[(u + 1) % XR]);
-      load_x(j + 1 + XR, xv[(u + 1) % XR]);
-      __syncthreads();
-    }
-  }
-
-  // Group sums: groups 1.. park theirs in the (now free) slab buffers, group 0
-  // adds them in group order and runs the epilogue.
-  if constexpr (G > 1 && (G - 1) * 4 * T * MT > G * 2 * MTP * 2) {
-    // (too many for the slab buffers at once: one tile at a time)
-    static_assert(G == 2, "tile-at-a-time group sums: two groups");
-    floatx4* park = reinterpret_cast<floatx4*>(&s_a[0][0][0][0][0]);
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      if (grp > 0) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) park[(wl * MT + mt) * kWave + lane] = acc[t][mt];
-      }
-      __syncthreads();
-      if (grp == 0) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[t][mt] += park[(wl * MT + mt) * kWave + lane];
-      }
-      __syncthreads();
-    }
-    if (grp > 0) return;
-  } else if constexpr (G > 1) {
-    floatx4* park = reinterpret_cast<floatx4*>(&s_a[0][0][0][0][0]);
-    if (grp > 0) {
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) park[(((grp - 1) * 4 + wl) * T * MT + t * MT + mt) * kWave + lane] = acc[t][mt];
-    }
-    __syncthreads();
-    if (grp > 0) return;
-#pragma unroll
-    for (int g = 1; g < G; ++g)
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[t][mt] += park[(((g - 1) * 4 + wl) * T * MT + t * MT + mt) * kWave + lane];
-  }
-
-  // Epilogue (group 0).  acc[t][mt][r] is row mt*16 + 4*(lane/16) + r, column lane%16 of tile t.
-  const int M = a.M, cl = lane & 15, rg = lane >> 4;
-  if constexpr (KIND == EPI_RESID) {
-    // Each 16 x 16 accumulator tile goes through a wave-private LDS square
-    // (inside the wave's own part of the group-sum area, which it has read):
-    // lane l then holds 4 consecutive columns of row l/4 and stores them as
-    // one 16-byte write, a quarter of the store instructions of writing each
-    // lane's 4 rows of one column.  (LDS operations of a wave complete in
-    // order; the wave barriers keep the compiler from reordering them.)
-    float* yp = a.ypart + (size_t)split * M * a.n_rows;
-    constexpr int PSTRIDE = ((G - 1) * 4 * T * MT > G * 2 * MTP * 2 ? MT : T * MT) * 256;  // floats per wave
-    float* sq = reinterpret_cast<float*>(&s_a[0][0][0][0][0]) + (size_t)wl * PSTRIDE;  // [16][17]
-    const int rr = lane >> 2, c4 = 4 * (lane & 3);
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int n0 = blk * NC + (wl * T + t) * 16;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sq[(4 * rg + r) * 17 + cl] = acc[t][mt][r];
-        __builtin_amdgcn_wave_barrier();
-        const f32x4 v = f32x4{sq[rr * 17 + c4], sq[rr * 17 + c4 + 1], sq[rr * 17 + c4 + 2], sq[rr * 17 + c4 + 3]};
-        __builtin_amdgcn_wave_barrier();
-        const int m = mt * 16 + rr;
-        if (m < M && n0 + c4 < a.n_rows) *(f32x4*)(yp + (size_t)m * a.n_rows + n0 + c4) = v;
-      }
-    }
-  } else if constexpr (KIND == EPI_STORE) {
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int n = blk * NC + (wl * T + t) * 16 + cl;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = mt * 16 + 4 * rg + r;
-          if (m < M && n < a.n_rows) a.out[(size_t)m * a.ldo + n] = acc[t][mt][r] * scale[m];
-        }
-    }
-  } else if constexpr (KIND == EPI_SWIGLU) {
-    const int f = blk * (NC / 2) + wl * 16 + cl;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = mt * 16 + 4 * rg + r;
-        if (m < M && f < a.n_rows)
-          a.out[(size_t)m * a.ldo + f] = silu_f(acc[0][mt][r] * scale[m]) * (acc[1][mt][r] * scale[m]);
-      }
-  } else {  // EPI_QKV: the RoPE partner of column c is column c ^ 8 of the same tile, i.e. lane ^ 8
-    const int H = a.n_heads, cap = a.kv.capacity;
-    const int n = n0 + cl;
-    const bool is_q = n < nq, is_v = n >= nqk;
-    const int head = r0 / hd, w = r0 % hd + cl, ec = cl, e = cl & 7;
-    const int j = 8 * tq + e, d = ec < 8 ? j : half + j;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = mt * 16 + 4 * rg + r;
-        const float x = acc[0][mt][r] * scale[m];
-        const float y = __shfl_xor(x, 8, kWave);
-        if (m >= M || n >= a.n_rows) continue;
-        const RowDesc rd = s_rows[m];
-        if (is_v) {
-          if (rd.valid) {
-            uint16_t* kvb = k_block<uint16_t>(a.kv, a.layer, rd.b, head);
-            Storage<uint16_t>::store(kvb + KvIndex<uint16_t>::v(rd.pos, w, hd, cap), x);
-          }
-          continue;
-        }
-        const f32x4 c4 = s_cs[wl][m][e >> 2], s4 = s_cs[wl][m][2 + (e >> 2)];
-        const float cs = c4[e & 3], sn = s4[e & 3];
-        const float out = ec < 8 ? x * cs - y * sn : x * cs + y * sn;
-        if (is_q) {
-          a.qr[((size_t)m * H + head) * hd + d] = out;
-        } else if (rd.valid) {
-          uint16_t* kvb = k_block<uint16_t>(a.kv, a.layer, rd.b, head);
-          Storage<uint16_t>::store(kvb + KvIndex<uint16_t>::k(rd.pos, d, hd, cap), out);
-        }
-      }
-  }
-}
-
-// Split-K partial sums of 4 columns of one row, added in split order; every
-// split's load is issued before the first add (the split index is clamped, so
-// loads past n_split re-read the last split and are not added).
-template <int NS>
-__device__ __forceinline__ f32x4 sum_splits_n(const float* yp, size_t split_stride, int n_split) {
-  f32x4 v[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) v[s] = *(const f32x4*)(yp + (size_t)min(s, n_split - 1) * split_stride);
-  f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-    if (s < n_split) y += v[s];
-  return y;
-}
-__device__ __forceinline__ f32x4 sum_splits(const float* yp, size_t split_stride, int n_split) {
-  if (n_split <= 4) return sum_splits_n<4>(yp, split_stride, n_split);  // (block-uniform)
-  if (n_split <= 8) return sum_splits_n<8>(yp, split_stride, n_split);
-  return sum_splits_n<kWideSplitMax>(yp, split_stride, n_split);
-}
-
-// RMSNorm scales of rows m0 .. m0+7 into s_scale: the block loads every
-// partial sum of squares at once (two per thread), then thread r < 8 adds its
-// row's in partial order.
-__device__ __forceinline__ void row_scales8(const GemmArgs& a, int m0, float* s_scale, float (*s_ss)[kWideMaxSs]) {
-  const int tid = threadIdx.x;
-  float v[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int i = tid + 256 * k, r = i / kWideMaxSs, p = i % kWideMaxSs, m = m0 + r;
-    v[k] = a.ss_in && p < a.n_ss && m < a.M ? a.ss_in[(size_t)p * a.ss_ld + m] : 0.f;
-  }
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int i = tid + 256 * k;
-    s_ss[i / kWideMaxSs][i % kWideMaxSs] = v[k];
-  }
-  __syncthreads();
-  if (tid < 8) {
-    float ss = 0.f;
-    for (int p = 0; p < a.n_ss; ++p) ss += s_ss[tid][p];
-    s_scale[tid] = a.ss_in ? 1.0f / sqrtf(ss / (float)a.K + a.eps) : 1.0f;
-  }
-  __syncthreads();
-}
-static_assert(8 * kWideMaxSs == 512, "row_scales8: two partials per thread of a 256-thread block");
-
-// Sum of the split-K partials of a residual GEMM in split order, residual
-// add, next RMSNorm input and its sums of squares.  Block = 128 columns x 8
-// rows; thread = 4 columns of one row; ss partial p = column block p.
-__global__ __launch_bounds__(256) void resid_reduce_kernel(GemmArgs a, int n_split) {
-  const int tid = threadIdx.x, m = (int)blockIdx.y * 8 + (tid >> 5);
-  const int n = (int)blockIdx.x * kWideCols + 4 * (tid & 31);
-  const int M = a.M;
-  float t = 0.f;
-  if (m < M && n < a.n_rows) {
-    const f32x4 y = sum_splits(a.ypart + (size_t)m * a.n_rows + n, (size_t)M * a.n_rows, n_split);
-    float* hp = a.out + (size_t)m * a.ldo + n;
-    const f32x4 h = *(const f32x4*)hp + y;
-    *(f32x4*)hp = h;
-    const uint16_t* g = (const uint16_t*)a.gain_out + n;
-    const f32x4 x = f32x4{h[0] * bf16_bits_to_f32(g[0]), h[1] * bf16_bits_to_f32(g[1]), h[2] * bf16_bits_to_f32(g[2]),
-                          h[3] * bf16_bits_to_f32(g[3])};
-    if (a.xs_out) put_stacked4(a.xs_out, a.stt, m, n, x);
-    else *(f32x4*)(a.xg_out + (size_t)m * a.ldo + n) = x;
-    t = h[0] * h[0] + h[1] * h[1] + h[2] * h[2] + h[3] * h[3];
-  }
-#pragma unroll
-  for (int o = 16; o > 0; o >>= 1) t += __shfl_xor(t, o, kWave);
-  if ((tid & 31) == 0 && m < M) a.ss_out[(size_t)blockIdx.x * a.ss_ld + m] = t;
-}
-
-// Sum of the split-K partial sums of a wide pass's gate and up projections
-// (rows [0, F) and [F, 2F) of the partials) in split order, times the row's
-// RMSNorm scale, then SwiGLU.  Block = 128 columns x 8 rows; thread = 4 columns of one row.
-__global__ __launch_bounds__(256) void swiglu_reduce_kernel(GemmArgs a, int n_split) {
-  __shared__ float s_scale[8];
-  __shared__ float s_ss[8][kWideMaxSs];
-  const int tid = threadIdx.x, m = (int)blockIdx.y * 8 + (tid >> 5);
-  const int f = (int)blockIdx.x * kWideCols + 4 * (tid & 31);
-  const int M = a.M, F = a.n_rows, W = 2 * F;
-  row_scales8(a, (int)blockIdx.y * 8, s_scale, s_ss);
-  if (m >= M || f >= F) return;
-  const float* yp = a.ypart + (size_t)m * W;
-  const f32x4 gs = sum_splits(yp + f, (size_t)M * W, n_split), us = sum_splits(yp + F + f, (size_t)M * W, n_split);
-  const float sc = s_scale[tid >> 5];
-  f32x4 o;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) o[e] = silu_f(gs[e] * sc) * (us[e] * sc);
-  *(f32x4*)(a.out + (size_t)m * a.ldo + f) = o;
-}
-
-// Sum of the split-K partial sums of a wide pass's Q|K|V projections in split
-// order, times the row's RMSNorm scale, then RoPE on the Q and K columns and
-// the stores: rotated queries to qr, rotated keys and the values appended to
-// the KV cache (valid rows).  Q and K columns come in the packed RoPE order:
-// column c of a head's 16-column tile tq is dim 8tq + c for c < 8, hd/2 + 8tq
-// + c - 8 otherwise, so each column's rotation partner (c ^ 8) is 8 columns
-// away, in the lane ^ 2 of the row's 32 threads.  Block = 128 columns x 8
-// rows; thread = 4 columns of one row.
-__global__ __launch_bounds__(256) void qkv_reduce_kernel(GemmArgs a, int n_split) {
-  __shared__ float s_scale[8];
-  __shared__ float s_ss[8][kWideMaxSs];
-  const int tid = threadIdx.x, m = (int)blockIdx.y * 8 + (tid >> 5);
-  const int n = (int)blockIdx.x * kWideCols + 4 * (tid & 31);
-  const int M = a.M;
-  row_scales8(a, (int)blockIdx.y * 8, s_scale, s_ss);
-  const bool live = m < M && n < a.n_rows;
-  f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (live) y = sum_splits(a.ypart + (size_t)m * a.n_rows + n, (size_t)M * a.n_rows, n_split);
-  const float sc = s_scale[tid >> 5];
-  f32x4 z;  // (every lane takes part in the shuffles)
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    y[e] *= sc;
-    z[e] = __shfl_xor(y[e], 2, kWave);
-  }
-  if (live) qkv_store4(a, m, n, y, z);
-}
-
-// ---------------------------------------------------------------- tile MFMA kernel (bf16 weights, 129+ rows)
-// Launches of more than 128 rows (prefill chunks, up to 4 row tiles of 256 per
-// launch, row tiles adjacent in the grid so the blocks sharing a weight
-// column tile run together): compute-bound.  A block
-// covers 256 rows x 128 weight rows (SwiGLU: 64 gate and the 64 matching up
-// rows) with 8 waves in a 4 x 2 grid, each owning 64 x 64 = 4 x 4 MFMA tiles.
-// Per k-step the block stages in LDS the x slab (256 rows x 32 columns, split
-// into hi + lo bf16 A fragments; each wave moves whole fragments) and its 8
-// weight fragments (wave w moves fragment w); each wave then reads 8 A and
-// 4 B fragments for its 32 products (384 bytes of LDS per product, against
-// 1 KB when a wave owns one column tile).  x and weights are fetched two
-// k-steps ahead.  Epilogues in place: store (Q|K|V columns written back in
-// natural order, RoPE and the KV append then run in rope_append_kernel),
-// SwiGLU, and residual partial sums over n_split k ranges for
-// resid_reduce_kernel.
-constexpr int kTileThreads = 512;
-constexpr int kTileRows = 256, kTileCols = 128;
-constexpr int kTileSplitMax = 8;
-constexpr int kTileLaunchRows = 1024;  // rows per launch: up to 4 row tiles share each weight column tile
-constexpr int kTilePartialRows = 2048; // split-K partials held: n_split * launch rows <= this
-
-template <int KIND>  // EPI_STORE (also Q|K|V), EPI_SWIGLU, EPI_RESID (partials)
-__global__ __launch_bounds__(kTileThreads) void gemm_bf16_tile(GemmArgs a, int n_ctiles, int ks_per_split,
-                                                               int n_split) {
-  constexpr int MTB = kTileRows / 16, NTB = kTileCols / 16;
-  constexpr int PJ = kTileRows * 4 / kTileThreads;  // 32-byte x pieces per thread per slab
-  constexpr int RSR = kTileRows / (kTileThreads / kWave);
-  constexpr bool SCALE = KIND != EPI_RESID, SWIGLU = KIND == EPI_SWIGLU;
-  __shared__ u32x4 s_a[2][MTB][2][kWave];  // [buffer][m tile][hi, lo][lane]
-  __shared__ u32x4 s_b[2][NTB][kWave];     // [buffer][weight tile][lane]
-  __shared__ float scale[kTileRows];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
-  const int K = a.K, KS = (K + 31) / 32;
-  const int n_rt = (a.M + kTileRows - 1) / kTileRows;
-  const int rt = (int)blockIdx.x % n_rt, ct = ((int)blockIdx.x / n_rt) % n_ctiles;
-  const int split = (int)blockIdx.x / (n_rt * n_ctiles);
-  const int ks_begin = split * ks_per_split, ks_end = min(KS, ks_begin + ks_per_split);
-  const int n_k = ks_end - ks_begin, n_steps = (n_k + 1) & ~1;
-  const int m0 = rt * kTileRows, rows = min(a.M - m0, kTileRows);
-  // weight tile j of the block: SwiGLU tiles 0..3 gate, 4..7 up (same columns)
-  auto btile = [&](int j) { return SWIGLU ? (j < 2 ? wn * 2 + j : 4 + wn * 2 + (j - 2)) : wn * 4 + j; };
-
-  bool ok;
-  const uint16_t* wbase = weight_tile(a, KIND, ct, kTileCols, wave, KS, ok);  // (the tile this wave stages)
-  const __amdgpu_buffer_rsrc_t wr = make_rsrc(wbase, ok ? (uint32_t)KS * 1024u : 0u);
-  const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x + (size_t)m0 * a.ldx, (uint32_t)rows * a.ldx * 4u);
-
-  floatx4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  f32x4 xv[2][PJ][2];
-  u32x4 bv[2];
-
-  auto load = [&](int i, f32x4 (&xs)[PJ][2], u32x4& b) {
-    const uint32_t bad = (uint32_t)(i >= n_k) << 31;
-    b = __builtin_amdgcn_raw_buffer_load_b128(wr, ((uint32_t)(ks_begin + i) * 1024u + lane * 16u) | bad, 0,
-                                              kNonTemporal);
-#pragma unroll
-    for (int q = 0; q < PJ; ++q) {
-      const int p = tid + q * kTileThreads, m = (p >> 6) * 16 + (p & 15);
-      const int k = (ks_begin + i) * 32 + ((p >> 4) & 3) * 8;
-      const uint32_t off = (((uint32_t)m * a.ldx + k) * 4u) | bad | ((uint32_t)(k >= K) << 31);
-      xs[q][0] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
-      xs[q][1] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, off + 16u, 0, 0));
-    }
-  };
-  auto store = [&](int buf, const f32x4 (&xs)[PJ][2], const u32x4& b) {
-#pragma unroll
-    for (int q = 0; q < PJ; ++q) {
-      const int p = tid + q * kTileThreads, mt = p >> 6, ln = p & 63;
-      bf16x8 hi, lo;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float v = xs[q][e >> 2][e & 3];
-        const __bf16 h = (__bf16)v;
-        hi[e] = h;
-        lo[e] = (__bf16)(v - (float)h);
-      }
-      s_a[buf][mt][0][ln] = __builtin_bit_cast(u32x4, hi);
-      s_a[buf][mt][1][ln] = __builtin_bit_cast(u32x4, lo);
-    }
-    s_b[buf][wave][lane] = b;
-  };
-  auto compute = [&](int buf) {
-    bf16x8 av[4][2], bw[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      av[i][0] = __builtin_bit_cast(bf16x8, s_a[buf][wm * 4 + i][0][lane]);
-      av[i][1] = __builtin_bit_cast(bf16x8, s_a[buf][wm * 4 + i][1][lane]);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) bw[j] = __builtin_bit_cast(bf16x8, s_b[buf][btile(j)][lane]);
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i][h], bw[j], acc[i][j], 0, 0, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 12, 0);  // LDS reads
-    __builtin_amdgcn_sched_group_barrier(0x008, 32, 0);  // then MFMAs
-  };
-
-  // Prologue: row-scale partial sums first, then slabs 0 and 1; slab 0 to LDS.
-  float rsv[SCALE ? RSR : 1];
-  if constexpr (SCALE) {
-    const __amdgpu_buffer_rsrc_t sr = make_rsrc(a.ss_in, a.ss_in ? (uint32_t)a.n_ss * a.ss_ld * 4u : 0u);
-#pragma unroll
-    for (int i = 0; i < RSR; ++i) {
-      const int m = m0 + wave + (kTileThreads / kWave) * i;
-      const uint32_t off = ((uint32_t)lane * a.ss_ld + m) * 4u | ((uint32_t)(m >= a.M || lane >= a.n_ss) << 31);
-      rsv[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, off, 0, 0));
-    }
-  }
-  load(0, xv[0], bv[0]);
-  load(1, xv[1], bv[1]);
-  if constexpr (SCALE) {
-    wave_sum_n(rsv);  // (n_ss <= 64: checked by the launcher)
-#pragma unroll
-    for (int i = 0; i < RSR; ++i) {
-      const int r = wave + (kTileThreads / kWave) * i, m = m0 + r;
-      if (lane == 0) scale[r] = (a.ss_in && m < a.M) ? 1.0f / sqrtf(rsv[i] / (float)a.K + a.eps) : 1.0f;
-    }
-  }
-  store(0, xv[0], bv[0]);
-  load(2, xv[0], bv[0]);
-  __syncthreads();
-
-  // Step i: multiply buffer i%2, move slab i+1 (register slot (i+1)%2) into the
-  // other buffer, fetch slab i+3 into that slot.  (Steps rounded up to even:
-  // the last one multiplies zeros when n_k is odd.)
-  for (int i0 = 0; i0 < n_steps; i0 += 2) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int i = i0 + u;
-      __builtin_amdgcn_sched_barrier(0);
-      compute(u);
-      __builtin_amdgcn_sched_barrier(0);
-      store(u ^ 1, xv[u ^ 1], bv[u ^ 1]);
-      load(i + 3, xv[u ^ 1], bv[u ^ 1]);
-      __syncthreads();
-    }
-  }
-
-  // Epilogue.  acc[i][j][r]: row m0 + (wm*4 + i)*16 + 4*(lane/16) + r, column lane%16 of weight tile btile(j).
-  const int cl = lane & 15, rg = lane >> 4;
-  if constexpr (KIND == EPI_SWIGLU) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int f = ct * (kTileCols / 2) + (wn * 2 + j) * 16 + cl;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int mr = (wm * 4 + i) * 16 + 4 * rg + r;
-          if (mr < rows && f < a.n_rows)
-            a.out[(size_t)(m0 + mr) * a.ldo + f] =
-                silu_f(acc[i][j][r] * scale[mr]) * (acc[i][j + 2][r] * scale[mr]);
-        }
-    }
-  } else if constexpr (KIND == EPI_RESID) {
-    float* yp = a.ypart + (size_t)split * a.M * a.n_rows;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = ct * kTileCols + btile(j) * 16 + cl;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int mr = (wm * 4 + i) * 16 + 4 * rg + r;
-          if (mr < rows && n < a.n_rows) yp[(size_t)(m0 + mr) * a.n_rows + n] = acc[i][j][r];
-        }
-    }
-  } else {
-    // store; Q|K|V: Q and K columns come in the packed RoPE order (column c of
-    // a head's tile tq is dim 8*tq + c for c < 8, hd/2 + 8*tq + c - 8 otherwise)
-    const int hd = a.head_dim, nqk = a.n_seg[0] + a.n_seg[1];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = ct * kTileCols + btile(j) * 16 + cl;
-      int col = n;
-      if (a.kind == EPI_QKV && n < nqk) {
-        const int base = n >= a.n_seg[0] ? a.n_seg[0] : 0, r = n - base, w = r % hd, tq = w >> 4, ec = w & 15;
-        col = base + (r / hd) * hd + (ec < 8 ? 8 * tq + ec : hd / 2 + 8 * tq + ec - 8);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int mr = (wm * 4 + i) * 16 + 4 * rg + r;
-          if (mr < rows && n < a.n_rows) a.out[(size_t)(m0 + mr) * a.ldo + col] = acc[i][j][r] * scale[mr];
-        }
-    }
-  }
-}
-
 // ---------------------------------------------------------------- vector kernel (float32 weights)
 // Block = 4 waves over NC weight rows; each wave takes NC/4 rows, lanes stride
 // over K; M processed 8 rows at a time.
@@ -1805,20 +1141,11 @@ hipError_t launch_pack(const void* src, void* dst, int N, int K, int rope_hd, hi
 
 bool gemm_wide(int dtype, int M) { return dtype == SPECDEC_BF16 && M > kMaxGemmRows; }
 int gemm_launch_rows(int dtype, int M) {
-  return !gemm_wide(dtype, M) ? kMaxGemmRows : (M > kWideRows ? kTileLaunchRows : kWideRows);
-}
-size_t wide_ypart_floats(int n_rows) {
-  return (size_t)std::max(kWideSplitMax * kWideRows, kTilePartialRows) * n_rows;
-}
-
-hipError_t launch_resid_reduce(const GemmArgs& a, int n_split, hipStream_t s) {
-  hipLaunchKernelGGL(resid_reduce_kernel, dim3((a.n_rows + kWideCols - 1) / kWideCols, (a.M + 7) / 8), dim3(256), 0, s,
-                     a, n_split);
-  return hipGetLastError();
+  return gemm_wide(dtype, M) ? kTileLaunchRows : kMaxGemmRows;
 }
 
 int gemm_row_blocks(int dtype, int kind, int n_rows, int M) {
-  if (kind == EPI_RESID && dtype == SPECDEC_BF16 && M > kSkinnyRows) return (n_rows + kWideCols - 1) / kWideCols;
+  if (kind == EPI_RESID && dtype == SPECDEC_BF16 && M > kSkinnyRows) return (n_rows + kTileReduceCols - 1) / kTileReduceCols;
   if (dtype == SPECDEC_BF16) {
     int nc = 16 * mfma_tiles(kind, n_rows);
     int per = kind == EPI_SWIGLU ? nc / 2 : nc;
@@ -1827,150 +1154,6 @@ int gemm_row_blocks(int dtype, int kind, int n_rows, int M) {
   int per = kind == EPI_SWIGLU ? 16 : 16;
   return (n_rows + per - 1) / per;
 }
-
-namespace {
-template <int MT, int T, int KIND>
-void launch_wide_mt(const GemmArgs& a, int blocks, int ks_per_split, int n_split, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_bf16_wide<MT, T, KIND>), dim3(blocks * n_split), dim3(kWideThreads), 0, s, a,
-                     ks_per_split, n_split);
-}
-template <int T, int KIND>
-void launch_wide_t(const GemmArgs& a, int blocks, int ks_per_split, int n_split, hipStream_t s) {
-  const int MT = (a.M + 15) / 16;
-  if (MT <= 4) launch_wide_mt<4, T, KIND>(a, blocks, ks_per_split, n_split, s);
-  else if (MT <= 7) launch_wide_mt<7, T, KIND>(a, blocks, ks_per_split, n_split, s);
-  else launch_wide_mt<8, T, KIND>(a, blocks, ks_per_split, n_split, s);
-}
-
-// Launches of 129..1024 rows on the tile kernel (Q|K|V: a store of the
-// projections in natural column order, then rope_append_kernel).
-hipError_t launch_tile(const GemmArgs& a, hipStream_t s) {
-  if (a.M > kTileLaunchRows || (a.ss_in && a.n_ss > kWideMaxSs)) return hipErrorInvalidValue;
-  const int KS = (a.K + 31) / 32, n_rt = (a.M + kTileRows - 1) / kTileRows;
-  switch (a.kind) {
-    case EPI_STORE:
-    case EPI_QKV: {
-      if (a.kind == EPI_QKV && (!a.out || a.ldo < a.n_rows || a.head_dim % 16 || a.n_seg[0] % a.head_dim ||
-                                a.n_seg[1] % a.head_dim))
-        return hipErrorInvalidValue;
-      const int nct = (a.n_rows + kTileCols - 1) / kTileCols;
-      hipLaunchKernelGGL(gemm_bf16_tile<EPI_STORE>, dim3(n_rt * nct), dim3(kTileThreads), 0, s, a, nct, KS, 1);
-      if (a.kind == EPI_QKV) {
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        AttnArgs r{};
-        r.rows = a.rows; r.M = a.M; r.rps = a.M; r.n_heads = a.n_heads; r.n_kv_heads = a.n_kv_heads;
-        r.head_dim = a.head_dim; r.qkv = a.out; r.rope_cs = a.rope_cs; r.qr = a.qr; r.kv = a.kv; r.layer = a.layer;
-        return launch_rope_append(r, s);
-      }
-      break;
-    }
-    case EPI_SWIGLU: {
-      const int nct = (a.n_rows + kTileCols / 2 - 1) / (kTileCols / 2);
-      hipLaunchKernelGGL(gemm_bf16_tile<EPI_SWIGLU>, dim3(n_rt * nct), dim3(kTileThreads), 0, s, a, nct, KS, 1);
-      break;
-    }
-    case EPI_RESID: {
-      if (!a.ypart || a.n_rows % 4) return hipErrorInvalidValue;
-      const int nct = (a.n_rows + kTileCols - 1) / kTileCols, blocks = n_rt * nct;
-      int n_split = std::min(kTileSplitMax, std::max(1, (compute_units() + blocks - 1) / blocks));
-      n_split = std::min({n_split, KS, kTilePartialRows / a.M});
-      const int per = (KS + n_split - 1) / n_split;
-      n_split = (KS + per - 1) / per;
-      hipLaunchKernelGGL(gemm_bf16_tile<EPI_RESID>, dim3(blocks * n_split), dim3(kTileThreads), 0, s, a, nct, per,
-                         n_split);
-      hipLaunchKernelGGL(resid_reduce_kernel, dim3((a.n_rows + kWideCols - 1) / kWideCols, (a.M + 7) / 8),
-                         dim3(256), 0, s, a, n_split);
-      break;
-    }
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_wide(const GemmArgs& a, hipStream_t s) {
-  if (a.M > kWideRows) return launch_tile(a, s);
-  if (a.ss_in && a.n_ss > kWideMaxSs) return hipErrorInvalidValue;
-  const int KS = (a.K + 31) / 32, cus = compute_units();
-  switch (a.kind) {
-    case EPI_STORE: {
-      const int T = (a.n_rows + 127) / 128 * 10 >= cus * 9 ? 2 : 1;
-      const int blocks = (a.n_rows + 64 * T - 1) / (64 * T);
-      if (T == 2) launch_wide_t<2, EPI_STORE>(a, blocks, KS, 1, s);
-      else launch_wide_t<1, EPI_STORE>(a, blocks, KS, 1, s);
-      break;
-    }
-    case EPI_QKV: {
-      if (a.kv.dtype != SPECDEC_BF16 || a.head_dim % 16 || a.n_seg[0] % a.head_dim || a.n_seg[1] % a.head_dim)
-        return hipErrorInvalidValue;
-      // Three tiles per wave over a K split that keeps the grid within the
-      // CUs (the 7B shape: 64 column blocks x 4 splits): raw partial sums,
-      // then qkv_reduce_kernel (row scale, RoPE, the query store and the KV
-      // append).  The wide kernel's time follows its k-steps per
-      // block more than its products per k-step, so fewer k-steps per block
-      // pay for the extra launches (16 long-context 7B sequences, 112 rows per
-      // verify: 16.53 -> 15.16 ms on one box together with the SwiGLU split,
-      // one tile per wave and no split before).
-      const int blocks = (a.n_rows + 191) / 192;
-      int n_split = std::min({kWideSplitMax, KS, std::max(1, cus / blocks)});
-      const int ks_per_split = (KS + n_split - 1) / n_split;
-      n_split = (KS + ks_per_split - 1) / ks_per_split;
-      if (!a.ypart || a.n_rows % 16 || (size_t)n_split * a.M * a.n_rows > wide_ypart_floats(a.K)) {
-        launch_wide_t<1, EPI_QKV>(a, (a.n_rows + 63) / 64, KS, 1, s);
-        break;
-      }
-      GemmArgs p = a;
-      p.kind = EPI_RESID;
-      launch_wide_t<3, EPI_RESID>(p, blocks, ks_per_split, n_split, s);
-      hipLaunchKernelGGL(qkv_reduce_kernel, dim3((a.n_rows + kWideCols - 1) / kWideCols, (a.M + 7) / 8), dim3(256), 0,
-                         s, a, n_split);
-      break;
-    }
-    case EPI_SWIGLU: {
-      // The gate and up rows as one 2F-row matrix, three tiles per wave, K
-      // split within the CUs: raw partial sums, then swiglu_reduce_kernel.
-      const int W = 2 * a.n_rows, blocks = (W + 191) / 192;
-      int n_split = std::min({kWideSplitMax, KS, std::max(1, cus / blocks)});
-      const int ks_per_split = (KS + n_split - 1) / n_split;
-      n_split = (KS + ks_per_split - 1) / ks_per_split;
-      if (n_split < 2 || !a.ypart || a.n_rows % 16 || a.ldo % 4 || (size_t)n_split * a.M * W > wide_ypart_floats(a.K)) {
-        launch_wide_t<2, EPI_SWIGLU>(a, (a.n_rows + 63) / 64, KS, 1, s);
-        break;
-      }
-      GemmArgs p = a;
-      p.kind = EPI_RESID;
-      p.n_rows = W;
-      p.n_seg[0] = a.n_rows;
-      p.n_seg[1] = a.n_rows;
-      p.n_seg[2] = 0;
-      launch_wide_t<3, EPI_RESID>(p, blocks, ks_per_split, n_split, s);
-      hipLaunchKernelGGL(swiglu_reduce_kernel, dim3((a.n_rows + kWideCols - 1) / kWideCols, (a.M + 7) / 8), dim3(256),
-                         0, s, a, n_split);
-      break;
-    }
-    case EPI_RESID: {
-      if (!a.ypart || a.n_rows % 16) return hipErrorInvalidValue;
-      // Three tiles per wave (each x slab serves 192 columns) and K split as far
-      // as the grid stays within the CUs (each split at least one k-step): the
-      // 7B O and down projections over 112 rows run 22 column blocks x 11
-      // splits.  (One tile per wave and 4 splits, then two tiles and 8 splits:
-      // the 16-sequence long-context verify 17.10 -> 16.50 ms, then
-      // 15.46-15.71 -> 15.11-15.25 ms, each on one box.)
-      const int blocks = (a.n_rows + 191) / 192;
-      int n_split = std::min(kWideSplitMax, std::max(1, cus / blocks));
-      n_split = std::min(n_split, KS);
-      const int ks_per_split = (KS + n_split - 1) / n_split;
-      n_split = (KS + ks_per_split - 1) / ks_per_split;
-      launch_wide_t<3, EPI_RESID>(a, blocks, ks_per_split, n_split, s);
-      hipLaunchKernelGGL(resid_reduce_kernel, dim3((a.n_rows + kWideCols - 1) / kWideCols, (a.M + 7) / 8),
-                         dim3(256), 0, s, a, n_split);
-      break;
-    }
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-}  // namespace
 
 // INT4 passes of at most 16 rows on gemm_q4_lds: hipErrorNotSupported where
 // its register budget does not cover the shape (the caller then runs the
@@ -2031,7 +1214,7 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
   if (a.wide) {
     if (a.q4) return hipErrorInvalidValue;  // (INT4 weights run passes of at most 64 rows)
     if (dtype != SPECDEC_BF16 || (a.kind == EPI_RESID && (!a.gain_bf16 || a.n_rows % 4))) return hipErrorInvalidValue;
-    return launch_wide(a, s);
+    return launch_gemm_tile(a, s);
   }
   if (a.M > kMaxGemmRows) return hipErrorInvalidValue;
   if (dtype == SPECDEC_BF16 && a.M > kSkinnyRows) return launch_gemm_rows(a, s);

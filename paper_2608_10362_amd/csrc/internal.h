@@ -60,12 +60,16 @@ enum EpiKind { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
 constexpr int kMaxGemmRows = 64;  // rows of x per launch of the skinny kernels (callers split larger M)
 constexpr int kSkinnyRows = 16;   // bf16 weights: passes of more rows run launch_gemm_rows (to kMaxGemmRows)
 constexpr int kRowsSplitMax = 8;  // K splits of its residual GEMMs (partials in ypart: kRowsSplitMax * M * n_rows)
-// Passes of more than kMaxGemmRows bf16 rows run the wide kernel in launches of
-// up to gemm_launch_rows() rows; residual GEMMs there split K over the grid
-// and need ypart = wide_ypart_floats(n_rows) floats.
+// Passes of more than kMaxGemmRows bf16 rows run launch_gemm_tile in launches
+// of up to kTileLaunchRows rows; GEMMs that split K over the grid there need
+// ypart (tile_ypart_floats(d_model) floats).
 bool gemm_wide(int dtype, int M);
 int gemm_launch_rows(int dtype, int M);
-size_t wide_ypart_floats(int n_rows);
+constexpr int kTileLaunchRows = 1024;
+constexpr int kTilePartialRows = 2048;  // split-K partials of a residual GEMM: n_split * rows <= this
+constexpr int kTileSplitMax = 12;
+constexpr int kTileReduceCols = 128;  // columns per RMSNorm partial of passes of more than kSkinnyRows rows
+size_t tile_ypart_floats(int d_model);
 
 struct GemmArgs {
   const float* x;      // [M, ldx] (for normalised inputs: h * gain, the producer applies the gain)
@@ -90,13 +94,13 @@ struct GemmArgs {
   float* qr;              // [M, H, hd] rotated queries
   KvLayout kv;
   int layer, n_heads, n_kv_heads, head_dim;
-  // wide passes
   int wide;               // 1: the whole pass has more than kMaxGemmRows rows (set by the caller for every launch)
-  float* ypart;           // RESID: split-K partial sums, wide_ypart_floats(n_rows) floats
-  // Passes of at most kMaxGemmRows rows, bf16 weights: x also as a stacked
-  // operand (put_stacked, stt fragments per k-step), read instead of x when xs
-  // is set; RESID and SwiGLU epilogues write their output stacked into xs_out
-  // (over more than kSkinnyRows rows in place of xg_out and out).
+  float* ypart;           // split-K partial sums, ypart_floats floats
+  size_t ypart_floats;
+  // x as a stacked operand (put_stacked, stt fragments per k-step), read
+  // instead of x when xs is set (always over more than kSkinnyRows rows); RESID
+  // and SwiGLU epilogues write their output stacked into xs_out (there in place
+  // of xg_out and out).
   const uint16_t* xs;
   uint16_t* xs_out;
   int stt;
@@ -124,6 +128,8 @@ hipError_t launch_pack_int4(const void* src, void* frag, void* scale, int N, int
 int gemm_row_blocks(int dtype, int kind, int n_rows, int M);
 // GEMMs of 17 to 64 rows over the stacked operand, bf16 or INT4 weights (gemm_rows.hip).
 hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s);
+// bf16 GEMMs of passes of more than 64 rows (gemm_tile.hip).
+hipError_t launch_gemm_tile(const GemmArgs& a, hipStream_t s);
 // Ordered sum of a residual GEMM's split-K partials (ypart), residual add, next RMSNorm input and its sums of squares.
 hipError_t launch_resid_reduce(const GemmArgs& a, int n_split, hipStream_t s);
 hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s);

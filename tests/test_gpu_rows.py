@@ -1,5 +1,5 @@
-"""Passes of 17 to 128 rows (the streaming GEMMs over the stacked operand)
-against the float64 oracle, at the edges of their row tiles, on shapes whose
+"""Passes of more than 16 rows (the GEMMs over the stacked operand: streaming
+to 64 rows, tiles above) against the float64 oracle, at the edges of their row tiles, on shapes whose
 tile counts leave remainders in every unit size and fewer k-steps than waves,
 and at the 7B widths that take the large units."""
 import numpy as np
@@ -31,7 +31,13 @@ def test_odd_shape_rows(B, g):
     _rows_case(ODD, 2, [1 + (37 * b) % 90 for b in range(B)], g, seed=B)
 
 
-@pytest.mark.parametrize("B,g", [(3, 5), (8, 4), (8, 6), (16, 3)])
+# (the tile kernel: more than 64 rows, row tiles of 96, 128 and 256 with remainders, launches of 1024 rows)
+@pytest.mark.parametrize("B,g", [(13, 4), (16, 4), (12, 7), (97, 0), (16, 7), (43, 2), (50, 5), (75, 7), (130, 7)])
+def test_odd_shape_tile_rows(B, g):
+    _rows_case(ODD, 2, [1 + (37 * b) % 90 for b in range(B)], g, seed=B)
+
+
+@pytest.mark.parametrize("B,g", [(3, 5), (8, 4), (8, 6), (16, 3), (9, 7), (16, 6), (32, 7), (56, 8)])
 def test_7b_width_rows(B, g):
     _rows_case(synth.LLAMA_7B, 1, [40 + 13 * b for b in range(B)], g, seed=B)
 
