@@ -282,7 +282,10 @@ hipError_t gemm_rows(int dtype, GemmArgs g, int M, hipStream_t s) {
 
 // One forward pass over M = B*rps rows described by `ra` (mode, token source),
 // writing logits [M, V] to `logits`.  ctx_bound: host upper bound of pos+1.
-specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int ctx_bound, float* logits,
+// kv_only (prefill): the pass only has to leave its keys and values in the
+// cache, so it ends with the last layer's K and V projections; what follows
+// them is recorded for specdec_time_kernel but not launched.
+specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int ctx_bound, float* logits, bool kv_only,
                        hipStream_t s) {
   const specdec_model_desc& d = m->desc;
   const int M = ra.M, dt = d.dtype;
@@ -308,6 +311,8 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   ra.rope_cs = m->rope_cs;
   ra.h = m->h;
   ra.ss = m->ss;
+  // (the attention's check of the host's bound, where the pass runs no attention)
+  ra.max_ctx = kv_only && m->n_layers == 1 ? ctx_bound : kv->capacity;
   // bf16 passes (INT4 weights: of more than 16 rows) hand x from kernel to kernel as a
   // stacked operand (put_stacked): the GEMMs then read 16-byte fragments (one
   // per k-step over at most 8 rows, two per 16 rows above) instead of float32
@@ -374,6 +379,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   at.stt = stt;
 
   for (int l = 0; l < m->n_layers; ++l) {
+    const bool last_kv = kv_only && l + 1 == m->n_layers;
     GemmArgs q = base;  // RMSNorm + Q|K|V projections
     q.x = m->xg; q.ldx = d.d_model; q.ss_in = m->ss; q.n_ss = n_ss;
     q.K = d.d_model;
@@ -389,7 +395,12 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
     if (stk) q.xs = m->xs_d;
     {
       Timed t(SPECDEC_KERNEL_QKV, s);
-      SD_TRY(gemm_rows(dt, q, M, s));
+      GemmArgs run = q;
+      if (last_kv && dt == SPECDEC_BF16) {  // K and V alone
+        run.w[0] = q.w[1]; run.n_seg[0] = 0; run.n_rows -= q.n_seg[0];
+        if (q4) run.wscale[0] = q.wscale[1];
+      }
+      SD_TRY(gemm_rows(dt, run, M, s));
     }
     rec(SPECDEC_KERNEL_QKV, l, q);
 
@@ -402,7 +413,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
       Timed t(SPECDEC_KERNEL_ROPE_APPEND, s);
       SD_TRY(launch_rope_append(at, s));
     }
-    {
+    if (!last_kv) {
       Timed t(SPECDEC_KERNEL_ATTENTION, s);
       SD_TRY(launch_attention(at, s));
     }
@@ -419,7 +430,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
     o.out = m->h; o.ldo = d.d_model; o.ss_out = m->ss; o.xg_out = m->xg; o.gain_out = m->ffn_norm[l];
     if (q4) { o.q4 = 1; o.wscale[0] = m->so[l]; }
     if (stk) { o.xs = m->xs_f; o.xs_out = m->xs_d; }
-    {
+    if (!last_kv) {
       Timed t(SPECDEC_KERNEL_O_PROJ, s);
       SD_TRY(gemm_rows(dt, o, M, s));
     }
@@ -433,7 +444,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
     gu.n_rows = d.ffn_dim; gu.kind = EPI_SWIGLU; gu.out = m->u; gu.ldo = d.ffn_dim;
     if (q4) { gu.q4 = 1; gu.wscale[0] = m->sg[l]; gu.wscale[1] = m->su[l]; }
     if (stk) { gu.xs = m->xs_d; gu.xs_out = m->xs_f; }
-    {
+    if (!last_kv) {
       Timed t(SPECDEC_KERNEL_GATE_UP, s);
       SD_TRY(gemm_rows(dt, gu, M, s));
     }
@@ -447,7 +458,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
     if (q4) { dn.q4 = 1; dn.wscale[0] = m->sd[l]; }
     if (stk) { dn.xs = m->xs_f; dn.xs_out = m->xs_d; }
     else if (head_stk && l + 1 == m->n_layers) dn.xs_out = m->xs_d;
-    {
+    if (!last_kv) {
       Timed t(SPECDEC_KERNEL_DOWN, s);
       SD_TRY(gemm_rows(dt, dn, M, s));
     }
@@ -459,7 +470,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   hd_.K = d.d_model; hd_.w[0] = m->lm_head; hd_.n_seg[0] = d.vocab; hd_.n_rows = d.vocab;
   hd_.kind = EPI_STORE; hd_.out = logits; hd_.ldo = d.vocab;
   if (stk || head_stk) hd_.xs = m->xs_d;
-  {
+  if (!kv_only) {
     Timed t(SPECDEC_KERNEL_LM_HEAD, s);
     SD_TRY(gemm_rows(dt, hd_, M, s));
   }
@@ -759,7 +770,7 @@ specdec_status specdec_prefill(const specdec_model* model, specdec_kv* kv, int32
     ra.tok_src = tokens;
     ra.ld_tok = n;
     ra.c0 = c0;
-    st = forward(model, kv, ra, (int)std::min<int64_t>(kv->len_upper + c0 + rps, kv->capacity), model->logits, s);
+    st = forward(model, kv, ra, (int)std::min<int64_t>(kv->len_upper + c0 + rps, kv->capacity), model->logits, true, s);
     if (st != SPECDEC_OK) return st;
   }
   hipLaunchKernelGGL(prefill_finish_kernel, dim3(1), dim3(64), 0, s, B, n, tokens, kv_len(kv), kv_pending(kv),
@@ -795,7 +806,7 @@ specdec_status specdec_draft_step(const specdec_model* draft, specdec_kv* kv, in
   }
   ra.M = B * ra.rps;
   if (ra.M > draft->max_rows) return SPECDEC_ERR_SHAPE;
-  st = forward(draft, kv, ra, (int)(kv->len_upper + slot + 2), draft->logits, s);
+  st = forward(draft, kv, ra, (int)(kv->len_upper + slot + 2), draft->logits, false, s);
   if (st != SPECDEC_OK) return st;
   DraftFinishArgs f{};
   f.B = B;
@@ -833,7 +844,7 @@ specdec_status specdec_verify(const specdec_model* target, specdec_kv* kv, int32
   ra.tok_src = d;
   ra.ld_tok = ld_d;
   if (ra.M > target->max_rows) return SPECDEC_ERR_SHAPE;
-  return forward(target, kv, ra, (int)(kv->len_upper + gamma + 1), logits_out, (hipStream_t)stream);
+  return forward(target, kv, ra, (int)(kv->len_upper + gamma + 1), logits_out, false, (hipStream_t)stream);
 }
 
 specdec_status specdec_packed_range(const specdec_model_desc* desc, int32_t first_layer, int32_t n_layers,

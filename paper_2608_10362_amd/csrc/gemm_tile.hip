@@ -301,10 +301,11 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(GemmArgs a, int n_sp
   const int tid = threadIdx.x, m = (int)blockIdx.y * 8 + (tid >> 5);
   const int f = (int)blockIdx.x * kReduceCols + 4 * (tid & 31);
   const int M = a.M, F = a.n_rows, W = 2 * F;
+  // (the splits' loads are issued before the row scales wait for anything)
+  const float* yp = a.ypart + (size_t)min(m, M - 1) * W + min(f, F - 4);
+  const f32x4 gs = sum_splits(yp, (size_t)M * W, n_split), us = sum_splits(yp + F, (size_t)M * W, n_split);
   row_scales8(a, (int)blockIdx.y * 8, s_scale, s_ss);
   if (m >= M || f >= F) return;
-  const float* yp = a.ypart + (size_t)m * W;
-  const f32x4 gs = sum_splits(yp + f, (size_t)M * W, n_split), us = sum_splits(yp + F + f, (size_t)M * W, n_split);
   const float sc = s_scale[tid >> 5];
   f32x4 o;
 #pragma unroll
@@ -326,10 +327,10 @@ __global__ __launch_bounds__(256) void qkv_reduce_kernel(GemmArgs a, int n_split
   const int tid = threadIdx.x, m = (int)blockIdx.y * 8 + (tid >> 5);
   const int n = (int)blockIdx.x * kReduceCols + 4 * (tid & 31);
   const int M = a.M;
-  row_scales8(a, (int)blockIdx.y * 8, s_scale, s_ss);
   const bool live = m < M && n < a.n_rows;
-  f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (live) y = sum_splits(a.ypart + (size_t)m * a.n_rows + n, (size_t)M * a.n_rows, n_split);
+  // (the splits' loads are issued before the row scales wait for anything)
+  f32x4 y = sum_splits(a.ypart + (size_t)min(m, M - 1) * a.n_rows + min(n, a.n_rows - 4), (size_t)M * a.n_rows, n_split);
+  row_scales8(a, (int)blockIdx.y * 8, s_scale, s_ss);
   const float sc = s_scale[tid >> 5];
   f32x4 z;  // (every lane takes part in the shuffles)
 #pragma unroll

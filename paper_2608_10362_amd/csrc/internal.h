@@ -147,6 +147,7 @@ struct RowsArgs {
   int slot;               // DRAFT_NEXT
   int c0;                 // PREFILL: first token index of this chunk
   int capacity, vocab, d_model, head_dim;
+  int max_ctx;            // status KV_CAPACITY where a row's pos + 1 exceeds it
   double rope_base;
   const void* embed;      // [V, d] storage type
   const void* gain;       // [d] first layer's attention RMSNorm gain

@@ -142,6 +142,8 @@ __global__ __launch_bounds__(256) void rows_embed_kernel(RowsArgs a) {
     if (pos < 0 || pos >= a.capacity) {
       if (threadIdx.x == 0) set_status(a.status, kStatusKvCapacity);
       valid = 0;
+    } else if (pos >= a.max_ctx && threadIdx.x == 0) {
+      set_status(a.status, kStatusKvCapacity);  // the host's bound was wrong
     }
   }
   if (!valid) {
