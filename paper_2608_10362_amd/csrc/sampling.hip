@@ -86,20 +86,11 @@ __device__ int block_draw(RF rf, int V, uint32_t x, SampShared& sh) {
   return sh.token;
 }
 
-// Online (max, sum exp) of z_j = row[j] / T over a row, block-wide, one pass.
-// Elements are read four at a time when the row is 16-byte aligned.  The
-// per-thread states are merged in a fixed order (deterministic).
+// (max, sum exp) of z_j = row[j] / T over part of a row; states are merged in a
+// fixed order (deterministic).
 struct MaxSum {
   float m, s;
 };
-__device__ __forceinline__ void ms_add(MaxSum& a, float z) {
-  if (z > a.m) {
-    a.s = a.s * expf(a.m - z) + 1.0f;
-    a.m = z;
-  } else {
-    a.s += expf(z - a.m);
-  }
-}
 __device__ __forceinline__ MaxSum ms_merge(MaxSum a, MaxSum b) {
   if (b.m == -INFINITY) return a;
   if (a.m == -INFINITY) return b;
@@ -108,10 +99,17 @@ __device__ __forceinline__ MaxSum ms_merge(MaxSum a, MaxSum b) {
 }
 
 // ---------------------------------------------------------------- rows + embedding
+// Grid (rows, 2): block (r, 0) gathers and scales row r's embedding, block (r,
+// 1) computes its RoPE table (in float64: the angle of position p at float32
+// resolution needs it) with one thread per cosine and one per sine.  Both are
+// latency chains (the table's pow, then cos or sin; the row's state words,
+// then its embedding), so they run side by side: 13.2 us for the two one after
+// the other over 5 rows of the 7B shape, 6.8 now.
 template <typename ET>
 __global__ __launch_bounds__(256) void rows_embed_kernel(RowsArgs a) {
   __shared__ float red[16];
   const int r = blockIdx.x, b = r / a.rps, i = r % a.rps;
+  const bool first = blockIdx.y == 0 && threadIdx.x == 0;  // (writes the row's descriptor and status)
   int pos = 0, tok = 0, valid = 1;
   switch (a.mode) {
     case ROWS_VERIFY:
@@ -136,13 +134,13 @@ __global__ __launch_bounds__(256) void rows_embed_kernel(RowsArgs a) {
   }
   if (valid) {
     if (tok < 0 || tok >= a.vocab) {
-      if (threadIdx.x == 0) set_status(a.status, kStatusBadToken);
+      if (first) set_status(a.status, kStatusBadToken);
       valid = 0;
     }
     if (pos < 0 || pos >= a.capacity) {
-      if (threadIdx.x == 0) set_status(a.status, kStatusKvCapacity);
+      if (first) set_status(a.status, kStatusKvCapacity);
       valid = 0;
-    } else if (pos >= a.max_ctx && threadIdx.x == 0) {
+    } else if (pos >= a.max_ctx && first) {
       set_status(a.status, kStatusKvCapacity);  // the host's bound was wrong
     }
   }
@@ -150,26 +148,33 @@ __global__ __launch_bounds__(256) void rows_embed_kernel(RowsArgs a) {
     tok = 0;
     pos = 0;
   }
-  if (threadIdx.x == 0) a.rows[r] = RowDesc{b, pos, tok, valid};
-  const int hd = a.head_dim, half = hd / 2;
-  for (int j = threadIdx.x; j < half; j += blockDim.x) {
-    const double inv_freq = pow(a.rope_base, -2.0 * (double)j / (double)hd);
-    const double ang = (double)pos * inv_freq;
-    a.rope_cs[(size_t)r * hd + j] = (float)cos(ang);
-    a.rope_cs[(size_t)r * hd + half + j] = (float)sin(ang);
+  if (blockIdx.y == 1) {
+    const int hd = a.head_dim, half = hd / 2;
+    for (int k = threadIdx.x; k < hd; k += blockDim.x) {
+      const int j = k < half ? k : k - half;
+      const double inv_freq = pow(a.rope_base, -2.0 * (double)j / (double)hd);
+      const double ang = (double)pos * inv_freq;
+      a.rope_cs[(size_t)r * hd + k] = (float)(k < half ? cos(ang) : sin(ang));
+    }
+    return;
   }
+  if (first) a.rows[r] = RowDesc{b, pos, tok, valid};
   const ET* e = (const ET*)a.embed + (size_t)tok * a.d_model;
   const ET* gn = (const ET*)a.gain;
   float* h = a.h + (size_t)r * a.d_model;
   float* xg = a.xg + (size_t)r * a.d_model;
   float ss = 0.f;
-  for (int k = threadIdx.x; k < a.d_model; k += blockDim.x) {
-    const float v = Storage<ET>::load(e + k);
-    h[k] = v;
-    const float xv = v * Storage<ET>::load(gn + k);
-    if (a.xs) put_stacked(a.xs, a.stt, r, k, xv);
-    else xg[k] = xv;
-    ss += v * v;
+  for (int k = 4 * threadIdx.x; k < a.d_model; k += 4 * blockDim.x) {  // (d_model % 64 == 0)
+    f32x4 v, x;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = Storage<ET>::load(e + k + q);
+      x[q] = v[q] * Storage<ET>::load(gn + k + q);
+    }
+    *(f32x4*)(h + k) = v;
+    if (a.xs) put_stacked4(a.xs, a.stt, r, k, x);
+    else *(f32x4*)(xg + k) = x;
+    ss += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
   }
   ss = block_sum(ss, red);
   if (threadIdx.x == 0) a.ss[r] = ss;
@@ -190,11 +195,14 @@ __host__ __device__ __forceinline__ int n_chunks(int V) {
   int nc = (V + 511) / 512;  // (512-entry chunks: 63 blocks per 32000-entry row; 1024 and 2048 were slower)
   return nc < 1 ? 1 : (nc > 64 ? 64 : nc);
 }
-__host__ __device__ __forceinline__ int chunk_size(int V) { return (V + n_chunks(V) - 1) / n_chunks(V); }
+// (whole quads: only a row's own end is ragged; the last chunk may be short or empty)
+__host__ __device__ __forceinline__ int chunk_size(int V) { return ((V + n_chunks(V) - 1) / n_chunks(V) + 3) / 4 * 4; }
 
 struct StatPart {
   float m, s, amax_v;
-  int amax_i, bad, pad0, pad1, pad2;
+  int amax_i, bad;
+  uint32_t count;  // of a sequence's first part: blocks of the decide-and-draw launch done (a line of its own per sequence)
+  int pad0, pad1;
 };
 struct DrawPart {
   unsigned long long res, prob;
@@ -209,7 +217,6 @@ struct SeqState {
 struct Scratch {
   StatPart* stats;  // [rows_total][NC]
   DrawPart* draw;   // [B][NC]
-  uint32_t* count;  // [B] blocks of the decide-and-draw launch done (zeroed by the stats launch)
 };
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 __host__ __device__ inline Scratch carve(void* base, int B, int rows, int V) {
@@ -219,15 +226,25 @@ __host__ __device__ inline Scratch carve(void* base, int B, int rows, int V) {
   s.stats = (StatPart*)p;
   p += align256(sizeof(StatPart) * (size_t)B * rows * NC);
   s.draw = (DrawPart*)p;
-  p += align256(sizeof(DrawPart) * (size_t)B * NC);
-  s.count = (uint32_t*)p;
   return s;
 }
 
-// p_i(j) of row i: softmax(l/T) from merged statistics, or the probability itself.
-__device__ __forceinline__ float prob_of(const float* row, int j, bool logits, float T, float2 ms) {
-  const float v = row[j];
-  return logits ? expf(v / T - ms.x) / ms.y : v;
+// Four consecutive entries of a row of V from j (a multiple of 4), `pad` past
+// j1 (a multiple of 4, or V).
+__device__ __forceinline__ void load_quad(const float* row, int j, int j1, int V, float pad, float (&v)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = pad;
+  if ((V & 3) == 0 || j + 4 <= j1) {  // (first test uniform: whole quads need no second path)
+    if (j < j1) {
+      const f32x4 t = *(const f32x4_a4*)(row + j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = t[e];
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (j + e < j1) v[e] = row[j + e];
+  }
 }
 
 // stats: grid (NC, B * rows_per_seq), block 256.  Row i of sequence b is
@@ -235,38 +252,70 @@ __device__ __forceinline__ float prob_of(const float* row, int j, bool logits, f
 // Every value of the row, and of the row `chk` pairs with it (the draft's q
 // row i of an accept, rows i < chk_rows), must be finite.
 // It also zeroes the sequence's counter of the decide-and-draw launch that follows.
+// Two quads per thread and round, all loaded before the first is used; the
+// block's maximum first (the argmax with it), then exponentials relative to it,
+// which neither wait for one another nor need merging by further ones.  Bound:
+// a block's latency chain (one load round trip, two reductions) for a single
+// row; over 16 x 7 rows of 128256 entries (107 MB with the drafts' rows) the
+// exponentials and divisions, 43.5 us with one entry per load and an online
+// maximum.
 __global__ __launch_bounds__(kChunkThreads) void stats_kernel(const float* x, int V, int rows_per_seq, int row_stride,
                                                               int row_off, float T, const float* chk, int chk_rows,
-                                                              StatPart* out, uint32_t* count) {
+                                                              StatPart* out) {
   __shared__ float sm_m[4], sm_s[4], sm_v[4];
   __shared__ int sm_i[4], sm_b[4];
   const int c = blockIdx.x, r = blockIdx.y, NC = gridDim.x;
   const int b = r / rows_per_seq, i = r % rows_per_seq;
-  if (c == 0 && i == 0 && threadIdx.x == 0) count[b] = 0u;
   const float* row = x + ((size_t)b * row_stride + row_off + i) * V;
   const int cs = chunk_size(V), j0 = c * cs, j1 = min(V, j0 + cs);
+  const float* crow = chk && i < chk_rows ? chk + ((size_t)b * chk_rows + i) * V : nullptr;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  constexpr int Q = 2, RND = 4 * Q * kChunkThreads;
   MaxSum st{-INFINITY, 0.f};
   float bv = -INFINITY;
   int bi = 0x7fffffff, bad = 0;
-  for (int j = j0 + threadIdx.x; j < j1; j += kChunkThreads) {
-    const float v = row[j];
-    bad |= !isfinite(v);
-    if (v > bv) { bv = v; bi = j; }
-    if (T > 0.f) ms_add(st, v / T);
-  }
-  if (chk && i < chk_rows) {
-    const float* crow = chk + ((size_t)b * chk_rows + i) * V;
-    for (int j = j0 + threadIdx.x; j < j1; j += kChunkThreads) bad |= !isfinite(crow[j]);
-  }
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int r0 = j0; r0 < j1; r0 += RND) {  // (block-uniform)
+    const int base = r0 + 4 * threadIdx.x;
+    float v[Q][4], u[Q][4];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    st = ms_merge(st, MaxSum{__shfl_xor(st.m, o, kWave), __shfl_xor(st.s, o, kWave)});
-    const float ov = __shfl_xor(bv, o, kWave);
-    const int oi = __shfl_xor(bi, o, kWave);
-    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-    bad |= __shfl_xor(bad, o, kWave);
+    for (int q = 0; q < Q; ++q) load_quad(row, base + 4 * q * kChunkThreads, j1, V, -INFINITY, v[q]);
+    if (crow) {  // (block-uniform)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) load_quad(crow, base + 4 * q * kChunkThreads, j1, V, 0.f, u[q]);
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bad |= !isfinite(u[q][e]);
+    }
+    // this thread's maximum, its lowest index, then the wave's (max, then the lowest index that holds it)
+    float mv = -INFINITY;
+    int mi = 0x7fffffff;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = base + 4 * q * kChunkThreads + e;
+        bad |= j < j1 && !isfinite(v[q][e]);
+        if (v[q][e] > mv) { mv = v[q][e]; mi = j; }
+      }
+    const float wv = wave_max(mv);
+    int wi = mv == wv ? mi : 0x7fffffff;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) wi = min(wi, __shfl_xor(wi, o, kWave));
+    if (wv > bv || (wv == bv && wi < bi)) { bv = wv; bi = wi; }
+    if (T > 0.f) {  // (z = v / T grows with v: the wave's maximum z is that of its largest entry)
+      const float m = fmaxf(st.m, T == 1.f ? wv : wv / T);
+      float sum = 0.f;
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum += expf((T == 1.f ? v[q][e] : v[q][e] / T) - m);  // (past the chunk: exp(-inf))
+      st.s = (st.m == -INFINITY ? 0.f : st.s * expf(st.m - m)) + sum;
+      st.m = m;
+    }
   }
+  st.s = wave_sum(st.s);  // (st.m and the argmax are the wave's already)
+  bad = __any(bad);
   if (lane == 0) { sm_m[w] = st.m; sm_s[w] = st.s; sm_v[w] = bv; sm_i[w] = bi; sm_b[w] = bad; }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -278,30 +327,30 @@ __global__ __launch_bounds__(kChunkThreads) void stats_kernel(const float* x, in
       if (sm_v[k] > tv || (sm_v[k] == tv && sm_i[k] < ti)) { tv = sm_v[k]; ti = sm_i[k]; }
       tb |= sm_b[k];
     }
-    out[(size_t)r * NC + c] = StatPart{t.m, t.s, tv, ti, tb, 0, 0, 0};
+    out[(size_t)r * NC + c] = StatPart{t.m, t.s, tv, ti, tb, 0u, 0, 0};
   }
 }
 
 // Merge the chunk statistics of one row across a wave: lane k holds chunk k
-// (NC <= 64), xor butterfly (every lane ends with the same, deterministic
-// result: each merge is symmetric in its operands).
+// (NC <= 64).  The row's maximum, then each chunk's sum relative to it, added
+// by a fixed shuffle tree: every lane ends with the same, deterministic result.
 __device__ StatPart wave_merge_stats(const StatPart* parts, int NC) {
   const int lane = threadIdx.x & 63;
-  StatPart p{-INFINITY, 0.f, -INFINITY, 0x7fffffff, 0, 0, 0, 0};
+  StatPart p{-INFINITY, 0.f, -INFINITY, 0x7fffffff, 0, 0u, 0, 0};
   if (lane < NC) p = parts[lane];
+  const float m = wave_max(p.m), v = wave_max(p.amax_v);
+  int i = p.amax_v == v ? p.amax_i : 0x7fffffff;
+  float s = p.m == -INFINITY ? 0.f : p.s * expf(p.m - m);
 #pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const MaxSum t = ms_merge(MaxSum{p.m, p.s}, MaxSum{__shfl_xor(p.m, o, kWave), __shfl_xor(p.s, o, kWave)});
-    const float ov = __shfl_xor(p.amax_v, o, kWave);
-    const int oi = __shfl_xor(p.amax_i, o, kWave);
-    if (ov > p.amax_v || (ov == p.amax_v && oi < p.amax_i)) {
-      p.amax_v = ov;
-      p.amax_i = oi;
-    }
-    p.bad |= __shfl_xor(p.bad, o, kWave);
-    p.m = t.m;
-    p.s = t.s;
+  for (int o = 32; o > 0; o >>= 1) {
+    i = min(i, __shfl_xor(i, o, kWave));
+    s += __shfl_xor(s, o, kWave);
   }
+  p.m = m;
+  p.s = s;
+  p.amax_v = v;
+  p.amax_i = i;
+  p.bad = __any(p.bad);
   return p;
 }
 
@@ -333,18 +382,24 @@ struct DrawArgs {
   int32_t* status;
 };
 
-// R_j weights of sequence b at column j, for the residual (res) and the plain row (prob).
-__device__ __forceinline__ void weights_at(const DrawArgs& a, const SeqState& st, int b, int j, float& res, float& prob) {
-  if (a.mode == W_ACCEPT) {
-    const int A = st.A, g = a.gamma;
-    const float* P = a.p + ((size_t)b * (g + 1) + A) * a.V;
-    const float pj = prob_of(P, j, a.logits, a.T, st.ms[A]);
-    prob = pj;
-    res = A < g ? fmaxf(0.f, __fsub_rn(pj, a.q[((size_t)b * g + A) * a.V + j])) : 0.f;
-  } else {
-    const float* lg = a.lg + ((size_t)b * a.rps + a.rps - 1) * a.V;
-    prob = expf(lg[j] / a.T - st.ms[0].x) / st.ms[0].y;
-    res = 0.f;
+// R_j weights of sequence b at the four columns from j (past j1: 0), for the
+// residual (res) and the plain row (prob).
+__device__ __forceinline__ void weights_quad(const DrawArgs& a, const SeqState& st, int b, int j, int j1, float (&res)[4],
+                                             float (&prob)[4]) {
+  const bool accept = a.mode == W_ACCEPT;
+  const int A = accept ? st.A : 0, g = a.gamma;
+  const float* P = accept ? a.p + ((size_t)b * (g + 1) + A) * a.V : a.lg + ((size_t)b * a.rps + a.rps - 1) * a.V;
+  const bool resid = accept && A < g;
+  float v[4], q[4] = {0.f, 0.f, 0.f, 0.f};
+  load_quad(P, j, j1, a.V, 0.f, v);
+  if (resid) load_quad(a.q + ((size_t)b * g + A) * a.V, j, j1, a.V, 0.f, q);
+  const bool softmax = !accept || a.logits;
+  const float2 ms = st.ms[A];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float p = softmax ? expf((a.T == 1.f ? v[e] : v[e] / a.T) - ms.x) / ms.y : v[e];
+    prob[e] = j + e < j1 ? p : 0.f;
+    res[e] = resid && j + e < j1 ? fmaxf(0.f, __fsub_rn(p, q[e])) : 0.f;
   }
 }
 
@@ -370,11 +425,23 @@ __global__ __launch_bounds__(kChunkThreads) void decide_draw_kernel(DrawArgs a) 
   const int c = blockIdx.x, b = blockIdx.y, V = a.V, NC = gridDim.x, cs = chunk_size(V);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   Scratch sc = carve(a.scratch, a.B, a.rows, V);
+  uint32_t* const count = &sc.stats[(size_t)b * a.rows * NC].count;
   const bool accept = a.mode == W_ACCEPT;
   const int g = accept ? a.gamma : 0;
   const float T = a.T;
   const uint64_t step = a.step_dev ? *a.step_dev : a.step;
   if (threadIdx.x == 0) bad_rows = 0;
+  // The accept tests' operands (lane i < g of wave 0: draft position i), on
+  // their way while the row statistics are merged.
+  int di = 0;
+  float pv = 0.f, qv = 0.f;
+  if (accept && w == 0 && lane < g) {
+    di = a.d[(size_t)b * a.ld_d + lane];
+    if (T > 0.f && di >= 0 && di < V) {
+      pv = a.p[((size_t)b * (g + 1) + lane) * V + di];
+      qv = a.q[((size_t)b * g + lane) * V + di];
+    }
+  }
   __syncthreads();
   // row statistics (wave w: rows w, w + 4, ...)
   for (int r = w; r <= g; r += kChunkThreads / kWave) {
@@ -391,20 +458,17 @@ __global__ __launch_bounds__(kChunkThreads) void decide_draw_kernel(DrawArgs a) 
     int bad = bad_rows, A = g;
     if (accept && !bad) {
       // lane i < g: event of draft position i (1 = rejection, 2 = error)
-      const int32_t* d = a.d + (size_t)b * a.ld_d;
       int ev = 0;
       if (lane < g) {
-        const int di = d[lane];
         if (T == 0.f) {
           ev = amax[lane] != di ? 1 : 0;
         } else if (di < 0 || di >= V) {
           ev = 2;
         } else {
-          const float pd = prob_of(a.p + ((size_t)b * (g + 1) + lane) * V, di, a.logits, T, st.ms[lane]);
-          const float qd = a.q[((size_t)b * g + lane) * V + di];
+          const float pd = a.logits ? expf(pv / T - st.ms[lane].x) / st.ms[lane].y : pv;
           const uint32_t wd = a.rand ? a.rand[(size_t)b * (g + 1) + lane]
                                      : draw_word(a.seed, b, step, SPECDEC_PURPOSE_ACCEPT, lane);
-          ev = !isfinite(qd) ? 2 : (!(__fmul_rn(word_to_uniform(wd), qd) < pd) ? 1 : 0);
+          ev = !isfinite(qv) ? 2 : (!(__fmul_rn(word_to_uniform(wd), qv) < pd) ? 1 : 0);
         }
       }
       const unsigned long long hit = __ballot(ev != 0);
@@ -437,12 +501,25 @@ __global__ __launch_bounds__(kChunkThreads) void decide_draw_kernel(DrawArgs a) 
     const int j0 = c * cs, j1 = min(V, j0 + cs);
     unsigned long long r_sum = 0, p_sum = 0;
     float* qo = !accept && a.q_out ? a.q_out + ((size_t)b * a.gamma + a.slot) * V : nullptr;
-    for (int j = j0 + threadIdx.x; j < j1; j += kChunkThreads) {
-      float res, prob;
-      weights_at(a, st, b, j, res, prob);
-      if (qo) qo[j] = prob;
-      r_sum += fp_weight(res);
-      p_sum += fp_weight(prob);
+    constexpr int Q = 2;  // quads per thread and round (their loads overlap)
+    for (int base = j0 + 4 * threadIdx.x; base < j1; base += 4 * Q * kChunkThreads) {
+      float res[Q][4], prob[Q][4];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) weights_quad(a, st, b, base + 4 * q * kChunkThreads, j1, res[q], prob[q]);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int j = base + 4 * q * kChunkThreads;
+        if (qo) {
+          if (j + 4 <= j1) *(f32x4_a4*)(qo + j) = f32x4{prob[q][0], prob[q][1], prob[q][2], prob[q][3]};
+          else
+            for (int e = 0; j + e < j1; ++e) qo[j + e] = prob[q][e];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          r_sum += fp_weight(res[q][e]);
+          p_sum += fp_weight(prob[q][e]);
+        }
+      }
     }
     r_sum = wave_sum_u64(r_sum);
     p_sum = wave_sum_u64(p_sum);
@@ -456,9 +533,9 @@ __global__ __launch_bounds__(kChunkThreads) void decide_draw_kernel(DrawArgs a) 
       __hip_atomic_store(&dst->prob, dp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       // (the stores have completed before the count: the last block reads them with agent-scope loads)
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      const uint32_t old = __hip_atomic_fetch_add(sc.count + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t old = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       last = old == (uint32_t)(NC - 1);
-      if (last) __hip_atomic_store(sc.count + b, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (last) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     if (!last) return;
@@ -516,12 +593,10 @@ __global__ __launch_bounds__(kChunkThreads) void decide_draw_kernel(DrawArgs a) 
   unsigned long long mine[4], tot = 0;
   for (int base = j0; base < j1; base += 4 * kChunkThreads) {
     const int jj = base + 4 * threadIdx.x;
+    float res[4], prob[4];
+    weights_quad(a, st, b, jj, j1, res, prob);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float res = 0.f, prob = 0.f;
-      if (jj + e < j1) weights_at(a, st, b, jj + e, res, prob);
-      mine[e] = jj + e < j1 ? fp_weight(use_res ? res : prob) : 0ull;
-    }
+    for (int e = 0; e < 4; ++e) mine[e] = fp_weight(use_res ? res[e] : prob[e]);
     const unsigned long long sum4 = mine[0] + mine[1] + mine[2] + mine[3];
     unsigned long long incl = sum4;
 #pragma unroll
@@ -605,9 +680,9 @@ __global__ void commit_kernel(CommitArgs a) {
 
 hipError_t launch_rows_embed(int dtype, const RowsArgs& a, hipStream_t s) {
   if (dtype == SPECDEC_BF16)
-    hipLaunchKernelGGL((rows_embed_kernel<uint16_t>), dim3(a.M), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((rows_embed_kernel<uint16_t>), dim3(a.M, 2), dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL((rows_embed_kernel<float>), dim3(a.M), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((rows_embed_kernel<float>), dim3(a.M, 2), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -626,7 +701,7 @@ hipError_t launch_draft_finish(const DraftFinishArgs& a, hipStream_t s) {
   }
   Scratch sc = carve(a.scratch, a.B, 1, a.V);
   hipLaunchKernelGGL(stats_kernel, dim3(NC, a.B), dim3(kChunkThreads), 0, s, a.logits, a.V, 1, a.rps, a.rps - 1,
-                     a.temperature, nullptr, 0, sc.stats, sc.count);
+                     a.temperature, nullptr, 0, sc.stats);
   DrawArgs d{};
   d.mode = W_DRAFT;
   d.B = a.B;
@@ -686,7 +761,7 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t s) {
   const bool logits = a.input_kind == SPECDEC_INPUT_LOGITS;
   hipLaunchKernelGGL(stats_kernel, dim3(NC, a.B * (a.gamma + 1)), dim3(kChunkThreads), 0, s, a.p, a.V, a.gamma + 1,
                      a.gamma + 1, 0, logits ? a.temperature : 0.f, a.temperature > 0.f ? a.q : nullptr, a.gamma,
-                     sc.stats, sc.count);
+                     sc.stats);
   DrawArgs d{};
   d.mode = W_ACCEPT;
   d.B = a.B;
