@@ -13,6 +13,7 @@
 #include <algorithm>
 
 #include "device_common.h"
+#include "gemm_common.h"
 #include "internal.h"
 
 namespace specdec {
@@ -840,6 +841,194 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
   }
 }
 
+// ---------------------------------------------------------------- many query rows (bf16 cache)
+// Prefill chunks: enough query rows that K and V are worth sharing.  Block = 64
+// queries (4 tiles of 16) of one (kv head, sequence), 8 waves: wave w works on
+// tile w % 4 and on every second sub-chunk of 32 keys (w / 4).  Stages of two
+// sub-chunks are copied from the cache to LDS as they lie there (1 KB fragments
+// in MFMA order, ST stages in flight) and shared by the tiles; every block runs
+// through all of its keys, so nothing is written but the output: no partial
+// sums, no combine.
+// The scores are taken as K Q^T: D[4 (l/16) + r][l % 16] is a key row and a
+// query column, so a lane holds 8 scores of one query.  The K rows are read in
+// the order that leaves lane group g with keys 8g .. 8g+7 (row i of tile t: key
+// 8 (i/4) + 4t + i%4), which is the k order of V's fragments: P feeds O^T = V^T
+// P^T from the registers it was made in.  The running maximum is then one value
+// per lane (two lane swaps per sub-chunk), the sums stay per lane to the end.
+// Bound: the softmax's vector work and the products, 4 waves to a SIMD pair.
+template <int HD>
+__global__ __launch_bounds__(512) void attn_rows_kernel(AttnArgs a, int n_sub) {
+  constexpr int KST = HD / 32, DT = HD / 16, ST = 4;
+  constexpr int KP = 4 * KST, NP = KP + 2 * DT;  // 1 KB pieces of a stage: K of two sub-chunks, then V
+  constexpr int PW = (NP + 7) / 8;               // per wave
+  __shared__ u32x4 s_kv[ST][NP][kWave];
+  __shared__ int s_nk[4];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qt = wave & 3, kg = wave >> 2;
+  const int g = blockIdx.y, b = blockIdx.z;
+  const int H = a.n_heads, G = a.n_kv_heads, group = H / G;
+  const int rps = a.rps, r0 = b * rps, nq = rps * group;
+  const int c16 = lane & 15, grp = lane >> 4;
+  const uint16_t* kb = k_block<uint16_t>(a.kv, a.layer, b, g);
+
+  // This lane's query: qa of the sequence's rps * group.
+  const int qa = ((int)blockIdx.x * 4 + qt) * 16 + c16;
+  const int row = r0 + min(qa, nq - 1) / group, head = g * group + min(qa, nq - 1) % group;
+  const RowDesc rd = a.rows[row];
+  const bool live = qa < nq && rd.valid;
+  const int qpos = live ? rd.pos : -1;
+  int nk = qpos + 1, lo = live ? qpos : 0x7fffffff;  // keys of the tile; its lowest position
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) {
+    nk = max(nk, __shfl_xor(nk, o, kWave));
+    lo = min(lo, __shfl_xor(lo, o, kWave));
+  }
+  nk = __builtin_amdgcn_readfirstlane(nk);
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  if (kg == 0 && lane == 0) s_nk[qt] = nk;
+  if (live && qpos + 1 > a.max_ctx && grp == 0) set_status(a.status, kStatusKvCapacity);  // the host's bound was wrong
+
+  // Q as the B operand: lane = query l % 16, dims 32c + 8 (l/16) .. +7
+  bf16x8 qhi[KST], qlo[KST];
+  const float scale = 1.0f / sqrtf((float)HD);
+#pragma unroll
+  for (int c = 0; c < KST; ++c) {
+    const float* q = a.qr + ((size_t)row * H + head) * HD + 32 * c + 8 * grp;
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = qa < nq ? q[j] * scale : 0.f;
+    split_hilo(v, qhi[c], qlo[c]);
+  }
+  __syncthreads();
+  const int bnk = max(max(s_nk[0], s_nk[1]), max(s_nk[2], s_nk[3]));
+  const int n_here = min(n_sub, (bnk + kSubKeys - 1) / kSubKeys), n_st = (n_here + 1) / 2;
+
+  const __amdgpu_buffer_rsrc_t kr = make_rsrc(kb, (uint32_t)a.kv.capacity * HD * 2u);
+  const __amdgpu_buffer_rsrc_t vr = make_rsrc(kb + (size_t)a.kv.capacity * HD, (uint32_t)a.kv.capacity * HD * 2u);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&s_kv[0][0][0];
+  auto issue = [&](int st) {
+#pragma unroll
+    for (int i = 0; i < PW; ++i) {
+      const int p = wave * PW + i;
+      if (NP % 8 != 0 && p >= NP) break;
+      // (sub-chunks past the last one, in the last stages: the last one again)
+      const bool is_k = p < KP;
+      const int half = is_k ? p / (KP / 2) : (p - KP) / DT, f = is_k ? p % (KP / 2) : (p - KP) % DT;
+      const uint32_t sub = (uint32_t)min(2 * st + half, n_here - 1);
+      const uint32_t off = (sub * (uint32_t)(is_k ? KP / 2 : DT) + f) * 1024u + lane * 16u;
+      load_lds16(lds0 + ((uint32_t)(st % ST) * NP + p) * 1024u, off, is_k ? kr : vr);
+    }
+  };
+  floatx4 of[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) of[dt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  float mx = -INFINITY, sm = 0.f;
+
+  if (n_st > 0) {
+#pragma unroll
+    for (int i = 0; i < ST - 1; ++i) issue(i);
+  }
+  // K rows of tile t: key 8 (i/4) + 4t + i%4 of the sub-chunk, i = l % 16
+  const int kp0 = 8 * (c16 >> 2) + (c16 & 3);
+  for (int st = 0; st < n_st; ++st) {
+    wait_vm<(ST - 2) * PW>();
+    __syncthreads();  // (stage st has landed for every wave, and every wave is done with stage st - 1)
+    issue(st + ST - 1);
+    const int k0 = (2 * st + kg) * kSubKeys;
+    if (2 * st + kg >= n_here || k0 >= nk) continue;  // (wave-uniform)
+    const u32x4(*sk)[kWave] = &s_kv[st % ST][kg * (KP / 2)];
+    const u32x4(*sv)[kWave] = &s_kv[st % ST][KP + kg * DT];
+    floatx4 sf[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int p = kp0 + 4 * t;
+      floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < KST; ++c) {
+        const bf16x8 kk = __builtin_bit_cast(bf16x8, sk[(p >> 4) * KST + c][16 * grp + (p & 15)]);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, qhi[c], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk, qlo[c], acc, 0, 0, 0);
+      }
+      sf[t] = acc;
+    }
+    if (k0 + kSubKeys - 1 > lo) {  // (wave-uniform) some query does not see the whole sub-chunk
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (k0 + 8 * grp + 4 * t + r > qpos) sf[t][r] = -INFINITY;
+    }
+    float m = fmaxf(fmaxf(fmaxf(sf[0][0], sf[0][1]), fmaxf(sf[0][2], sf[0][3])),
+                    fmaxf(fmaxf(sf[1][0], sf[1][1]), fmaxf(sf[1][2], sf[1][3])));
+    m = fmaxf(m, __shfl_xor(m, 16, kWave));
+    m = fmaxf(m, __shfl_xor(m, 32, kWave));
+    const float mnew = fmaxf(mx, m);
+    if (__any(mnew > mx)) {  // (rescaled only where a maximum rose)
+      const float alpha = mx == -INFINITY ? 0.f : expf(mx - mnew);
+      sm *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) of[dt] *= alpha;
+      mx = mnew;
+    }
+    float pv[8];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        // (a query that has seen no key yet keeps the maximum -inf)
+        pv[4 * t + r] = mx == -INFINITY ? 0.f : expf(sf[t][r] - mx);
+        sm += pv[4 * t + r];
+      }
+    bf16x8 phi, plo;
+    split_hilo(pv, phi, plo);
+    const int nvalid = nk - (k0 + 8 * grp);
+    const bool tail = k0 + kSubKeys > nk;  // (wave-uniform) keys past the tile's: V zeroed, never multiply stale memory
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      u32x4 v = sv[dt][lane];
+      if (tail) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (2 * q >= nvalid) v[q] = 0u;
+          else if (2 * q + 1 >= nvalid) v[q] &= 0xffffu;
+        }
+      }
+      const bf16x8 vv = __builtin_bit_cast(bf16x8, v);
+      of[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, phi, of[dt], 0, 0, 0);
+      of[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv, plo, of[dt], 0, 0, 0);
+    }
+  }
+  sm += __shfl_xor(sm, 16, kWave);
+  sm += __shfl_xor(sm, 32, kWave);
+
+  // The two key halves of each tile: waves 4..7 park theirs in LDS, waves 0..3 add them.
+  wait_vm<0>();
+  __syncthreads();
+  float* park = (float*)&s_kv[0][0][0] + (size_t)qt * (4 * DT + 2) * kWave;
+  static_assert(4 * (4 * DT + 2) * kWave * 4 <= sizeof(s_kv), "parked sums fit in the stages");
+  if (kg == 1) {
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) park[(4 * dt + r) * kWave + lane] = of[dt][r];
+    park[4 * DT * kWave + lane] = mx;
+    park[(4 * DT + 1) * kWave + lane] = sm;
+  }
+  __syncthreads();
+  if (kg == 1 || qa >= nq) return;
+  const float m1 = park[4 * DT * kWave + lane], s1 = park[(4 * DT + 1) * kWave + lane], M = fmaxf(mx, m1);
+  const float e0 = mx == -INFINITY ? 0.f : expf(mx - M), e1 = m1 == -INFINITY ? 0.f : expf(m1 - M);
+  const float inv = live ? 1.0f / (e0 * sm + e1 * s1) : 0.f;
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) {
+    f32x4 o;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      o[r] = live ? (e0 * of[dt][r] + e1 * park[(4 * dt + r) * kWave + lane]) * inv : 0.f;
+    put_stacked4(a.xs, a.stt, row, head * HD + 16 * dt + 4 * grp, o);
+  }
+}
+
 // ---------------------------------------------------------------- combine
 // Block (head, row): weights w_c = exp(m_c - max_c m_c) of the row's chunks
 // in LDS (fixed-order reductions), then o = sum_c w_c o_c / sum_c w_c l_c with
@@ -1055,6 +1244,19 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
     if (n_sub * kSubKeys > a.kv.capacity || n_sub > a.n_split * (a.chunk / kSubKeys)) return hipErrorInvalidValue;
     const long units = (long)a.n_kv_heads * B * n_mt;
     const int cus = device_compute_units();
+    // Many query rows: blocks of 4 tiles that share K and V and need no combine,
+    // where there are enough of them for half the CUs.
+    const int n_qb = (nq + 63) / 64;
+    if (a.xs && nq >= 64 && (long)n_qb * a.n_kv_heads * B * 2 >= cus) {
+      const dim3 qgrid(n_qb, a.n_kv_heads, B);
+      switch (a.head_dim) {
+        case 32: hipLaunchKernelGGL((attn_rows_kernel<32>), qgrid, dim3(512), 0, s, a, n_sub); break;
+        case 64: hipLaunchKernelGGL((attn_rows_kernel<64>), qgrid, dim3(512), 0, s, a, n_sub); break;
+        case 128: hipLaunchKernelGGL((attn_rows_kernel<128>), qgrid, dim3(512), 0, s, a, n_sub); break;
+        default: return hipErrorInvalidValue;
+      }
+      return hipGetLastError();
+    }
     int S = 0, n_part = 0, NW = 0;
     if (n_sub * units <= (long)cus * kMaxPartWaves) {
       // One sub-chunk per wave, one round: parts of S sub-chunks (the last one

@@ -1,4 +1,4 @@
-// Device pieces shared by the GEMM kernel files.
+// Device pieces shared by the GEMM and attention kernel files.
 #pragma once
 
 #include "device_common.h"
@@ -16,6 +16,17 @@ constexpr uint32_t kOutOfRange = 0x80000000u;
 constexpr int kNonTemporal = 2;  // cache-policy bit of a streamed (read-once) load
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
+}
+
+// Waits until at most N of this wave's vector-memory loads are outstanding.
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// 16 bytes per lane from rsrc at `off` into LDS at dst + 16 * lane, without
+// passing the registers.  (Inline asm, so that the compiler does not wait for
+// every such load before each LDS read: the kernel counts them itself.)
+__device__ __forceinline__ void load_lds16(uint32_t dst, uint32_t off, __amdgpu_buffer_rsrc_t rsrc) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rsrc)
+               : "memory", "m0");
 }
 
 // Base of the packed 16-row tile `t` (t < NC/16) of block `blk`.  Packed

@@ -33,17 +33,6 @@ constexpr int kMaxSs = 64;                    // ss partials a reduction sums
 // 45 -> 35, down 105 -> 78, against staging float32 x through registers; 112
 // rows: gate|up 63 -> 50, Q|K|V 40 -> 31, O 21 -> 15, down 37 -> 29, LM head
 // 101 -> 75 (there 3.2 to 3.7 TB/s of weights).
-// Waits until at most N of this wave's vector-memory loads are outstanding.
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-
-// 16 bytes per lane from rsrc at `off` into LDS at dst + 16 * lane, without
-// passing the registers.  (Inline asm, so that the compiler does not wait for
-// every such load before each LDS read: the kernel counts them itself.)
-__device__ __forceinline__ void load_lds16(uint32_t dst, uint32_t off, __amdgpu_buffer_rsrc_t rsrc) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rsrc)
-               : "memory", "m0");
-}
-
 template <int WM, int WN, int MTW, int NTW, int ST, bool RD, int KIND>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile(GemmArgs a, int n_ctiles, int ks_per_split, int n_split) {
   constexpr int NW = WM * WN, MTB = WM * MTW, NTB = WN * NTW;  // row and weight tiles of the block

@@ -8,7 +8,7 @@ import pytest
 from paper_2608_10362_amd import synth
 from tests.gpu_util import log
 from tests.test_gpu_int4 import _int4_case
-from tests.test_gpu_model import _bf16_case
+from tests.test_gpu_model import _bf16_case, test_bf16_prefill_in_large_chunks as _prefill_case
 
 pytestmark = pytest.mark.gpu
 
@@ -51,3 +51,11 @@ def test_int4_odd_shape_rows(B, g):
 @pytest.mark.parametrize("B,g", [(3, 5), (8, 4), (16, 3)])
 def test_int4_7b_width_rows(B, g):
     _int4_case(synth.LLAMA_7B, 1, [40 + 13 * b for b in range(B)], g, seed=B)
+
+
+# (one pass of 1500 rows, two launches of the tile kernel; the shared-K/V attention with 32-dim heads, 3 query heads per
+# kv head: 900 query rows in 15 blocks of 64, the last of them ragged; then ragged chunks of it)
+@pytest.mark.parametrize("B,rows,n", [(5, 1500, 301), (7, 1470, 380)])
+def test_odd_shape_prefill(monkeypatch, B, rows, n):
+    monkeypatch.setattr(synth, "ODD", ODD, raising=False)
+    _prefill_case("ODD", B, rows, n)
