@@ -40,11 +40,11 @@ struct specdec_model {
   uint16_t* xs_f = nullptr;  // bf16: the stacked attention output (the O projection's x), then SwiGLU output
   float* ypart = nullptr;  // split-K partials (passes of more than 16 rows)
   size_t ypart_floats = 0;
-  uint32_t* attn_ctr = nullptr;           // bf16: the attention combine's epochs
+  uint32_t* attn_pass = nullptr;          // bf16: forward passes run (tags of the attention's partial words)
   uint32_t* attn_cnt = nullptr;           // bf16: the one-round attention combine's arrival counters
   uint64_t* attn_ll = nullptr;            // bf16: the attention combine's tagged partial words
   size_t attn_ll_words = 0;
-  mutable bool attn_ctr_ready = false;    // set once all three have been zeroed on a stream
+  mutable bool attn_ready = false;        // set once all three have been zeroed on a stream
   int chunk, n_split_max;
   // per-layer launches of the last forward pass, for specdec_time_kernel
   // (entry l: layer l; the head and the embedding have one)
@@ -145,7 +145,7 @@ WsLayout ws_layout(const specdec_model_desc* d, int max_rows, int max_ctx) {
                                ? (size_t)kRowsSplitMax * std::min(max_rows, kMaxGemmRows) * d->d_model : 0;
   w.ypart_floats = std::max(rows_part, wide ? tile_ypart_floats(d->d_model) : 0);
   w.ypart = take(w.ypart_floats * 4);
-  w.ctr = take(d->dtype == SPECDEC_BF16 ? attention_counter_count(H, G, max_rows) * 4 : 0);
+  w.ctr = take(d->dtype == SPECDEC_BF16 ? 4 : 0);
   w.cnt = take(d->dtype == SPECDEC_BF16 ? attention_counter_count(H, G, max_rows) * 4 : 0);
   w.ll = take(d->dtype == SPECDEC_BF16 ? attention_ll_words(H, hd, max_rows, w.n_split) * 8 : 0);
   w.total = off;
@@ -323,6 +323,13 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   const bool head_stk = q4 && M <= kSkinnyRows;  // (INT4 layers convert float32 x themselves; the bf16 LM head does not)
   ra.xs = stk ? m->xs_d : nullptr;
   ra.stt = stt;
+  if (m->attn_pass && !m->attn_ready) {  // (fill kernels: a capturing caller may record them)
+    SD_TRY(launch_fill_u32(m->attn_pass, 1, 0u, s));
+    SD_TRY(launch_fill_u32(m->attn_cnt, attention_counter_count(H, G, m->max_rows), 0u, s));
+    SD_TRY(launch_fill_u32((uint32_t*)m->attn_ll, 2 * m->attn_ll_words, 0u, s));
+    m->attn_ready = true;
+  }
+  ra.pass = m->attn_pass;
   {
     Timed t(SPECDEC_KERNEL_EMBED, s);
     SD_TRY(launch_rows_embed(dt, ra, s));
@@ -366,15 +373,11 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   at.o = m->o;
   at.status = kv_status(kv);
   at.seq_bound = M / ra.rps > 1;
-  if (m->attn_ctr && !m->attn_ctr_ready) {  // (fill kernels: a capturing caller may record them)
-    SD_TRY(launch_fill_u32(m->attn_ctr, attention_counter_count(H, G, m->max_rows), 0u, s));
-    SD_TRY(launch_fill_u32(m->attn_cnt, attention_counter_count(H, G, m->max_rows), 0u, s));
-    SD_TRY(launch_fill_u32((uint32_t*)m->attn_ll, 2 * m->attn_ll_words, 0u, s));
-    m->attn_ctr_ready = true;
-  }
-  at.epochs = m->attn_ctr;
   at.counters = m->attn_cnt;
   at.ll = m->attn_ll;
+  at.ll_parts = std::min(kLlMaxParts, m->n_split_max);
+  at.n_layers = m->n_layers;
+  at.pass = m->attn_pass;
   at.xs = stk ? m->xs_f : nullptr;
   at.stt = stt;
 
@@ -650,7 +653,7 @@ specdec_status specdec_model_create_fmt(const specdec_model_desc* desc, const sp
   m->xs_f = desc->dtype == SPECDEC_BF16 ? (uint16_t*)(base + L.xs_f) : nullptr;
   m->ypart_floats = L.ypart_floats;
   m->ypart = bf16 && max_rows > kSkinnyRows ? (float*)(base + L.ypart) : nullptr;
-  m->attn_ctr = desc->dtype == SPECDEC_BF16 ? (uint32_t*)(base + L.ctr) : nullptr;
+  m->attn_pass = desc->dtype == SPECDEC_BF16 ? (uint32_t*)(base + L.ctr) : nullptr;
   m->attn_cnt = desc->dtype == SPECDEC_BF16 ? (uint32_t*)(base + L.cnt) : nullptr;
   m->attn_ll = desc->dtype == SPECDEC_BF16 ? (uint64_t*)(base + L.ll) : nullptr;
   m->attn_ll_words = desc->dtype == SPECDEC_BF16 ? attention_ll_words(desc->n_heads, desc->head_dim, max_rows, L.n_split) : 0;

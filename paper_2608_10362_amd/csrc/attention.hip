@@ -203,16 +203,13 @@ __device__ __forceinline__ float group16_sum(float v) {
 // Dynamic LDS: per wave a P tile [16][36] (the transposed read of P V), then,
 // reused once every wave is past P V, the merge buffers [NW][RS][HD + 4] of
 // O (rows padded against bank conflicts) and [NW][RS][2] of (max, sum), RS =
-// query rows of the tile.  With the in-kernel combine (own), the combining
-// block's own part [RS][HD + 2] (O, max, sum) follows them.
+// query rows of the tile.
 __host__ __device__ inline size_t attn_block_shared(int NW, int RS, int HD) {
   const size_t p = (size_t)NW * 16 * (kSubKeys + 4);
   const size_t m = (size_t)NW * RS * (HD + 6);
   return p > m ? p : m;
 }
-__host__ __device__ inline size_t attn_block_lds(int NW, int RS, int HD, bool own = false) {
-  return (attn_block_shared(NW, RS, HD) + (own ? (size_t)RS * (HD + 2) : 0)) * sizeof(float);
-}
+__host__ __device__ inline size_t attn_block_lds(int NW, int RS, int HD) { return attn_block_shared(NW, RS, HD) * sizeof(float); }
 
 // Flagged partial words of the in-kernel combine: the float in the low half,
 // the launch's tag in the high half, written and read as single 64-bit
@@ -229,15 +226,9 @@ constexpr int kCoherentLoad = 16;
 constexpr int kLlMaxPolls = 1 << 18;
 
 constexpr int kMaxPartWaves = 12;  // 3 waves per SIMD: up to 170 VGPRs per lane
-constexpr int kLoopWaves = 4;      // waves per block when waves loop over several sub-chunks
 
-// LOOP: wave w takes sub-chunks w, w + NW, ... of its part (online softmax
-// across them), so long contexts keep every wave streaming K/V instead of
-// ending the block after one sub-chunk (4-wave blocks, up to 256 registers);
-// otherwise each wave takes one sub-chunk (up to 12-wave blocks).
-template <int HD, bool LOOP>
-__global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ? 2 : 1) void attn_block_kernel(
-    AttnArgs a, int S, int n_sub, int NW) {
+template <int HD>
+__global__ __launch_bounds__(64 * kMaxPartWaves) void attn_block_kernel(AttnArgs a, int S, int n_sub, int NW) {
   constexpr int KST = HD / 32;  // k-steps of Q K^T
   constexpr int DT = HD / 16;   // 16-wide dimension tiles of P V
   constexpr int NT = kSubKeys / 16;
@@ -292,17 +283,6 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
     rd_pos = (int)__builtin_amdgcn_raw_buffer_load_b32(rr, roff + offsetof(RowDesc, pos), 0, 0);
     rd_valid = (int)__builtin_amdgcn_raw_buffer_load_b32(rr, roff + offsetof(RowDesc, valid), 0, 0);
   }
-  // In-kernel combine of looping launches: the epoch of the sequence, tile
-  // and kv head (this launch tags its words with epoch + 1), read through the
-  // coherent level (sc1) and used only once the partials are out.
-  const bool ll_mode = LOOP && a.ll != nullptr;
-  const uint32_t ep_idx = (uint32_t)(((size_t)b * (gridDim.x / n_part) + mt) * G + g);
-  uint32_t ep_raw = 0;
-  if constexpr (LOOP)  // (unconditional load, range 0 without the combine: a branch here made the key loads wait for it)
-    ep_raw = __builtin_amdgcn_raw_buffer_load_b32(
-        __builtin_amdgcn_make_buffer_rsrc(a.epochs, (short)0, ll_mode ? (ep_idx + 1u) * 4u : 0u, 0x00020000),
-        ep_idx * 4u, 0, kCoherentLoad);
-  float* const sown = smem + attn_block_shared(NW, RS, HD);  // (combiner: its own part per row)
   if (wave < sub_here) {  // (wave-uniform) a wave past the part's sub-chunks only joins the merge
     // K fragments of a sub-chunk: 2 x KST contiguous 1 KB fragments (k0 + 32 <= capacity);
     // V fragments: DT contiguous 1 KB fragments (32 positions x 16 dims each).
@@ -319,7 +299,7 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) vf[dt] = *(const u32x4*)(vfrag + (size_t)dt * 512);
     };
-    int k0 = (part * S + wave) * kSubKeys;
+    const int k0 = (part * S + wave) * kSubKeys;
     load_k(k0);
     // Q fragments (A operand): query qa = mt*16 + l%16 (zeros past nq).
     f32x4 qv4[KST][2];
@@ -368,11 +348,7 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
       split_hilo(v, qhi[c], qlo[c]);
     }
 
-    for (int j = wave; j < sub_here && k0 < nk; j += NW) {  // (wave-uniform)
-      if (j != wave) {  // the first sub-chunk's fragments were loaded above
-        load_k(k0);
-        load_v(k0);
-      }
+    if (k0 < nk) {  // (wave-uniform)
       // keys past the context: zero their V entries (never multiply stale memory)
       const int nvalid = nk - (k0 + 8 * grp);
       if (nvalid < 8) {
@@ -400,26 +376,20 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
           if (key > qpos[r]) acc[r] = -INFINITY;
         sf[t] = acc;
       }
-      // Online softmax: the running (max, sum, O) of each row is rescaled by
-      // exp(old max - new max) when this sub-chunk raises the max.
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float m = -INFINITY;
 #pragma unroll
         for (int t = 0; t < NT; ++t) m = fmaxf(m, sf[t][r]);
-        const float mnew = fmaxf(mx[r], group16_max(m));
-        const float alpha = mx[r] == -INFINITY ? 0.f : expf(mx[r] - mnew);
+        mx[r] = group16_max(m);
         float sum = 0.f;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          const float p = mnew == -INFINITY || sf[t][r] == -INFINITY ? 0.f : expf(sf[t][r] - mnew);
+          const float p = mx[r] == -INFINITY || sf[t][r] == -INFINITY ? 0.f : expf(sf[t][r] - mx[r]);
           pbuf[(4 * grp + r) * (kSubKeys + 4) + 16 * t + c16] = p;
           sum += p;
         }
-        sm[r] = sm[r] * alpha + group16_sum(sum);
-        mx[r] = mnew;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) of[dt][r] *= alpha;
+        sm[r] = group16_sum(sum);
       }
       __builtin_amdgcn_wave_barrier();  // P written by all lanes of the wave before the transposed reads
       float pv[8];
@@ -433,40 +403,10 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
         of[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(phi, vv, of[dt], 0, 0, 0);
         of[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plo, vv, of[dt], 0, 0, 0);
       }
-      if constexpr (!LOOP) break;
-      __builtin_amdgcn_wave_barrier();  // the transposed reads of P done before the next sub-chunk writes it
-      k0 += NW * kSubKeys;
     }
   }
 
   constexpr int DPL = HD >= 64 ? HD / 64 : 1;
-  // The combining block.  Looping launches (several rounds of blocks per
-  // CU): the block of the last part holding a key some valid row of the tile
-  // sees (the parts after it hold none); every part it waits for has a lower
-  // block index, so it was dispatched before it, and no other block waits for
-  // anything; its own part stays in LDS.  The other blocks end without
-  // waiting for their stores, which frees their CU for the next round sooner.
-  // One-round launches: the last block to count itself, after its partial
-  // stores are acknowledged (faster there than a fixed combining block that
-  // polls: all blocks run at once, and polling started before the other
-  // parts' words had landed).  (Lane reads of the descriptors, long arrived.)
-  // (The descriptor values pass through an empty asm here so that the
-  // compiler does not share this test with the one before the key loads and
-  // wait for the descriptors before issuing them.)
-  int last_part = n_part - 1;
-  uint32_t tag = 0;
-  if (ll_mode) {
-    int rp = rd_pos, rv = rd_valid;
-    asm volatile("" : "+v"(rp), "+v"(rv));
-    const int vpos = (lane < 16 && ql < nq && rv) ? rp : -1;
-    int mpos = -1;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) mpos = max(mpos, __builtin_amdgcn_readlane(vpos, i));
-    if (mpos >= 0) last_part = min(mpos / a.chunk, n_part - 1);
-    tag = ep_raw + 1u == 0u ? 1u : ep_raw + 1u;
-  }
-  const bool combiner = LOOP && ll_mode && part == last_part;
-  uint32_t* const epoch = a.epochs + ep_idx;  // (combiner: the next launch's epoch goes here)
   if (NW == 1) {  // (block-uniform) the wave's own (max, sum, O) rows are the part's partials
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -474,23 +414,7 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
       if (row >= RS || qpos[r] < 0 || mx[r] == -INFINITY) continue;
       const int qc = mt * 16 + row;
       const size_t slot = ((size_t)(r0 + qc / group) * H + g * group + qc % group) * n_part + part;
-      if (combiner) {
-        float* own = sown + (size_t)row * (HD + 2);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) own[dt * 16 + c16] = of[dt][r];
-        if (c16 == 0) {
-          own[HD] = mx[r];
-          own[HD + 1] = sm[r];
-        }
-      } else if (ll_mode) {
-        uint64_t* w = a.ll + slot * (HD + 2);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) ll_put(w + dt * 16 + c16, of[dt][r], tag);
-        if (c16 == 0) {
-          ll_put(w + HD, mx[r], tag);
-          ll_put(w + HD + 1, sm[r], tag);
-        }
-      } else if (a.counters) {
+      if (a.counters) {
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
           __hip_atomic_store(&a.o_part[slot * HD + dt * 16 + c16], of[dt][r], __ATOMIC_RELAXED,
@@ -529,7 +453,7 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
   __syncthreads();
   // One wave per row: the waves' weights exp(m_w - M) are uniform across the
   // wave, each lane sums HD / 64 dims over the waves in fixed order.
-  constexpr int MAXW = LOOP ? kLoopWaves : kMaxPartWaves;
+  constexpr int MAXW = kMaxPartWaves;
   for (int row = wave; row < RS; row += NW) {  // (wave-uniform)
     // The waves' partials in groups of 4: every read of a group first, then
     // the arithmetic (a wave past NW or without keys gets weight 0, and adding
@@ -570,25 +494,7 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
     const int qc = mt * 16 + row;
     const int qrow = r0 + qc / group, head = g * group + qc % group;
     const size_t slot = ((size_t)qrow * H + head) * n_part + part;
-    if (combiner) {  // (kept in LDS for its own combine)
-      float* own = sown + (size_t)row * (HD + 2);
-#pragma unroll
-      for (int j = 0; j < DPL; ++j)
-        if (lane + 64 * j < HD) own[lane + 64 * j] = O[j];
-      if (lane == 0) {
-        own[HD] = M;
-        own[HD + 1] = L;
-      }
-    } else if (ll_mode) {  // (tagged words: the combining block polls them)
-      uint64_t* w = a.ll + slot * (HD + 2);
-#pragma unroll
-      for (int j = 0; j < DPL; ++j)
-        if (lane + 64 * j < HD) ll_put(w + lane + 64 * j, O[j], tag);
-      if (lane == 0) {
-        ll_put(w + HD, M, tag);
-        ll_put(w + HD + 1, L, tag);
-      }
-    } else if (a.counters) {  // (agent-scope stores: visible to the combining block on any XCD once completed)
+    if (a.counters) {  // (agent-scope stores: visible to the combining block on any XCD once completed)
 #pragma unroll
       for (int j = 0; j < DPL; ++j)
         if (lane + 64 * j < HD)
@@ -640,128 +546,7 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
       asm volatile("" ::"v"(keep));
     }
   };
-  if constexpr (LOOP) {
-    if (!ll_mode) return;
-    if (!combiner) {
-      read_ahead();
-      return;
-    }
-    // The combining block: one wave per query row of the tile.  Its own part
-    // comes from LDS; the other parts' words are polled until every one read
-    // carries this launch's tag (each write and read is a whole 64-bit word),
-    // in batches of PB parts; the parts are added in part order.
-    __syncthreads();  // (the block's own part in LDS)
-    for (int row = wave; row < RS; row += NW) {  // (wave-uniform)
-      const int qc = mt * 16 + row;
-      const int qrow = r0 + qc / group, head = g * group + qc % group;
-      RowDesc rd;
-      rd.pos = __shfl(rd_pos, row, kWave);  // (lane `row` loaded this query's row descriptor)
-      rd.valid = __shfl(rd_valid, row, kWave);
-      float* o = a.o + ((size_t)qrow * H + head) * HD;
-      if (!rd.valid) {
-#pragma unroll
-        for (int j = 0; j < DPL; ++j)
-          if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, 0.f);
-        continue;
-      }
-      // parts holding keys <= pos (the last part also holds the remainder); the
-      // last one, when among them, is this block's own (nch <= last_part + 1)
-      const int nch = min(rd.pos / a.chunk + 1, n_part);
-      if (rd.pos + 1 > a.max_ctx && lane == 0) set_status(a.status, kStatusKvCapacity);  // the host's bound was wrong
-      const bool own_row = nch == last_part + 1;
-      const int npoll = own_row ? last_part : nch;  // parts read from memory
-      const float* own = sown + (size_t)row * (HD + 2);
-      const uint64_t* w = a.ll + ((size_t)qrow * H + head) * n_part * (HD + 2);
-      constexpr int PB = 8;
-      // lane p < nch: part p's (max, sum)
-      float mp = -INFINITY, lp = 0.f;
-      if (lane == last_part && own_row) {
-        mp = own[HD];
-        lp = own[HD + 1];
-      }
-      float acc[DPL];
-#pragma unroll
-      for (int j = 0; j < DPL; ++j) acc[j] = 0.f;
-      float mx = 0.f, wgt = 0.f;
-      bool expired = false;
-      const int pl = min(lane, max(npoll - 1, 0));  // (clamped: every load below reads a polled slot)
-      for (int p0 = 0; p0 < nch; p0 += PB) {  // (wave-uniform)
-        float ov[PB][DPL];
-        for (int poll = 0;; ++poll) {  // (wave-uniform)
-          // Every load first (branch-free, addresses clamped to polled slots),
-          // then the tag tests and the selection of own and absent parts.
-          uint64_t wm = 0, wl = 0, wo[PB][DPL];
-          if (npoll > 0) {  // (wave-uniform)
-            if (p0 == 0) {
-              wm = __hip_atomic_load(const_cast<uint64_t*>(w) + (size_t)pl * (HD + 2) + HD, __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
-              wl = __hip_atomic_load(const_cast<uint64_t*>(w) + (size_t)pl * (HD + 2) + HD + 1, __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
-            }
-#pragma unroll
-            for (int pp = 0; pp < PB; ++pp) {
-              const int pc = min(p0 + pp, npoll - 1);
-#pragma unroll
-              for (int j = 0; j < DPL; ++j)
-                wo[pp][j] = __hip_atomic_load(const_cast<uint64_t*>(w) + (size_t)pc * (HD + 2) + min(lane + 64 * j, HD - 1),
-                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-          }
-          bool ok = true;
-          if (p0 == 0 && lane < npoll) {
-            ok = (uint32_t)(wm >> 32) == tag && (uint32_t)(wl >> 32) == tag;
-            mp = __uint_as_float((uint32_t)wm);
-            lp = __uint_as_float((uint32_t)wl);
-          }
-#pragma unroll
-          for (int pp = 0; pp < PB; ++pp) {
-            const int p = p0 + pp;
-#pragma unroll
-            for (int j = 0; j < DPL; ++j) {
-              const int dd = lane + 64 * j;
-              const bool polled = p < npoll && dd < HD;
-              ok = ok && (!polled || (uint32_t)(wo[pp][j] >> 32) == tag);
-              ov[pp][j] = polled ? __uint_as_float((uint32_t)wo[pp][j])
-                                 : (p < nch && dd < HD ? own[min(dd, HD - 1)] : 0.f);
-            }
-          }
-          if (__all(ok)) break;
-          if (poll >= kLlMaxPolls) {
-            expired = true;
-            break;
-          }
-        }
-        if (expired) break;
-        if (p0 == 0) {
-          mx = wave_max(lane < nch ? mp : -INFINITY);
-          wgt = lane < nch ? expf(mp - mx) : 0.f;
-        }
-#pragma unroll
-        for (int pp = 0; pp < PB; ++pp) {
-          const float wp = __shfl(wgt, (p0 + pp) & 63, kWave);
-          const float wv = p0 + pp < nch ? wp : 0.f;
-#pragma unroll
-          for (int j = 0; j < DPL; ++j) acc[j] += wv * ov[pp][j];
-        }
-      }
-      if (expired) {  // (a part never arrived: report it, write zeros)
-        if (lane == 0) set_status(a.status, kStatusWaitExpired);
-#pragma unroll
-        for (int j = 0; j < DPL; ++j)
-          if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, 0.f);
-        continue;
-      }
-      const float L = wave_sum(wgt * lp);
-      const float inv = 1.0f / L;
-#pragma unroll
-      for (int j = 0; j < DPL; ++j)
-        if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, acc[j] * inv);
-    }
-    // Every part of this launch has been read (so every block of it has read
-    // the epoch): the next launch's tag.
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(epoch, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  } else {
+  {
     if (!a.counters) return;
 
     // The last block of this (sequence, tile, kv head) to finish combines the
@@ -772,7 +557,7 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
-      uint32_t* ctr = a.counters + ep_idx;
+      uint32_t* ctr = a.counters + ((size_t)b * (gridDim.x / n_part) + mt) * G + g;
       const uint32_t old = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int last = old == (uint32_t)(n_part - 1);
       if (last) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -838,6 +623,429 @@ __global__ __launch_bounds__(LOOP ? 64 * kLoopWaves : 64 * kMaxPartWaves, LOOP ?
       for (int j = 0; j < DPL; ++j)
         if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, acc[j] * inv);
     }
+  }
+}
+
+// ---------------------------------------------------------------- long contexts and batches (bf16 cache)
+// More sub-chunks than one round of waves takes: a persistent grid (two blocks
+// of 4 waves per CU) over the work itself.  The sub-chunks of every unit
+// (sequence, kv head, 16-query tile), each sequence's counted from its own last
+// row on the device, form one line, sequence by sequence, and block i takes the
+// i-th `per` of them: all blocks stream the same bytes whatever the lengths, and
+// a block pays for its start and its merge once or twice instead of per part.
+// Within a unit's segment wave w takes sub-chunks w, w + 4, ... with an online
+// softmax, then the waves merge in LDS.  A unit inside one block is finished
+// there; of a unit that spans blocks, the block that ends it combines, last of
+// all its work: the others store their part as tagged words (ll_put) and go on.
+// It polls until every word read carries this launch's tag.  Every block it
+// waits for has a lower index (so it was dispatched no later) and stores all its
+// words before it polls itself, so the wait always ends; a bounded poll count
+// turns a broken invariant into a status.  The tag is the pass count, which the
+// embedding kernel advances, times the layers, plus the layer: no two launches
+// of a handle share one.
+// Bound: the key and value stream.  16 sequences of 1024 to 8192 keys (1.26 GB
+// per layer of the 7B shape): 255 us in parts sized for 12 blocks per CU
+// (4.9 TB/s), @@LONG@@; 8 sequences of 513 to 2048: 53 us, @@B8@@.
+constexpr int kLoopWaves = 4;
+__host__ __device__ inline size_t attn_stream_lds(int RS, int HD) {
+  const size_t p = (size_t)kLoopWaves * 16 * (kSubKeys + 4), m = (size_t)kLoopWaves * RS * (HD + 6);
+  return ((p > m ? p : m) + (size_t)RS * (HD + 2)) * sizeof(float);
+}
+template <int HD>
+__global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArgs a, int n_sub, int n_mt) {
+  constexpr int KST = HD / 32, DT = HD / 16, NT = kSubKeys / 16, NW = kLoopWaves;
+  constexpr int DPL = HD >= 64 ? HD / 64 : 1;
+  constexpr int OS = HD + 4;
+  extern __shared__ float smem[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int H = a.n_heads, G = a.n_kv_heads, group = H / G;
+  const int rps = a.rps, nq = rps * group, B = a.M / rps, U = G * n_mt;
+  const int RSM = min(16, nq);
+  const int c16 = lane & 15, grp = lane >> 4;
+  float* const pbuf = smem + (size_t)wave * 16 * (kSubKeys + 4);
+  float* const so = smem;                                   // [NW][RS][OS] (P's place, once every wave is past P V)
+  float* const sml = smem + (size_t)NW * RSM * OS;          // [NW][RS][2]
+  float* const sown = (float*)((char*)smem + attn_stream_lds(RSM, HD)) - (size_t)RSM * (HD + 2);
+
+  // Sub-chunks of sequence s: up to its last row's position (a batch's own
+  // count where that row is invalid).
+  auto subs_of = [&](int s) {
+    const RowDesc last = a.rows[s * rps + rps - 1];
+    return last.valid ? min(n_sub, last.pos / kSubKeys + 1) : n_sub;
+  };
+  const uint32_t tag = a.pass[0] * (uint32_t)a.n_layers + (uint32_t)a.layer + 1u;
+  const int n0 = lane < B ? subs_of(lane) : 0;  // (the first 64 sequences stay in a register)
+  int subs = 0;
+  for (int c = 0; c < B; c += kWave) {
+    int n = c == 0 ? n0 : (c + lane < B ? subs_of(c + lane) : 0);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, kWave);
+    subs += n;
+  }
+  subs = __builtin_amdgcn_readfirstlane(subs);
+  const int tot = subs * U, nblk = (int)gridDim.x, blk = (int)blockIdx.x;
+  // (a unit spans at most kLlMaxParts blocks; every wave gets a sub-chunk)
+  const int per = max(max((tot + nblk - 1) / nblk, (n_sub + kLlMaxParts - 3) / (kLlMaxParts - 2)), NW);
+  int x = blk * per;
+  const int hi = min(tot, x + per);
+  if (x >= tot) return;
+  // the sequence that holds x, and the sub-chunks before it
+  int b = 0, before = 0;
+  for (int c = 0; c < B; c += kWave) {
+    const int n = c == 0 ? n0 : (c + lane < B ? subs_of(c + lane) : 0);
+    int incl = n;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int t = __shfl_up(incl, o, kWave);
+      if (lane >= o) incl += t;
+    }
+    const unsigned long long hit = __ballot((before + incl) * U > x);
+    if (hit) {
+      const int l = __ffsll(hit) - 1;
+      b = c + l;
+      before += __shfl(incl - n, l, kWave);
+      break;
+    }
+    before += __shfl(incl, kWave - 1, kWave);
+  }
+  b = __builtin_amdgcn_readfirstlane(b);
+  before = __builtin_amdgcn_readfirstlane(before);
+
+  // the unit this block ends and others began (combined last): part count, its place, its first block
+  int c_parts = 0, c_b = 0, c_u = 0, c_x0 = 0;
+  const float scale = 1.0f / sqrtf((float)HD);
+
+  while (x < hi) {  // (block-uniform)
+    const int n_b = __builtin_amdgcn_readfirstlane(b < kWave ? __shfl(n0, b & 63, kWave) : subs_of(b));
+    const int off = x - before * U, u = off / n_b, j0 = off % n_b, j1 = min(n_b, j0 + hi - x);
+    const int g = u / n_mt, mt = u % n_mt, r0 = b * rps;
+    const int RS = min(16, nq - mt * 16);
+    const int x0 = x - j0;
+    const uint16_t* kb = k_block<uint16_t>(a.kv, a.layer, b, g);
+    const uint16_t* vb = kb + (size_t)a.kv.capacity * HD;
+
+    floatx4 of[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) of[dt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY}, sm[4] = {0.f, 0.f, 0.f, 0.f};
+    int qpos[4] = {-1, -1, -1, -1};
+    // (loads in the order they are needed: descriptors, K, Q, V; see attn_block_kernel)
+    const int ql = mt * 16 + lane;
+    const __amdgpu_buffer_rsrc_t rr = make_rsrc(a.rows, (uint32_t)a.M * (uint32_t)sizeof(RowDesc));
+    const uint32_t roff = ((uint32_t)(r0 + min(ql, nq - 1) / group) * (uint32_t)sizeof(RowDesc)) |
+                          ((uint32_t)(lane >= 16 || ql >= nq) << 31);
+    const int rd_pos = (int)__builtin_amdgcn_raw_buffer_load_b32(rr, roff + offsetof(RowDesc, pos), 0, 0);
+    const int rd_valid = (int)__builtin_amdgcn_raw_buffer_load_b32(rr, roff + offsetof(RowDesc, valid), 0, 0);
+    if (j0 + wave < j1) {  // (wave-uniform)
+      u32x4 kf[NT][KST], vf[DT];
+      auto load_k = [&](int k0) {
+        const uint16_t* kfrag = kb + (size_t)(k0 / 16) * KST * 512 + lane * 8;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int c = 0; c < KST; ++c) kf[t][c] = *(const u32x4*)(kfrag + (size_t)(t * KST + c) * 512);
+      };
+      auto load_v = [&](int k0) {
+        const uint16_t* vfrag = vb + (size_t)(k0 / 32) * DT * 512 + lane * 8;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) vf[dt] = *(const u32x4*)(vfrag + (size_t)dt * 512);
+      };
+      int k0 = (j0 + wave) * kSubKeys;
+      load_k(k0);
+      f32x4 qv4[KST][2];
+      {
+        const int qa = mt * 16 + c16;
+        const int row = r0 + qa / group, head = g * group + qa % group;
+        const __amdgpu_buffer_rsrc_t qrs = make_rsrc(a.qr, (uint32_t)a.M * H * HD * 4u);
+        const uint32_t qoff = ((((uint32_t)row * H + head) * HD + 8 * grp) * 4u) | ((uint32_t)(qa >= nq) << 31);
+#pragma unroll
+        for (int c = 0; c < KST; ++c) {
+          qv4[c][0] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(qrs, qoff + 128u * c, 0, 0));
+          qv4[c][1] =
+              __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(qrs, qoff + 128u * c + 16u, 0, 0));
+        }
+      }
+      load_v(k0);
+      asm volatile("" ::: "memory");  // (keeps what follows from being hoisted above the loads)
+      const int mypos = (lane < 16 && ql < nq && rd_valid) ? rd_pos : -1;
+      int lp[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) lp[i] = __builtin_amdgcn_readlane(mypos, i);
+      int nk = lp[0] + 1;
+#pragma unroll
+      for (int i = 1; i < 16; ++i) nk = max(nk, lp[i] + 1);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        qpos[r] = grp == 0 ? lp[r] : (grp == 1 ? lp[4 + r] : (grp == 2 ? lp[8 + r] : lp[12 + r]));
+      bf16x8 qhi[KST], qlo[KST];
+#pragma unroll
+      for (int c = 0; c < KST; ++c) {
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          v[j] = qv4[c][0][j] * scale;
+          v[4 + j] = qv4[c][1][j] * scale;
+        }
+        split_hilo(v, qhi[c], qlo[c]);
+      }
+      for (int j = j0 + wave; j < j1 && k0 < nk; j += NW) {  // (wave-uniform)
+        if (j != j0 + wave) {  // the first sub-chunk's fragments were loaded above
+          load_k(k0);
+          load_v(k0);
+        }
+        // keys past the context: zero their V entries (never multiply stale memory)
+        const int nvalid = nk - (k0 + 8 * grp);
+        if (nvalid < 8) {
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              if (2 * q >= nvalid) vf[dt][q] = 0u;
+              else if (2 * q + 1 >= nvalid) vf[dt][q] &= 0xffffu;
+            }
+        }
+        floatx4 sf[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int c = 0; c < KST; ++c) {
+            const bf16x8 kk = __builtin_bit_cast(bf16x8, kf[t][c]);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qhi[c], kk, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qlo[c], kk, acc, 0, 0, 0);
+          }
+          const int key = k0 + 16 * t + c16;
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (key > qpos[r]) acc[r] = -INFINITY;
+          sf[t] = acc;
+        }
+        // Online softmax: the running (max, sum, O) of each row is rescaled by
+        // exp(old max - new max) when this sub-chunk raises the max.
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          float m = -INFINITY;
+#pragma unroll
+          for (int t = 0; t < NT; ++t) m = fmaxf(m, sf[t][r]);
+          const float mnew = fmaxf(mx[r], group16_max(m));
+          const float alpha = mx[r] == -INFINITY ? 0.f : expf(mx[r] - mnew);
+          float sum = 0.f;
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            const float p = mnew == -INFINITY || sf[t][r] == -INFINITY ? 0.f : expf(sf[t][r] - mnew);
+            pbuf[(4 * grp + r) * (kSubKeys + 4) + 16 * t + c16] = p;
+            sum += p;
+          }
+          sm[r] = sm[r] * alpha + group16_sum(sum);
+          mx[r] = mnew;
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) of[dt][r] *= alpha;
+        }
+        __builtin_amdgcn_wave_barrier();  // P written by all lanes of the wave before the transposed reads
+        float pv[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) pv[q] = pbuf[c16 * (kSubKeys + 4) + 8 * grp + q];
+        bf16x8 phi, plo;
+        split_hilo(pv, phi, plo);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          const bf16x8 vv = __builtin_bit_cast(bf16x8, vf[dt]);
+          of[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(phi, vv, of[dt], 0, 0, 0);
+          of[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plo, vv, of[dt], 0, 0, 0);
+        }
+        __builtin_amdgcn_wave_barrier();  // the transposed reads of P done before the next sub-chunk writes it
+        k0 += NW * kSubKeys;
+      }
+    }
+    // Merge the waves' partials of the segment (P's LDS reused: every wave is past P V).
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 4 * grp + r;
+      if (row >= RS) continue;
+      const bool live = qpos[r] >= 0 && mx[r] != -INFINITY;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) so[((size_t)wave * RS + row) * OS + dt * 16 + c16] = live ? of[dt][r] : 0.f;
+      if (c16 == 0) {
+        sml[((size_t)wave * RS + row) * 2] = live ? mx[r] : -INFINITY;
+        sml[((size_t)wave * RS + row) * 2 + 1] = live ? sm[r] : 0.f;
+      }
+    }
+    __syncthreads();
+    const bool whole = j0 == 0 && j1 == n_b, ends = j1 == n_b;
+    const int part = blk - x0 / per;
+    for (int row = wave; row < RS; row += NW) {  // (wave-uniform) one wave per query row
+      const int qc = mt * 16 + row;
+      const int qrow = r0 + qc / group, head = g * group + qc % group;
+      const int pos = __shfl(rd_pos, row, kWave), valid = __shfl(rd_valid, row, kWave);
+      float mw[NW], lw[NW], ow[NW][DPL], M = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const size_t wr = (size_t)w * RS + row;
+        mw[w] = sml[wr * 2];
+        lw[w] = sml[wr * 2 + 1];
+#pragma unroll
+        for (int j = 0; j < DPL; ++j) ow[w][j] = lane + 64 * j < HD ? so[wr * OS + lane + 64 * j] : 0.f;
+      }
+#pragma unroll
+      for (int w = 0; w < NW; ++w) M = fmaxf(M, mw[w]);
+      float L = 0.f, O[DPL];
+#pragma unroll
+      for (int j = 0; j < DPL; ++j) O[j] = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float e = mw[w] != -INFINITY ? expf(mw[w] - M) : 0.f;
+        L += e * lw[w];
+#pragma unroll
+        for (int j = 0; j < DPL; ++j) O[j] += e * ow[w][j];
+      }
+      if (whole) {
+        const float inv = valid ? 1.0f / L : 0.f;
+        if (valid && pos + 1 > a.max_ctx && lane == 0) set_status(a.status, kStatusKvCapacity);  // the host's bound was wrong
+        float* o = a.o + ((size_t)qrow * H + head) * HD;
+#pragma unroll
+        for (int j = 0; j < DPL; ++j)
+          if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, valid ? O[j] * inv : 0.f);
+      } else if (ends) {  // (kept in LDS for this block's combine)
+        float* own = sown + (size_t)row * (HD + 2);
+#pragma unroll
+        for (int j = 0; j < DPL; ++j)
+          if (lane + 64 * j < HD) own[lane + 64 * j] = O[j];
+        if (lane == 0) {
+          own[HD] = M;
+          own[HD + 1] = L;
+        }
+      } else if (M != -INFINITY) {
+        uint64_t* w = a.ll + (((size_t)qrow * H + head) * a.ll_parts + part) * (HD + 2);
+#pragma unroll
+        for (int j = 0; j < DPL; ++j)
+          if (lane + 64 * j < HD) ll_put(w + lane + 64 * j, O[j], tag);
+        if (lane == 0) {
+          ll_put(w + HD, M, tag);
+          ll_put(w + HD + 1, L, tag);
+        }
+      }
+    }
+    if (ends && !whole) {
+      c_parts = part + 1;
+      c_b = b;
+      c_u = u;
+      c_x0 = x0;
+    }
+    x += j1 - j0;
+    if (x == (before + n_b) * U) {
+      before += n_b;
+      ++b;
+    }
+    __syncthreads();  // (the merge buffers are P's again)
+  }
+
+  if (c_parts == 0) return;
+  // Combine: one wave per query row.  This block's part (the last) comes from
+  // LDS; the other parts' words are polled until every one read carries the tag
+  // (each write and read is a whole 64-bit word), in batches of PB parts, and
+  // added in part order.
+  const int g = c_u / n_mt, mt = c_u % n_mt, r0 = c_b * rps, RS = min(16, nq - mt * 16), p_first = c_x0 / per;
+  for (int row = wave; row < RS; row += NW) {  // (wave-uniform)
+    const int qc = mt * 16 + row;
+    const int qrow = r0 + qc / group, head = g * group + qc % group;
+    const RowDesc rd = a.rows[qrow];
+    float* o = a.o + ((size_t)qrow * H + head) * HD;
+    if (!rd.valid) {
+#pragma unroll
+      for (int j = 0; j < DPL; ++j)
+        if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, 0.f);
+      continue;
+    }
+    if (rd.pos + 1 > a.max_ctx && lane == 0) set_status(a.status, kStatusKvCapacity);  // the host's bound was wrong
+    // parts whose first sub-chunk holds a key <= pos
+    const int nch = min((c_x0 + rd.pos / kSubKeys) / per - p_first + 1, c_parts);
+    const bool own_row = nch == c_parts;
+    const int npoll = own_row ? c_parts - 1 : nch;  // (>= 1: a unit combined here began in another block)
+    const float* own = sown + (size_t)row * (HD + 2);
+    const uint64_t* w = a.ll + ((size_t)qrow * H + head) * a.ll_parts * (HD + 2);
+    constexpr int PB = 8;
+    // lane p < nch: part p's (max, sum)
+    float mp = -INFINITY, lp = 0.f;
+    if (lane == c_parts - 1 && own_row) {
+      mp = own[HD];
+      lp = own[HD + 1];
+    }
+    float acc[DPL];
+#pragma unroll
+    for (int j = 0; j < DPL; ++j) acc[j] = 0.f;
+    float M = 0.f, wgt = 0.f;
+    bool expired = false;
+    const int pl = min(lane, npoll - 1);  // (clamped: every load below reads a polled slot)
+    for (int p0 = 0; p0 < nch; p0 += PB) {  // (wave-uniform)
+      float ov[PB][DPL];
+      for (int poll = 0;; ++poll) {  // (wave-uniform)
+        // Every load first (branch-free, addresses clamped to polled slots),
+        // then the tag tests and the selection of own and absent parts.
+        uint64_t wm = 0, wl = 0, wo[PB][DPL];
+        if (p0 == 0) {
+          wm = __hip_atomic_load(const_cast<uint64_t*>(w) + (size_t)pl * (HD + 2) + HD, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+          wl = __hip_atomic_load(const_cast<uint64_t*>(w) + (size_t)pl * (HD + 2) + HD + 1, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int pp = 0; pp < PB; ++pp) {
+          const int pc = min(p0 + pp, npoll - 1);
+#pragma unroll
+          for (int j = 0; j < DPL; ++j)
+            wo[pp][j] = __hip_atomic_load(const_cast<uint64_t*>(w) + (size_t)pc * (HD + 2) + min(lane + 64 * j, HD - 1),
+                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        bool ok = true;
+        if (p0 == 0 && lane < npoll) {
+          ok = (uint32_t)(wm >> 32) == tag && (uint32_t)(wl >> 32) == tag;
+          mp = __uint_as_float((uint32_t)wm);
+          lp = __uint_as_float((uint32_t)wl);
+        }
+#pragma unroll
+        for (int pp = 0; pp < PB; ++pp) {
+          const int p = p0 + pp;
+#pragma unroll
+          for (int j = 0; j < DPL; ++j) {
+            const int dd = lane + 64 * j;
+            const bool polled = p < npoll && dd < HD;
+            ok = ok && (!polled || (uint32_t)(wo[pp][j] >> 32) == tag);
+            ov[pp][j] = polled ? __uint_as_float((uint32_t)wo[pp][j])
+                               : (p < nch && dd < HD ? own[min(dd, HD - 1)] : 0.f);
+          }
+        }
+        if (__all(ok)) break;
+        if (poll >= kLlMaxPolls) {
+          expired = true;
+          break;
+        }
+      }
+      if (expired) break;
+      if (p0 == 0) {
+        M = wave_max(lane < nch ? mp : -INFINITY);
+        wgt = lane < nch ? expf(mp - M) : 0.f;
+      }
+#pragma unroll
+      for (int pp = 0; pp < PB; ++pp) {
+        const float wp = __shfl(wgt, (p0 + pp) & 63, kWave);
+        const float wv = p0 + pp < nch ? wp : 0.f;
+#pragma unroll
+        for (int j = 0; j < DPL; ++j) acc[j] += wv * ov[pp][j];
+      }
+    }
+    if (expired) {  // (a part never arrived: report it, write zeros)
+      if (lane == 0) set_status(a.status, kStatusWaitExpired);
+#pragma unroll
+      for (int j = 0; j < DPL; ++j)
+        if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, 0.f);
+      continue;
+    }
+    const float L = wave_sum(wgt * lp);
+    const float inv = 1.0f / L;
+#pragma unroll
+    for (int j = 0; j < DPL; ++j)
+      if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, acc[j] * inv);
   }
 }
 
@@ -1272,44 +1480,28 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
         if (S == 1 || (NW <= kMaxPartWaves && attn_block_lds(NW, RS, a.head_dim) <= 65536)) break;
       }
     } else {
-      // Long contexts: 4-wave blocks whose waves loop over the sub-chunks of
-      // their part; parts sized for about 12 blocks per CU (two resident per
-      // CU, six rounds: short tails when sequences differ in length; measured
-      // on 16 sequences of 1024-8192 keys: 4, 8, 10, 12, 16 and 24 blocks per
-      // CU, 12 the fastest).
-      NW = kLoopWaves;
-      const long parts = std::max(1L, (12L * cus + units - 1) / units);
-      S = (int)((n_sub + parts - 1) / parts);
-      S = (S + NW - 1) / NW * NW;
-      n_part = (n_sub + S - 1) / S;
+      // Long contexts and batches: the persistent kernel over the sub-chunks themselves.
+      if (!a.ll || !a.pass) return hipErrorInvalidValue;
+      const dim3 sgrid(2 * cus);
+      const size_t slds = attn_stream_lds(RS, a.head_dim);
+      switch (a.head_dim) {
+        case 32: hipLaunchKernelGGL((attn_stream_kernel<32>), sgrid, dim3(64 * kLoopWaves), slds, s, a, n_sub, n_mt); break;
+        case 64: hipLaunchKernelGGL((attn_stream_kernel<64>), sgrid, dim3(64 * kLoopWaves), slds, s, a, n_sub, n_mt); break;
+        case 128: hipLaunchKernelGGL((attn_stream_kernel<128>), sgrid, dim3(64 * kLoopWaves), slds, s, a, n_sub, n_mt); break;
+        default: return hipErrorInvalidValue;
+      }
+      return hipGetLastError();
     }
     if (NW > kMaxPartWaves || attn_block_lds(NW, RS, a.head_dim) > 65536) return hipErrorInvalidValue;
     ab.n_split = n_part;
     ab.chunk = S * kSubKeys;
     // In-kernel combine: one part per lane, at most two query rows per wave of
-    // the combining block (its rows go one after another), and its own part's
-    // rows fit in LDS next to the merge buffers; otherwise the separate
-    // combine kernel (one wave per row and head).
-    // (Looping launches combine through the tagged words and keep the
-    // combining block's own part in LDS; one-round launches count arrivals.)
-    const bool loop = S > NW;
-    if (loop) ab.counters = nullptr;
-    else {
-      ab.ll = nullptr;
-      ab.epochs = nullptr;
-    }
-    if (n_part > kLlMaxParts || (RS + NW - 1) / NW > 2 || attn_block_lds(NW, RS, a.head_dim, loop) > 65536 ||
-        (loop ? !ab.ll || !ab.epochs : !ab.counters)) {
-      ab.epochs = nullptr;
-      ab.counters = nullptr;
-      ab.ll = nullptr;
-    }
-    dim3 grid(n_part * n_mt, a.n_kv_heads, B);
-    const size_t lds = attn_block_lds(NW, RS, a.head_dim, ab.ll != nullptr);
-    if (loop && NW > kLoopWaves) return hipErrorInvalidValue;  // (the looping kernel's block bound)
-#define SD_ATTN(HDV)                                                                                       \
-  if (loop) hipLaunchKernelGGL((attn_block_kernel<HDV, true>), grid, dim3(64 * NW), lds, s, ab, S, n_sub, NW); \
-  else hipLaunchKernelGGL((attn_block_kernel<HDV, false>), grid, dim3(64 * NW), lds, s, ab, S, n_sub, NW);
+    // the combining block (its rows go one after another); otherwise the
+    // separate combine kernel (one wave per row and head).
+    if (n_part > kLlMaxParts || (RS + NW - 1) / NW > 2) ab.counters = nullptr;
+    const dim3 grid(n_part * n_mt, a.n_kv_heads, B);
+    const size_t lds = attn_block_lds(NW, RS, a.head_dim);
+#define SD_ATTN(HDV) hipLaunchKernelGGL((attn_block_kernel<HDV>), grid, dim3(64 * NW), lds, s, ab, S, n_sub, NW);
     switch (a.head_dim) {
       case 32: SD_ATTN(32) break;
       case 64: SD_ATTN(64) break;
@@ -1324,7 +1516,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (ab.kv.dtype == SPECDEC_BF16 && (ab.ll || ab.counters)) return hipSuccess;  // combined by the blocks
+  if (ab.kv.dtype == SPECDEC_BF16 && ab.counters) return hipSuccess;  // combined by the blocks
   if (ab.kv.dtype == SPECDEC_BF16 && ab.n_split <= kCombineMaxSplits) {
     switch (ab.head_dim) {
       case 32: hipLaunchKernelGGL((attn_combine_wave_kernel<32>), dim3(ab.n_heads, ab.M), dim3(64), 0, s, ab); break;

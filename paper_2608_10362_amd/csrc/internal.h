@@ -156,6 +156,7 @@ struct RowsArgs {
   float* h;               // out [M, d]
   float* xg;              // out [M, d] h * gain
   float* ss;              // out [M] sum of squares of h rows
+  uint32_t* pass;         // or null: the handle's pass count, advanced by one
   uint16_t* xs;           // or null: xg goes out as the stacked operand (put_stacked, stt fragments per k-step) only
   int stt;
 };
@@ -180,18 +181,16 @@ struct AttnArgs {
   int stt;
   int32_t* status;
   int seq_bound;         // 1: bound each sequence's keys by its own last row (batches of several sequences)
-  // bf16 in-kernel combine (all null: a separate combine kernel adds the
-  // parts).  epochs: one word per (sequence, query tile, kv head), zero at
-  // first use; a launch reads e and tags every partial word it writes with
-  // e + 1 (never 0), and the combining block stores e + 1 once it has read
-  // every part.  ll: [M, h, parts <= kLlMaxParts, hd + 2] tagged words, zero
-  // at first use: low half the float (hd O values, then max and sum), high
-  // half the tag.  counters (one-round launches): one word per (sequence,
-  // query tile, kv head), zero between launches; the last block to count
-  // combines.
-  uint32_t* epochs;
-  uint64_t* ll;
+  // bf16 in-kernel combines.  counters (one-round launches; null: a separate
+  // combine kernel adds the parts): one word per (sequence, query tile, kv
+  // head), zero between launches; the last block to count combines.  ll (long
+  // contexts and batches): [M, h, ll_parts, hd + 2] tagged words: low half the
+  // float (hd O values, then max and sum), high half the launch's tag, pass[0]
+  // * n_layers + layer + 1 (the embedding kernel advances pass[0]).
   uint32_t* counters;
+  uint64_t* ll;
+  int ll_parts, n_layers;
+  const uint32_t* pass;
   // Or null: the weights the next launch streams (the O projection's image,
   // next_w_bytes long).  With the in-kernel combine, every block that does not
   // combine reads up to kNextWeightsPerBlock bytes of its share of them after
@@ -202,7 +201,7 @@ struct AttnArgs {
 };
 constexpr uint32_t kNextWeightsPerBlock = 48u << 10;
 constexpr int kLlMaxParts = 64;  // parts of one head the in-kernel combine takes (one per lane)
-// Epoch words a model workspace holds for the attention's in-kernel combine.
+// Counter words a model workspace holds for the one-round in-kernel combine.
 size_t attention_counter_count(int n_heads, int n_kv_heads, int max_rows);
 // Flagged partial words (uint64) of the in-kernel combine for max_rows rows.
 size_t attention_ll_words(int n_heads, int head_dim, int max_rows, int n_split_max);

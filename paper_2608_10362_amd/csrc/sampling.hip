@@ -158,7 +158,10 @@ __global__ __launch_bounds__(256) void rows_embed_kernel(RowsArgs a) {
     }
     return;
   }
-  if (first) a.rows[r] = RowDesc{b, pos, tok, valid};
+  if (first) {
+    a.rows[r] = RowDesc{b, pos, tok, valid};
+    if (r == 0 && a.pass) *a.pass += 1u;
+  }
   const ET* e = (const ET*)a.embed + (size_t)tok * a.d_model;
   const ET* gn = (const ET*)a.gain;
   float* h = a.h + (size_t)r * a.d_model;
