@@ -211,6 +211,16 @@ __host__ __device__ inline size_t attn_block_shared(int NW, int RS, int HD) {
 }
 __host__ __device__ inline size_t attn_block_lds(int NW, int RS, int HD) { return attn_block_shared(NW, RS, HD) * sizeof(float); }
 
+// 16 bytes of a K or V fragment; ONCE: no other block reads them (one query
+// tile), so they need not stay in a cache (247 -> 218 us for the 16 long
+// sequences below; no difference in the one-round kernel, where each CU reads
+// its share at once).
+template <bool ONCE>
+__device__ __forceinline__ u32x4 load_kv(const uint16_t* p) {
+  if constexpr (ONCE) return __builtin_nontemporal_load((const u32x4*)p);
+  else return *(const u32x4*)p;
+}
+
 // Flagged partial words of the in-kernel combine: the float in the low half,
 // the launch's tag in the high half, written and read as single 64-bit
 // agent-scope accesses (a reader sees a whole word, old or new).
@@ -645,13 +655,13 @@ __global__ __launch_bounds__(64 * kMaxPartWaves) void attn_block_kernel(AttnArgs
 // of a handle share one.
 // Bound: the key and value stream.  16 sequences of 1024 to 8192 keys (1.26 GB
 // per layer of the 7B shape): 255 us in parts sized for 12 blocks per CU
-// (4.9 TB/s), @@LONG@@; 8 sequences of 513 to 2048: 53 us, @@B8@@.
+// (4.9 TB/s), 218 now (5.8 TB/s); 8 sequences of 513 to 2048: 53 us, 44 now.
 constexpr int kLoopWaves = 4;
 __host__ __device__ inline size_t attn_stream_lds(int RS, int HD) {
   const size_t p = (size_t)kLoopWaves * 16 * (kSubKeys + 4), m = (size_t)kLoopWaves * RS * (HD + 6);
   return ((p > m ? p : m) + (size_t)RS * (HD + 2)) * sizeof(float);
 }
-template <int HD>
+template <int HD, bool ONCE>
 __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArgs a, int n_sub, int n_mt) {
   constexpr int KST = HD / 32, DT = HD / 16, NT = kSubKeys / 16, NW = kLoopWaves;
   constexpr int DPL = HD >= 64 ? HD / 64 : 1;
@@ -743,12 +753,12 @@ __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArg
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-          for (int c = 0; c < KST; ++c) kf[t][c] = *(const u32x4*)(kfrag + (size_t)(t * KST + c) * 512);
+          for (int c = 0; c < KST; ++c) kf[t][c] = load_kv<ONCE>(kfrag + (size_t)(t * KST + c) * 512);
       };
       auto load_v = [&](int k0) {
         const uint16_t* vfrag = vb + (size_t)(k0 / 32) * DT * 512 + lane * 8;
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) vf[dt] = *(const u32x4*)(vfrag + (size_t)dt * 512);
+        for (int dt = 0; dt < DT; ++dt) vf[dt] = load_kv<ONCE>(vfrag + (size_t)dt * 512);
       };
       int k0 = (j0 + wave) * kSubKeys;
       load_k(k0);
@@ -1484,12 +1494,16 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
       if (!a.ll || !a.pass) return hipErrorInvalidValue;
       const dim3 sgrid(2 * cus);
       const size_t slds = attn_stream_lds(RS, a.head_dim);
+#define SD_STREAM(HDV)                                                                                            \
+  if (n_mt == 1) hipLaunchKernelGGL((attn_stream_kernel<HDV, true>), sgrid, dim3(64 * kLoopWaves), slds, s, a, n_sub, 1); \
+  else hipLaunchKernelGGL((attn_stream_kernel<HDV, false>), sgrid, dim3(64 * kLoopWaves), slds, s, a, n_sub, n_mt);
       switch (a.head_dim) {
-        case 32: hipLaunchKernelGGL((attn_stream_kernel<32>), sgrid, dim3(64 * kLoopWaves), slds, s, a, n_sub, n_mt); break;
-        case 64: hipLaunchKernelGGL((attn_stream_kernel<64>), sgrid, dim3(64 * kLoopWaves), slds, s, a, n_sub, n_mt); break;
-        case 128: hipLaunchKernelGGL((attn_stream_kernel<128>), sgrid, dim3(64 * kLoopWaves), slds, s, a, n_sub, n_mt); break;
+        case 32: SD_STREAM(32) break;
+        case 64: SD_STREAM(64) break;
+        case 128: SD_STREAM(128) break;
         default: return hipErrorInvalidValue;
       }
+#undef SD_STREAM
       return hipGetLastError();
     }
     if (NW > kMaxPartWaves || attn_block_lds(NW, RS, a.head_dim) > 65536) return hipErrorInvalidValue;
