@@ -21,9 +21,9 @@ constexpr int kMaxSs = 64;                    // ss partials a reduction sums
 // wave owns MTW x NTW of them.  Both operands are already 1 KB fragments in
 // MFMA order, so a stage (one k-step of 32: 2 KB of x per row tile, 1 KB per
 // weight tile) is copied from memory to LDS as it is, by loads that do not
-// pass the registers; ST stages are in flight.  RD: a wave reads the next
-// k-step's fragments while it multiplies the current ones (one barrier per
-// k-step); else it reads and multiplies in turn (larger tiles, fewer registers).
+// pass the registers; ST stages are in flight.  A wave reads the next k-step's
+// fragments while it multiplies the current ones, one barrier per k-step (7B
+// gate|up, 512 rows: 155 us; reading and multiplying in turn 170).
 // The weights are the A operand: D[4 (l/16) + r][l % 16] is weight row 4 (l/16)
 // + r, x row l % 16, so each lane stores four consecutive columns of one row;
 // a RoPE partner (column ^ 8) is lane ^ 32.
@@ -33,7 +33,7 @@ constexpr int kMaxSs = 64;                    // ss partials a reduction sums
 // 45 -> 35, down 105 -> 78, against staging float32 x through registers; 112
 // rows: gate|up 63 -> 50, Q|K|V 40 -> 31, O 21 -> 15, down 37 -> 29, LM head
 // 101 -> 75 (there 3.2 to 3.7 TB/s of weights).
-template <int WM, int WN, int MTW, int NTW, int ST, bool RD, int KIND>
+template <int WM, int WN, int MTW, int NTW, int ST, int KIND>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile(GemmArgs a, int n_ctiles, int ks_per_split, int n_split) {
   constexpr int NW = WM * WN, MTB = WM * MTW, NTB = WN * NTW;  // row and weight tiles of the block
   constexpr bool SCALE = KIND != EPI_RESID, SWIGLU = KIND == EPI_SWIGLU;
@@ -131,46 +131,33 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile(GemmArgs a, int n
       scale[m] = a.ss_in && row < M ? 1.0f / sqrtf(t / (float)K + a.eps) : 1.0f;
     }
   }
-  if constexpr (RD) {
-    Frags ra, rb;
-    wait_stages(std::integral_constant<int, ST - 1>{});
-    __builtin_amdgcn_s_barrier();
-    read(0, ra);
-    for (int i = 0; i < n_k; i += 2) {
+  Frags ra, rb;
+  wait_stages(std::integral_constant<int, ST - 1>{});
+  __builtin_amdgcn_s_barrier();
+  read(0, ra);
+  for (int i = 0; i < n_k; i += 2) {
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        if (i + u >= n_k) break;
-        wait_stages(std::integral_constant<int, ST - 2>{});
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        issue(i + u + ST);
-        if (u == 0) {
-          read(i + 1, rb);
-          multiply(ra);
-        } else {
-          read(i + 2, ra);
-          multiply(rb);
-        }
-        // the next step's fragment reads spread over this step's products
-        constexpr int NR = 2 * MTW + NTW, NM = 2 * MTW * NTW, PER = NM / NR;
-#pragma unroll
-        for (int k = 0; k < NR; ++k) {
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, NM - NR * PER, 0);
-      }
-    }
-  } else {
-    for (int i = 0; i < n_k; ++i) {
-      wait_stages(std::integral_constant<int, ST - 1>{});
-      __builtin_amdgcn_s_barrier();
-      Frags r;
-      read(i, r);
-      multiply(r);
+    for (int u = 0; u < 2; ++u) {
+      if (i + u >= n_k) break;
+      wait_stages(std::integral_constant<int, ST - 2>{});
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
-      issue(i + ST);
+      issue(i + u + ST);
+      if (u == 0) {
+        read(i + 1, rb);
+        multiply(ra);
+      } else {
+        read(i + 2, ra);
+        multiply(rb);
+      }
+      // the next step's fragment reads spread over this step's products
+      constexpr int NR = 2 * MTW + NTW, NM = 2 * MTW * NTW, PER = NM / NR;
+#pragma unroll
+      for (int k = 0; k < NR; ++k) {
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, NM - NR * PER, 0);
     }
   }
   wait_vm<0>();  // (the re-read stages past the range have landed before the block can end)
@@ -376,26 +363,26 @@ TilePlan plan_tile(int M, int n, int KS, bool pairs, bool can_split, bool always
   return best;
 }
 
-template <int WM, int WN, int MTW, int NTW, int ST, bool RD, int KIND>
+template <int WM, int WN, int MTW, int NTW, int ST, int KIND>
 void launch_shape(const GemmArgs& a, const TilePlan& p, hipStream_t s) {
   constexpr int BM = 16 * WM * MTW, BN = (KIND == EPI_SWIGLU ? 8 : 16) * WN * NTW;
   const int rt = (a.M + BM - 1) / BM, ct = (a.n_rows + BN - 1) / BN;
-  hipLaunchKernelGGL((gemm_bf16_tile<WM, WN, MTW, NTW, ST, RD, KIND>), dim3(rt * ((ct + 7) / 8 * 8) * p.n_split),
+  hipLaunchKernelGGL((gemm_bf16_tile<WM, WN, MTW, NTW, ST, KIND>), dim3(rt * ((ct + 7) / 8 * 8) * p.n_split),
                      dim3(64 * WM * WN), 0, s, a, ct, p.per, p.n_split);
 }
 template <int KIND>
 hipError_t launch_plan(const GemmArgs& a, const TilePlan& p, hipStream_t s) {
   switch (p.shape) {
-    case 0: launch_shape<4, 2, 4, 6, 3, false, KIND>(a, p, s); break;
-    case 1: launch_shape<4, 2, 4, 4, 3, true, KIND>(a, p, s); break;
-    case 2: launch_shape<8, 1, 2, 6, 4, true, KIND>(a, p, s); break;
-    case 3: launch_shape<4, 2, 2, 6, 4, true, KIND>(a, p, s); break;
-    case 4: launch_shape<2, 4, 4, 2, 4, true, KIND>(a, p, s); break;
-    case 7: launch_shape<2, 4, 3, 2, 4, true, KIND>(a, p, s); break;
+    case 0: launch_shape<4, 2, 4, 6, 3, KIND>(a, p, s); break;
+    case 1: launch_shape<4, 2, 4, 4, 3, KIND>(a, p, s); break;
+    case 2: launch_shape<8, 1, 2, 6, 4, KIND>(a, p, s); break;
+    case 3: launch_shape<4, 2, 2, 6, 4, KIND>(a, p, s); break;
+    case 4: launch_shape<2, 4, 4, 2, 4, KIND>(a, p, s); break;
+    case 7: launch_shape<2, 4, 3, 2, 4, KIND>(a, p, s); break;
     default:
       if constexpr (KIND != EPI_SWIGLU) {
-        if (p.shape == 5) launch_shape<4, 2, 2, 3, 4, true, KIND>(a, p, s);
-        else if (p.shape == 6) launch_shape<2, 4, 3, 3, 4, true, KIND>(a, p, s);
+        if (p.shape == 5) launch_shape<4, 2, 2, 3, 4, KIND>(a, p, s);
+        else if (p.shape == 6) launch_shape<2, 4, 3, 3, 4, KIND>(a, p, s);
         else return hipErrorInvalidValue;
         break;
       }
