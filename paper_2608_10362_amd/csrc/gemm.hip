@@ -67,7 +67,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, int blk, float (*yfi
         *hp = hv;
         const float xv = hv * load_gain(a.gain_out, a.gain_bf16, n);
         a.xg_out[(size_t)m * a.ldo + n] = xv;
-        if (a.xs_out) put_stacked(a.xs_out, a.stt, m, n, xv);
+        if (a.xs_out) put_stacked(a.xs_out, a.stt_out, m, n, xv);
       }
       yfin[m][c] = hv;
     }
@@ -87,7 +87,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, int blk, float (*yfi
         float u = yfin[m][H + c] * scale[m];
         const float y = silu_f(g) * u;
         a.out[(size_t)m * a.ldo + n] = y;
-        if (a.xs_out) put_stacked(a.xs_out, a.stt, m, n, y);
+        if (a.xs_out) put_stacked(a.xs_out, a.stt_out, m, n, y);
       }
     }
   }
@@ -414,8 +414,8 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
           hv = p.h + yfin[m][c];
           a.out[(size_t)m * a.ldo + n] = hv;
           const float xv = hv * bf16_bits_to_f32((uint16_t)p.g);
-          a.xg_out[(size_t)m * a.ldo + n] = xv;
-          if (a.xs_out) put_stacked(a.xs_out, a.stt, m, n, xv);
+          if (a.xs_out) put_stacked(a.xs_out, a.stt_out, m, n, xv);
+          else a.xg_out[(size_t)m * a.ldo + n] = xv;
         }
         yfin[m][c] = hv;
       }
@@ -915,7 +915,7 @@ __global__ __launch_bounds__(kQ4Threads) void gemm_q4_lds(GemmArgs a, int n_unit
         hv = pre_h + yfin[0][m][c];
         a.out[(size_t)m * a.ldo + n] = hv;
         const float xv = hv * bf16_bits_to_f32((uint16_t)pre_g);
-        if (a.xs_out) put_stacked(a.xs_out, a.stt, m, n, xv);
+        if (a.xs_out) put_stacked(a.xs_out, a.stt_out, m, n, xv);
         else a.xg_out[(size_t)m * a.ldo + n] = xv;
       }
       yfin[0][m][c] = hv;
@@ -1217,7 +1217,7 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
     return launch_gemm_tile(a, s);
   }
   if (a.M > kMaxGemmRows) return hipErrorInvalidValue;
-  if (dtype == SPECDEC_BF16 && a.M > kSkinnyRows) return launch_gemm_rows(a, s);
+  if (dtype == SPECDEC_BF16 && (a.M > kSkinnyRows || (!a.q4 && a.kind != EPI_RESID))) return launch_gemm_rows(a, s);
   const int blocks = gemm_row_blocks(dtype, a.kind, a.n_rows, a.M);
   if (a.q4) {  // INT4 layer weights (passes of at most 64 rows)
     if (dtype != SPECDEC_BF16 || (a.K % 32) != 0) return hipErrorInvalidValue;

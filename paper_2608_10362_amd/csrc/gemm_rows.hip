@@ -1,5 +1,5 @@
-// Weight-streaming GEMMs of passes of 17 to 128 rows (the verify blocks of
-// several sequences, draft steps of many, catch-up and prefill chunks):
+// Weight-streaming GEMMs of passes of at most 64 rows (verify blocks, draft
+// steps, catch-up and small prefill chunks):
 //   y[m, n] = s_m * sum_k W[n, k] x[m, k]
 // with bf16 weights from the packed image and x handed over by its producer
 // as the stacked bf16 operand (put_stacked: hi and lo parts, x = hi + lo +
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
         f32x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = silu_f(y[e] * sc) * (yu[e] * sc);
-        put_stacked4(a.xs_out, a.stt, m, n, o);
+        put_stacked4(a.xs_out, a.stt_out, m, n, o);
       }
     } else {
       const int n = unit * NC + 16 * t + 4 * rg;
@@ -241,31 +241,38 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
   // Prologue: the row-scale partial sums are requested before the weights
   // (loads complete in order), then both buffers.
   constexpr int RS = (MP + NW - 1) / NW;  // scale rows per wave
-  float rs[SCALE ? RS : 1];
+  constexpr int RP = MT == 1 ? 4 : 1;     // partial sums per lane held (passes of at most 16 rows: one per 16 columns)
+  float rs[SCALE ? RS : 1][RP];
   if constexpr (SCALE) {
     const __amdgpu_buffer_rsrc_t sr = make_rsrc(a.ss_in, a.ss_in ? (uint32_t)a.n_ss * a.ss_ld * 4u : 0u);
 #pragma unroll
-    for (int r = 0; r < RS; ++r) {
-      const int m = wave + r * NW;
-      const uint32_t off = ((uint32_t)lane * a.ss_ld + m) * 4u | ((uint32_t)(m >= M || lane >= a.n_ss) << 31);
-      rs[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, off, 0, 0));
-    }
+    for (int r = 0; r < RS; ++r)
+#pragma unroll
+      for (int i = 0; i < RP; ++i) {
+        const int m = wave + r * NW, p = lane + i * kWave;
+        const uint32_t off = ((uint32_t)p * a.ss_ld + m) * 4u | ((uint32_t)(m >= M || p >= a.n_ss) << 31);
+        rs[r][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, off, 0, 0));
+      }
   }
   load(wA, xA, sA);
   if (total > 1) load(wB, xB, sB);
   if constexpr (SCALE) {
-    // s_m = 1/sqrt(sum_p ss[p][m] / K + eps): partial p in lane p % 64, fixed shuffle tree
-    for (int p0 = kWave; p0 < a.n_ss; p0 += kWave)
-#pragma unroll
-      for (int r = 0; r < RS; ++r) {
-        const int m = wave + r * NW, p = p0 + lane;
-        if (a.ss_in && m < M && p < a.n_ss) rs[r] += a.ss_in[(size_t)p * a.ss_ld + m];
-      }
-    wave_sum_n(rs);
+    // s_m = 1/sqrt(sum_p ss[p][m] / K + eps): partial p in lane p % 64, in p order, fixed shuffle tree
+    float t[RS];
 #pragma unroll
     for (int r = 0; r < RS; ++r) {
       const int m = wave + r * NW;
-      if (lane == 0 && m < MP) scale[m] = (a.ss_in && m < M) ? 1.0f / sqrtf(rs[r] / (float)K + a.eps) : 1.0f;
+      t[r] = rs[r][0];
+#pragma unroll
+      for (int i = 1; i < RP; ++i) t[r] += rs[r][i];
+      if (a.ss_in && m < M)
+        for (int p = RP * kWave + lane; p < a.n_ss; p += kWave) t[r] += a.ss_in[(size_t)p * a.ss_ld + m];
+    }
+    wave_sum_n(t);
+#pragma unroll
+    for (int r = 0; r < RS; ++r) {
+      const int m = wave + r * NW;
+      if (lane == 0 && m < MP) scale[m] = (a.ss_in && m < M) ? 1.0f / sqrtf(t[r] / (float)K + a.eps) : 1.0f;
     }
   }
 
@@ -290,10 +297,11 @@ void launch_mt(const GemmArgs& a, int n_split, int per_split, hipStream_t s) {
   hipLaunchKernelGGL((gemm_bf16_rows<T, MT, NW, UB, KIND, Q4>), dim3(grid), dim3(64 * NW), 0, s, a, units, n_split,
                      per_split);
 }
-template <int T, int NW, int UB, int KIND, bool Q4 = false>
+template <int T, int NW, int UB, int KIND, bool Q4 = false, bool MT1 = false>
 void launch_t(const GemmArgs& a, int n_split, int per_split, hipStream_t s) {
   const int MT = (a.M + 15) / 16;
-  if (MT == 2) launch_mt<T, 2, NW, UB, KIND, Q4>(a, n_split, per_split, s);
+  if constexpr (MT1) launch_mt<T, 1, NW, UB, KIND, Q4>(a, n_split, per_split, s);
+  else if (MT == 2) launch_mt<T, 2, NW, UB, KIND, Q4>(a, n_split, per_split, s);
   else if (MT == 3) launch_mt<T, 3, NW, UB, KIND, Q4>(a, n_split, per_split, s);
   else launch_mt<T, 4, NW, UB, KIND, Q4>(a, n_split, per_split, s);
 }
@@ -303,6 +311,37 @@ void launch_t(const GemmArgs& a, int n_split, int per_split, hipStream_t s) {
 int unit_cost(int n_tiles, int T) {
   const int units = (n_tiles + T - 1) / T, cus = device_compute_units();
   return (units + cus - 1) / cus * (T + 1);
+}
+
+// Passes of at most 16 rows, bf16 weights: Q|K|V, gate|up and the LM head (the
+// residual GEMMs run gemm_bf16_mfma).  The unit sizes do not depend on the row
+// count, so a verify block equals its rows run one by one bit for bit.  A row
+// tile costs one register set here, so units hold two to four k-steps per
+// buffer.
+hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
+  const int KS = a.K / 32, tiles = a.n_rows / 16;
+  if (a.q4) return hipErrorInvalidValue;
+  switch (a.kind) {
+    case EPI_STORE:
+      // (a wave keeps at least 16 k-steps of a unit: fewer waves where K is
+      // short; K = 2048, 32000 rows: 22.2 us on 4 waves, 27.7 on 8)
+      if (KS >= 128) launch_t<4, 8, 2, EPI_STORE, false, true>(a, 1, KS, s);
+      else launch_t<4, 4, 4, EPI_STORE, false, true>(a, 1, KS, s);
+      break;
+    case EPI_QKV: {
+      const int c1 = unit_cost(tiles, 1), c2 = unit_cost(tiles, 2), c3 = unit_cost(tiles, 3);
+      if (c3 <= c2 && c3 <= c1) launch_t<3, 8, 2, EPI_QKV, false, true>(a, 1, KS, s);
+      else if (c2 <= c1) launch_t<2, 8, 4, EPI_QKV, false, true>(a, 1, KS, s);
+      else launch_t<1, 8, 4, EPI_QKV, false, true>(a, 1, KS, s);
+      break;
+    }
+    case EPI_SWIGLU:
+      if (unit_cost(2 * tiles, 6) <= unit_cost(2 * tiles, 4)) launch_t<6, 8, 2, EPI_SWIGLU, false, true>(a, 1, KS, s);
+      else launch_t<4, 8, 2, EPI_SWIGLU, false, true>(a, 1, KS, s);
+      break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 // INT4 weights: 4-wave blocks (a wave holds two groups' x and codes).
@@ -342,13 +381,14 @@ hipError_t launch_q4(const GemmArgs& a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
-  if (a.M <= kSkinnyRows || a.M > kMaxGemmRows || !a.xs || a.stt != 2 * ((a.M + 15) / 16) || a.K % 32 || a.n_rows % 16)
+  if (a.M <= 0 || a.M > kMaxGemmRows || !a.xs || a.stt != 2 * ((a.M + 15) / 16) || a.K % 32 || a.n_rows % 16)
     return hipErrorInvalidValue;
   if (a.kind == EPI_QKV && (a.kv.dtype != SPECDEC_BF16 || a.head_dim % 16 || a.n_seg[0] % a.head_dim ||
                             a.n_seg[1] % a.head_dim))
     return hipErrorInvalidValue;
   if (a.kind == EPI_SWIGLU && !a.xs_out) return hipErrorInvalidValue;
-  if (a.kind == EPI_RESID && (!a.ypart || !a.xs_out || !a.gain_bf16)) return hipErrorInvalidValue;
+  if (a.kind == EPI_RESID && (a.M <= kSkinnyRows || !a.ypart || !a.xs_out || !a.gain_bf16)) return hipErrorInvalidValue;
+  if (a.M <= kSkinnyRows) return launch_one(a, s);
   if (a.q4) return launch_q4(a, s);
   const int KS = a.K / 32, tiles = a.n_rows / 16;
   switch (a.kind) {

@@ -184,7 +184,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile(GemmArgs a, int n
           f32x4 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] = silu_f(y[e] * sc) * (yu[e] * sc);
-          put_stacked4(a.xs_out, a.stt, m, n, o);
+          put_stacked4(a.xs_out, a.stt_out, m, n, o);
         }
       } else {
         const int n = ct * 16 * NTB + 16 * btile(j) + 4 * rg;
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(GemmArgs a, int n_spl
     const uint16_t* g = (const uint16_t*)a.gain_out + n;
     const f32x4 x = f32x4{h[0] * bf16_bits_to_f32(g[0]), h[1] * bf16_bits_to_f32(g[1]), h[2] * bf16_bits_to_f32(g[2]),
                           h[3] * bf16_bits_to_f32(g[3])};
-    put_stacked4(a.xs_out, a.stt, m, n, x);
+    put_stacked4(a.xs_out, a.stt_out, m, n, x);
     t = h[0] * h[0] + h[1] * h[1] + h[2] * h[2] + h[3] * h[3];
   }
 #pragma unroll
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(GemmArgs a, int n_sp
   f32x4 o;
 #pragma unroll
   for (int e = 0; e < 4; ++e) o[e] = silu_f(gs[e] * sc) * (us[e] * sc);
-  put_stacked4(a.xs_out, a.stt, m, f, o);
+  put_stacked4(a.xs_out, a.stt_out, m, f, o);
 }
 
 // Sum of the split-K partial sums of a wide pass's Q|K|V projections in split

@@ -103,7 +103,7 @@ struct GemmArgs {
   // of xg_out and out).
   const uint16_t* xs;
   uint16_t* xs_out;
-  int stt;
+  int stt, stt_out;
   // INT4 weights: w[] are INT4 images (packed_int4_*), wscale[] their group scales
   int q4;
   const uint16_t* wscale[3];
