@@ -36,7 +36,7 @@ struct specdec_model {
   float* u;
   float* logits;
   void* samp;  // scratch of the draft's softmax / draw kernels
-  uint16_t* xs_d = nullptr;  // bf16: the stacked x operand of the d_model-column GEMMs (passes of <= 16 rows)
+  uint16_t* xs_d = nullptr;  // bf16: the stacked x operand of the d_model-column GEMMs
   uint16_t* xs_f = nullptr;  // bf16: the stacked attention output (the O projection's x), then SwiGLU output
   float* ypart = nullptr;  // split-K partials (passes of more than 16 rows)
   size_t ypart_floats = 0;

@@ -23,8 +23,8 @@ namespace {
 // ---------------------------------------------------------------- RoPE + append
 // Block (head slot, row): slots [0, H) rotate a query head into qr, [H, H+G)
 // rotate a key head and store it at the row's position, [H+G, H+2G) store a
-// value head (transposed).  Thread j handles the pair (j, j + hd/2).
-template <typename KT>
+// value head (transposed).  Thread j handles the pair (j, j + hd/2).  (float32
+// models; the bf16 Q|K|V GEMMs do this in their epilogues.)
 __global__ __launch_bounds__(64) void rope_append_kernel(AttnArgs a) {
   const int hs = blockIdx.x, r = blockIdx.y, j = threadIdx.x;
   const int hd = a.head_dim, half = hd / 2, H = a.n_heads, G = a.n_kv_heads;
@@ -35,9 +35,9 @@ __global__ __launch_bounds__(64) void rope_append_kernel(AttnArgs a) {
   const int cap = a.kv.capacity;
   if (hs >= H + G) {  // value head
     if (!rd.valid) return;
-    KT* blk = k_block<KT>(a.kv, a.layer, rd.b, hs - H - G);
-    Storage<KT>::store(blk + KvIndex<KT>::v(rd.pos, j, hd, cap), x1);
-    Storage<KT>::store(blk + KvIndex<KT>::v(rd.pos, j + half, hd, cap), x2);
+    float* blk = k_block<float>(a.kv, a.layer, rd.b, hs - H - G);
+    Storage<float>::store(blk + KvIndex<float>::v(rd.pos, j, hd, cap), x1);
+    Storage<float>::store(blk + KvIndex<float>::v(rd.pos, j + half, hd, cap), x2);
     return;
   }
   const float* cs = a.rope_cs + (size_t)r * hd;
@@ -48,9 +48,9 @@ __global__ __launch_bounds__(64) void rope_append_kernel(AttnArgs a) {
     q[j] = y1;
     q[j + half] = y2;
   } else if (rd.valid) {
-    KT* blk = k_block<KT>(a.kv, a.layer, rd.b, hs - H);
-    Storage<KT>::store(blk + KvIndex<KT>::k(rd.pos, j, hd, cap), y1);
-    Storage<KT>::store(blk + KvIndex<KT>::k(rd.pos, j + half, hd, cap), y2);
+    float* blk = k_block<float>(a.kv, a.layer, rd.b, hs - H);
+    Storage<float>::store(blk + KvIndex<float>::k(rd.pos, j, hd, cap), y1);
+    Storage<float>::store(blk + KvIndex<float>::k(rd.pos, j + half, hd, cap), y2);
   }
 }
 
@@ -1421,11 +1421,8 @@ int attention_chunk(int dtype, int head_dim) {
 }
 
 hipError_t launch_rope_append(const AttnArgs& a, hipStream_t s) {
-  dim3 grid(a.n_heads + 2 * a.n_kv_heads, a.M);
-  if (a.kv.dtype == SPECDEC_BF16)
-    hipLaunchKernelGGL((rope_append_kernel<uint16_t>), grid, dim3(64), 0, s, a);
-  else
-    hipLaunchKernelGGL((rope_append_kernel<float>), grid, dim3(64), 0, s, a);
+  if (a.kv.dtype != SPECDEC_F32) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(rope_append_kernel, dim3(a.n_heads + 2 * a.n_kv_heads, a.M), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 

@@ -1,15 +1,12 @@
-// Skinny-M weight-streaming GEMMs of the verify and draft passes:
+// Weight-streaming GEMMs of passes of at most 16 rows that gemm_rows.hip does
+// not take, the float32 GEMMs, and the weight images:
 //   y[m, n] = s_m * sum_k W[n, k] * (x[m, k] * g[k])
-// with M = rows of the pass (gamma+1 per sequence for verify, 1-2 for a draft
-// step) and W streamed once from HBM.  Epilogues: store (Q|K|V projections,
-// LM head), residual add (O and down projections, also emitting the partial
-// sums of squares the next RMSNorm needs), and SwiGLU (gate|up).
-//
-// bf16 weights run on MFMA (v_mfma_f32_16x16x32_bf16).  The float32
-// activations are split into hi + lo bf16 parts (x = hi + lo + O(2^-17 |x|)),
-// so two MFMAs per weight fragment reproduce a float32-accuracy product while
-// the weight fragment is read from HBM once; the padding of M up to 16 is
-// free because the pass is bandwidth-bound (about M flops per weight byte).
+// with W streamed once from HBM.  gemm_bf16_mfma: the residual GEMMs (O and
+// down projections) of bf16 weights, which add to h and emit the partial sums
+// of squares the next RMSNorm needs, and INT4 shapes gemm_q4_lds does not
+// cover.  gemm_q4_lds: INT4 layers.  Both run on MFMA (v_mfma_f32_16x16x32_bf16)
+// with x as hi + lo bf16 parts (x = hi + lo + O(2^-17 |x|)), so two products
+// per weight fragment give float32 accuracy while the weights are read once.
 // float32 weights (the tiny configuration) run on a plain vector kernel.
 #include <algorithm>
 #include <type_traits>
@@ -164,7 +161,7 @@ struct Q4Frag {
   uint32_t scale;  // bf16 bits of the group scale of the lane's row (lane % 16)
 };
 
-// ---------------------------------------------------------------- MFMA kernel (bf16 weights)
+// ---------------------------------------------------------------- MFMA kernel
 // Persistent: one 16-wave block per CU loops over row tiles of NC = 16*T
 // weight rows (tile = blockIdx.x + i*gridDim.x).  Within a tile, wave w
 // reduces k-steps [w*KS/16, (w+1)*KS/16) of 32 columns each, UB k-steps per
@@ -174,23 +171,24 @@ struct Q4Frag {
 // MFMA operand layout (16x16x32): lane l holds A[l%16][8(l/16)+j] (x rows),
 // B[8(l/16)+j][l%16] (= W[n0 + l%16][k0 + 8(l/16) + j]: 16 bytes at lane*16 of
 // the packed 1 KB fragment), D[4(l/16)+r][l%16].
-template <int T, int UB, int KIND, bool Q4 = false, int XS = 0>
+template <int T, int UB, int KIND, int XS>
 __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n_tiles) {
-  // Q4: INT4 weights (Q4Frag).  A code q is fed to the MFMA as the bf16 value
-  // 136 + q (bits 0x4300 | (q + 8): two byte permutes and an OR per four
-  // codes), and the bias is cancelled inside the accumulator by a product of
-  // the same x with the constant -136, shared by the unit's tiles; each
-  // k-step's product is then multiplied by the lane's row scale in float32,
-  // so the effective weights are code * scale.
-  // XS > 0: x comes as the stacked operand a.xs (put_stacked, XS fragments
-  // per k-step, at most 8 rows when XS = 1, 16 when XS = 2) in place of the
-  // float32 rows: one 16-byte load per fragment and one product per fragment
-  // and tile.  The hi and lo parts accumulate apart (accumulator tiles 0 and
-  // 1, or rows m and 8 + m of tile 0) and are added once per tile before the
-  // cross-wave sums, the same arithmetic for either count of fragments.
+  // XS = 0: INT4 weights (Q4Frag) and float32 x.  A code q is fed to the MFMA
+  // as the bf16 value 136 + q (bits 0x4300 | (q + 8): two byte permutes and an
+  // OR per four codes), and the bias is cancelled inside the accumulator by a
+  // product of the same x with the constant -136, shared by the unit's tiles;
+  // each k-step's product is then multiplied by the lane's row scale in
+  // float32, so the effective weights are code * scale.
+  // XS > 0: bf16 weights and x as the stacked operand a.xs (put_stacked, XS
+  // fragments per k-step, at most 8 rows when XS = 1, 16 when XS = 2): one
+  // 16-byte load per fragment and one product per fragment and tile.  The hi
+  // and lo parts accumulate apart (accumulator tiles 0 and 1, or rows m and
+  // 8 + m of tile 0) and are added once per tile before the cross-wave sums,
+  // the same arithmetic for either count of fragments.
   // XS = 3: XS = 1 with each wave's x fragments (at most 8 k-steps, K <= 4096)
   // fetched once into LDS and read from there for every unit of the block.
-  static_assert(XS == 0 || !Q4, "stacked x: bf16 weights");
+  constexpr bool Q4 = XS == 0;
+  static_assert(Q4 || KIND == EPI_RESID, "bf16 weights: residual GEMMs");
   constexpr int MT = 1;  // (at most kSkinnyRows rows)
   using WReg = std::conditional_t<Q4, Q4Frag, u32x4>;
   constexpr bool XL = XS == 3;
@@ -337,9 +335,7 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
           acc[t][0] =
               __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, __builtin_bit_cast(bf16x8, wv[u][t]), acc[t][0], 0, 0, 0);
       }
-      return;
-    }
-    if constexpr (XS) {
+    } else if constexpr (XS) {
 #pragma unroll
       for (int u = 0; u < UB; ++u)
 #pragma unroll
@@ -350,14 +346,12 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
             acc[t][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, __builtin_bit_cast(bf16x8, wv[u][t]), acc[t][f],
                                                                 0, 0, 0);
         }
-      return;
-    }
+    } else {
 #pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      // Q4: the codes of each tile as biased bf16 operands and the row scales
-      bf16x8 bq[Q4 ? T : 1];
-      float sc[Q4 ? T : 1];
-      if constexpr (Q4) {
+      for (int u = 0; u < UB; ++u) {
+        // the codes of each tile as biased bf16 operands and the row scales
+        bf16x8 bq[T];
+        float sc[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
           const uint32_t c = wv[u][t].codes ^ 0x88888888u;  // q + 8 in each nibble
@@ -371,35 +365,25 @@ __global__ __launch_bounds__(kMfmaThreads) void gemm_bf16_mfma(GemmArgs a, int n
           bq[t] = __builtin_bit_cast(bf16x8, v);
           sc[t] = bf16_bits_to_f32((uint16_t)wv[u][t].scale);
         }
-      }
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
         bf16x8 hi, lo;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-          const float v = xv[u][mt][j >> 2][j & 3];
+          const float v = xv[u][0][j >> 2][j & 3];
           const __bf16 h = (__bf16)v;
           hi[j] = h;
           lo[j] = (__bf16)(v - (float)h);
         }
+        // -136 * sum_k x[m][k] in every column
+        const u32x4 m136 = u32x4{0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u};
         floatx4 bias = floatx4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (Q4) {  // -136 * sum_k x[m][k] in every column
-          const u32x4 m136 = u32x4{0xC308C308u, 0xC308C308u, 0xC308C308u, 0xC308C308u};
-          bias = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, __builtin_bit_cast(bf16x8, m136), bias, 0, 0, 0);
-          bias = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, __builtin_bit_cast(bf16x8, m136), bias, 0, 0, 0);
-        }
+        bias = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, __builtin_bit_cast(bf16x8, m136), bias, 0, 0, 0);
+        bias = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, __builtin_bit_cast(bf16x8, m136), bias, 0, 0, 0);
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-          if constexpr (Q4) {
-            floatx4 p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, bq[t], bias, 0, 0, 0);
-            p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, bq[t], p, 0, 0, 0);
+          floatx4 p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, bq[t], bias, 0, 0, 0);
+          p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, bq[t], p, 0, 0, 0);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[t][mt][r] = fmaf(sc[t], p[r], acc[t][mt][r]);
-          } else {
-            const bf16x8 b = __builtin_bit_cast(bf16x8, wv[u][t]);
-            acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, b, acc[t][mt], 0, 0, 0);
-            acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, b, acc[t][mt], 0, 0, 0);
-          }
+          for (int r = 0; r < 4; ++r) acc[t][0][r] = fmaf(sc[t], p[r], acc[t][0][r]);
         }
       }
     }
@@ -991,37 +975,25 @@ int compute_units() {
 // stacked x fragment per k-step, from memory or LDS, have the registers for
 // four: measured 9.9 -> 9.2 us for the 7B O projection; two fragments per
 // k-step or float32 x would spill.)
-template <int T, bool Q4, int XS> struct Batch {
-  static constexpr int UB = T == 1 ? (!Q4 && (XS == 1 || XS == 3) ? 4 : 3) : (T == 2 ? 2 : 1);
+template <int T, int XS> struct Batch {
+  static constexpr int UB = T == 1 ? (XS == 1 || XS == 3 ? 4 : 3) : (T == 2 ? 2 : 1);
 };
 
-template <int T, int KIND, bool Q4 = false, int XS = 0>
-void launch_mfma_x(const GemmArgs& a, int tiles, hipStream_t s) {
+template <int T, int KIND, int XS>
+hipError_t launch_mfma_x(const GemmArgs& a, int tiles, hipStream_t s) {
   const int grid = tiles < compute_units() ? tiles : compute_units();
-  hipLaunchKernelGGL((gemm_bf16_mfma<T, Batch<T, Q4, XS>::UB, KIND, Q4, XS>), dim3(grid), dim3(kMfmaThreads), 0, s, a,
-                     tiles);
+  hipLaunchKernelGGL((gemm_bf16_mfma<T, Batch<T, XS>::UB, KIND, XS>), dim3(grid), dim3(kMfmaThreads), 0, s, a, tiles);
+  return hipGetLastError();
 }
 
-template <int T, int KIND, bool Q4 = false>
+// bf16 weights: a residual GEMM, x held in LDS where a wave's share of one
+// fragment per k-step fits.
+template <int T>
 hipError_t launch_mfma_t(const GemmArgs& a, int blocks, hipStream_t s) {
-  if (a.M > kSkinnyRows) return hipErrorInvalidValue;
-  if constexpr (!Q4) {
-    if (a.xs) {
-      if (a.stt != (a.M <= 8 ? 1 : 2)) return hipErrorInvalidValue;
-      // (x held in LDS: measured faster for the store, SwiGLU and residual GEMMs, slower for Q|K|V, whose
-      // epilogue tables then leave room for one reduction fragment per round only)
-      if (KIND != EPI_QKV && a.stt == 1 && (a.K + 31) / 32 <= 8 * kMfmaWaves)
-        launch_mfma_x<T, KIND, false, 3>(a, blocks, s);
-      else if (a.stt == 1) launch_mfma_x<T, KIND, false, 1>(a, blocks, s);
-      else launch_mfma_x<T, KIND, false, 2>(a, blocks, s);
-      return hipGetLastError();
-    }
-  }
-  if constexpr (Q4 || KIND == EPI_STORE) {  // (float32 x: INT4 layers, and the LM head behind them)
-    launch_mfma_x<T, KIND, Q4>(a, blocks, s);
-    return hipGetLastError();
-  }
-  return hipErrorInvalidValue;
+  if (a.stt != (a.M <= 8 ? 1 : 2)) return hipErrorInvalidValue;
+  if (a.M > 8) return launch_mfma_x<T, EPI_RESID, 2>(a, blocks, s);
+  if ((a.K + 31) / 32 <= 8 * kMfmaWaves) return launch_mfma_x<T, EPI_RESID, 3>(a, blocks, s);
+  return launch_mfma_x<T, EPI_RESID, 1>(a, blocks, s);
 }
 
 // 16-row tiles per work unit of the bf16 kernel.  More tiles per unit mean
@@ -1231,46 +1203,23 @@ hipError_t launch_gemm(int dtype, const GemmArgs& a, hipStream_t s) {
     switch (a.kind) {
       case EPI_RESID:
         if (!a.gain_bf16) return hipErrorInvalidValue;
-        return T == 1 ? launch_mfma_t<1, EPI_RESID, true>(a, blocks, s)
-                      : (T == 2 ? launch_mfma_t<2, EPI_RESID, true>(a, blocks, s)
-                                : launch_mfma_t<3, EPI_RESID, true>(a, blocks, s));
-      case EPI_SWIGLU: return launch_mfma_t<2, EPI_SWIGLU, true>(a, blocks, s);
+        return T == 1 ? launch_mfma_x<1, EPI_RESID, 0>(a, blocks, s)
+                      : (T == 2 ? launch_mfma_x<2, EPI_RESID, 0>(a, blocks, s)
+                                : launch_mfma_x<3, EPI_RESID, 0>(a, blocks, s));
+      case EPI_SWIGLU: return launch_mfma_x<2, EPI_SWIGLU, 0>(a, blocks, s);
       case EPI_QKV:
         if (a.kv.dtype != SPECDEC_BF16 || a.head_dim % 16 || a.n_seg[0] % a.head_dim || a.n_seg[1] % a.head_dim)
           return hipErrorInvalidValue;
-        return T == 1 ? launch_mfma_t<1, EPI_QKV, true>(a, blocks, s)
-                      : (T == 2 ? launch_mfma_t<2, EPI_QKV, true>(a, blocks, s)
-                                : launch_mfma_t<3, EPI_QKV, true>(a, blocks, s));
+        return T == 1 ? launch_mfma_x<1, EPI_QKV, 0>(a, blocks, s)
+                      : (T == 2 ? launch_mfma_x<2, EPI_QKV, 0>(a, blocks, s)
+                                : launch_mfma_x<3, EPI_QKV, 0>(a, blocks, s));
       default: return hipErrorInvalidValue;
     }
   }
-  if (dtype == SPECDEC_BF16) {
-    if (a.kind == EPI_RESID && !a.gain_bf16) return hipErrorInvalidValue;
-    const int T = mfma_tiles(a.kind, a.n_rows);
-    switch (a.kind) {
-      case EPI_STORE: {
-        // (x as the stacked operand: single-tile units, which hold four k-steps
-        // per register buffer, where they balance over the CUs as well; the 7B
-        // LM head over 5 rows took 43.3 us in 2000 units against 45.3 us in 1000.
-        // With float32 x the larger unit stays: 46 against 59 us.)
-        const int cus = compute_units(), u1 = (a.n_rows + 15) / 16;
-        const double e1 = (double)u1 / ((double)((u1 + cus - 1) / cus) * cus);
-        const double eT = (double)blocks / ((double)((blocks + cus - 1) / cus) * cus);
-        if (a.xs && T > 1 && e1 >= eT - 1e-9) return launch_mfma_t<1, EPI_STORE>(a, u1, s);
-        return T == 1 ? launch_mfma_t<1, EPI_STORE>(a, blocks, s)
-                      : (T == 2 ? launch_mfma_t<2, EPI_STORE>(a, blocks, s) : launch_mfma_t<3, EPI_STORE>(a, blocks, s));
-      }
-      case EPI_RESID:
-        return T == 1 ? launch_mfma_t<1, EPI_RESID>(a, blocks, s)
-                      : (T == 2 ? launch_mfma_t<2, EPI_RESID>(a, blocks, s) : launch_mfma_t<3, EPI_RESID>(a, blocks, s));
-      case EPI_SWIGLU: return launch_mfma_t<2, EPI_SWIGLU>(a, blocks, s);
-      case EPI_QKV:
-        if (a.kv.dtype != SPECDEC_BF16 || a.head_dim % 16 || a.n_seg[0] % a.head_dim || a.n_seg[1] % a.head_dim)
-          return hipErrorInvalidValue;
-        return T == 1 ? launch_mfma_t<1, EPI_QKV>(a, blocks, s)
-                      : (T == 2 ? launch_mfma_t<2, EPI_QKV>(a, blocks, s) : launch_mfma_t<3, EPI_QKV>(a, blocks, s));
-    }
-    return hipErrorInvalidValue;
+  if (dtype == SPECDEC_BF16) {  // (RESID: the other kinds run launch_gemm_rows)
+    if (!a.gain_bf16 || !a.xs || !a.xs_out) return hipErrorInvalidValue;
+    const int T = mfma_tiles(EPI_RESID, a.n_rows);
+    return T == 1 ? launch_mfma_t<1>(a, blocks, s) : (T == 2 ? launch_mfma_t<2>(a, blocks, s) : launch_mfma_t<3>(a, blocks, s));
   }
   switch (a.kind) {
     case EPI_STORE: hipLaunchKernelGGL((gemm_f32_vector<16, EPI_STORE>), dim3(blocks), dim3(256), 0, s, a); break;

@@ -58,7 +58,7 @@ template <> struct KvIndex<uint16_t> {
 // same 16-row tile, which the packed image provides (see launch_pack).
 enum EpiKind { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
 constexpr int kMaxGemmRows = 64;  // rows of x per launch of the skinny kernels (callers split larger M)
-constexpr int kSkinnyRows = 16;   // bf16 weights: passes of more rows run launch_gemm_rows (to kMaxGemmRows)
+constexpr int kSkinnyRows = 16;   // passes of more rows (to kMaxGemmRows) run launch_gemm_rows throughout
 constexpr int kRowsSplitMax = 8;  // K splits of its residual GEMMs (partials in ypart: kRowsSplitMax * M * n_rows)
 // Passes of more than kMaxGemmRows bf16 rows run launch_gemm_tile in launches
 // of up to kTileLaunchRows rows; GEMMs that split K over the grid there need
@@ -98,9 +98,9 @@ struct GemmArgs {
   float* ypart;           // split-K partial sums, ypart_floats floats
   size_t ypart_floats;
   // x as a stacked operand (put_stacked, stt fragments per k-step), read
-  // instead of x when xs is set (always over more than kSkinnyRows rows); RESID
-  // and SwiGLU epilogues write their output stacked into xs_out (there in place
-  // of xg_out and out).
+  // instead of x when xs is set (always, except for INT4 weights over at most
+  // kSkinnyRows rows); RESID and SwiGLU epilogues write their output stacked
+  // into xs_out, stt_out fragments per k-step (in place of xg_out and out).
   const uint16_t* xs;
   uint16_t* xs_out;
   int stt, stt_out;
@@ -126,7 +126,8 @@ hipError_t launch_pack_int4(const void* src, void* frag, void* scale, int N, int
 // Number of row blocks the launcher uses for this GEMM (for ss partial counts)
 // in a pass of M rows.
 int gemm_row_blocks(int dtype, int kind, int n_rows, int M);
-// GEMMs of 17 to 64 rows over the stacked operand, bf16 or INT4 weights (gemm_rows.hip).
+// GEMMs of at most 64 rows over the stacked operand (gemm_rows.hip): bf16
+// weights (residual GEMMs from 17 rows), INT4 weights from 17 rows.
 hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s);
 // bf16 GEMMs of passes of more than 64 rows (gemm_tile.hip).
 hipError_t launch_gemm_tile(const GemmArgs& a, hipStream_t s);
