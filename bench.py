@@ -158,7 +158,7 @@ def measured_traffic(kernel: str):
         if ":" in line and not line.startswith(("|", "#", "`", "-")):
             k, v = line.split(":", 1)
             fields[k.strip()] = v.strip()
-    src = os.path.join(ROOT, "paper_2608_10362_amd", "csrc", "gemm.hip")
+    src = os.path.join(ROOT, "paper_2608_10362_amd", "csrc", "gemm_rows.hip")
     if not os.path.exists(src):
         return None
     sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
