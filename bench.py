@@ -580,9 +580,11 @@ def run_prefill(args):
     dw = device_weights(shape)
     tok = torch.from_numpy(synth.make_prompt(n, shape.vocab)).cuda()
     d, f = shape.d_model, shape.ffn_dim
-    # linear-layer flops per token (2 per multiply-add) and attention flops over the causal prefix
-    lin = 2 * (shape.n_layers * (d * (shape.q_dim + 2 * shape.kv_dim) + shape.q_dim * d + 3 * d * f) + d * shape.vocab)
-    attn = shape.n_layers * 2 * 2 * shape.q_dim * (n - 1) * n / 2
+    # linear-layer flops per token (2 per multiply-add) and attention flops over the causal prefix; a prefill pass
+    # ends with the last layer's K and V projections
+    full = shape.n_layers - 1
+    lin = 2 * (full * (d * (shape.q_dim + 2 * shape.kv_dim) + shape.q_dim * d + 3 * d * f) + 2 * d * shape.kv_dim)
+    attn = full * 2 * 2 * shape.q_dim * (n - 1) * n / 2
     flops = lin * (n - 1) + attn
     out = {}
     for rows in (64, 128, 256, 512):
