@@ -255,7 +255,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
       }
   }
   load(wA, xA, sA);
-  if (total > 1) load(wB, xB, sB);
+  constexpr bool PEEL = MT > 1 || T == 3 || T == 6;
+  if (PEEL || total > 1) load(wB, xB, sB);  // (PEEL, past the last batch: weights out of range)
   if constexpr (SCALE) {
     // s_m = 1/sqrt(sum_p ss[p][m] / K + eps): partial p in lane p % 64, in p order, fixed shuffle tree
     float t[RS];
@@ -276,16 +277,46 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
     }
   }
 
-  int q = 0, cu = u0, cb = 0;  // compute cursor
-  while (true) {
+  // Refills without a branch, the last batches peeled off (PEEL): with a branch
+  // around a refill the compiler waits for both buffers before the first
+  // product of either (40 rows, 7B: Q|K|V 28.0 -> 26.8 us, O and down 33.8 ->
+  // 32.0 together, LM head 57 -> 50; 5 rows: Q|K|V 18.5 -> 18.0).  Not in the
+  // units of 1, 2 or 4 tiles over at most 16 rows: their k loops are a few
+  // batches (K = 2048), and the longer code costs more (1.1B draft 804 -> 808).
+  int cu = u0, cb = 0, left = total;  // compute cursor, batches left
+  auto done = [&]() {
+    if (++cb == nbat) { finish(cu); cb = 0; cu += us; }
+  };
+  if constexpr (!PEEL) {
+    while (true) {
+      compute(wA, xA, sA);
+      if (left > 2) load(wA, xA, sA);
+      done();
+      if (--left == 0) return;
+      compute(wB, xB, sB);
+      if (left > 2) load(wB, xB, sB);
+      done();
+      if (--left == 0) return;
+    }
+  }
+  for (; left > 3; left -= 2) {
     compute(wA, xA, sA);
-    if (q + 2 < total) load(wA, xA, sA);
-    if (++cb == nbat) { finish(cu); cb = 0; cu += us; }
-    if (++q >= total) break;
+    load(wA, xA, sA);
+    done();
     compute(wB, xB, sB);
-    if (q + 2 < total) load(wB, xB, sB);
-    if (++cb == nbat) { finish(cu); cb = 0; cu += us; }
-    if (++q >= total) break;
+    load(wB, xB, sB);
+    done();
+  }
+  compute(wA, xA, sA);
+  if (left == 3) load(wA, xA, sA);
+  done();
+  if (left > 1) {
+    compute(wB, xB, sB);
+    done();
+  }
+  if (left == 3) {
+    compute(wA, xA, sA);
+    done();
   }
 }
 
@@ -393,11 +424,13 @@ hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
   const int KS = a.K / 32, tiles = a.n_rows / 16;
   switch (a.kind) {
     case EPI_STORE:
-      // Larger units read x fewer times: 8 tiles unless 4 fill the CUs' rounds
-      // better (7B LM head, 40 rows: 52.6 us in 250 units of 8, 54.7 in 500 of
-      // 4) or the k loop is too short to cover a unit's reduction (K = 2048, 20
-      // rows: 31.8 us against 26.4).
-      if (KS >= 128 && unit_cost(tiles, 8) <= unit_cost(tiles, 4)) launch_t<8, 4, 1, EPI_STORE>(a, 1, KS, s);
+      // Larger units read x fewer times: 8 tiles over more than two row tiles,
+      // unless 4 fill the CUs' rounds better (7B LM head, 40 rows: 50 us in 250
+      // units of 8; 20 rows: 47.5, in 500 of 4 44.4).  Where K is short a unit
+      // of 4 on 4 waves, which keep 16 k-steps each (K = 2048, 32000 rows, 20
+      // rows of x: 24.7 us, 27.7 on 8 waves, 28.5 in units of 8).
+      if (KS < 128) launch_t<4, 4, 1, EPI_STORE>(a, 1, KS, s);
+      else if (a.M > 32 && unit_cost(tiles, 8) <= unit_cost(tiles, 4)) launch_t<8, 4, 1, EPI_STORE>(a, 1, KS, s);
       else launch_t<4, 8, 1, EPI_STORE>(a, 1, KS, s);
       break;
     case EPI_QKV: {
