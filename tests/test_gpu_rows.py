@@ -1,5 +1,5 @@
-"""Passes of more than 16 rows (the GEMMs over the stacked operand: streaming
-to 64 rows, tiles above) against the float64 oracle, at the edges of their row tiles, on shapes whose
+"""Passes of the GEMMs over the stacked operand (streaming to 64 rows, tiles
+above) against the float64 oracle, at the edges of their row tiles, on shapes whose
 tile counts leave remainders in every unit size and fewer k-steps than waves,
 and at the 7B widths that take the large units."""
 import numpy as np
@@ -14,6 +14,9 @@ pytestmark = pytest.mark.gpu
 
 # 20 Q|K|V tiles, 12 residual tiles, 22 gate / up pairs, 31 head tiles; K of 192 (6 k-steps) and 352 (11)
 ODD = synth.ModelShape(2, 192, 6, 2, 32, 352, 496)
+# K of 576 (18 k-steps) and 1184 (37): waves of a block with different numbers of batches, odd and even, fewer than the
+# two a wave holds and more; 275 LM-head units of four tiles, more than one round of the CUs
+UNEVEN = synth.ModelShape(2, 576, 18, 6, 32, 1184, 17600)
 # float32-accuracy products (2^-17 per product) behind keys and values stored in bf16: single values one
 # bf16 unit apart (2^-8) move the logits by 1e-5 to 5e-5 of their norm
 REL = 2e-4
@@ -29,6 +32,11 @@ def _rows_case(shape, n_layers, lengths, g, seed):
 @pytest.mark.parametrize("B,g", [(17, 0), (4, 7), (11, 2), (6, 7), (7, 6), (8, 7)])
 def test_odd_shape_rows(B, g):
     _rows_case(ODD, 2, [1 + (37 * b) % 90 for b in range(B)], g, seed=B)
+
+
+@pytest.mark.parametrize("B,g", [(1, 0), (1, 7), (3, 2), (4, 3), (5, 3), (5, 7), (7, 7)])
+def test_uneven_k_rows(B, g):
+    _rows_case(UNEVEN, 1, [1 + (37 * b) % 90 for b in range(B)], g, seed=B)
 
 
 # (the tile kernel: more than 64 rows, row tiles of 96, 128 and 256 with remainders, launches of 1024 rows)
