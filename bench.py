@@ -569,8 +569,8 @@ def run_switching(args):
 def run_prefill(args):
     """Prefill of a 2048-token prompt on the 7B-shaped bf16 target (32 layers),
     in chunks of 64, 128, 256 and 512 rows (the handle's max_rows): chunks of
-    more than 64 rows run the wide GEMM in launches of up to 128 rows and the
-    looping attention.  Eager launches timed with HIP events, best of 3 after a
+    more than 64 rows run the tile GEMM, chunks of 64 and more the attention of
+    64-query blocks.  Eager launches timed with HIP events, best of 3 after a
     warm-up; the cache length is reset between runs."""
     import torch
 

@@ -268,7 +268,7 @@ __global__ __launch_bounds__(256) void resid_reduce_kernel(GemmArgs a, int n_spl
   if ((tid & 31) == 0 && m < M) a.ss_out[(size_t)blockIdx.x * a.ss_ld + m] = t;
 }
 
-// Sum of the split-K partial sums of a wide pass's gate and up projections
+// Sum of the split-K partial sums of a pass's gate and up projections
 // (rows [0, F) and [F, 2F) of the partials) in split order, times the row's
 // RMSNorm scale, then SwiGLU.  Block = 128 columns x 8 rows; thread = 4 columns of one row.
 __global__ __launch_bounds__(256) void swiglu_reduce_kernel(GemmArgs a, int n_split) {
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256) void swiglu_reduce_kernel(GemmArgs a, int n_sp
   put_stacked4(a.xs_out, a.stt_out, m, f, o);
 }
 
-// Sum of the split-K partial sums of a wide pass's Q|K|V projections in split
+// Sum of the split-K partial sums of a pass's Q|K|V projections in split
 // order, times the row's RMSNorm scale, then RoPE on the Q and K columns and
 // the stores: rotated queries to qr, rotated keys and the values appended to
 // the KV cache (valid rows).  Q and K columns come in the packed RoPE order:
