@@ -23,9 +23,11 @@ template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_wai
 
 // 16 bytes per lane from rsrc at `off` into LDS at dst + 16 * lane, without
 // passing the registers.  (Inline asm, so that the compiler does not wait for
-// every such load before each LDS read: the kernel counts them itself.)
+// every such load before each LDS read: the kernel counts them itself.  The
+// load takes its LDS address from M0, which needs one wait state after a
+// scalar write, and the compiler adds none inside an asm block: the s_nop.)
 __device__ __forceinline__ void load_lds16(uint32_t dst, uint32_t off, __amdgpu_buffer_rsrc_t rsrc) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rsrc)
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(rsrc)
                : "memory", "m0");
 }
 
