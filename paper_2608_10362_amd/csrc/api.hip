@@ -333,6 +333,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
     m->attn_ready = true;
   }
   ra.pass = m->attn_pass;
+  ra.n_layers = m->n_layers;
   {
     Timed t(SPECDEC_KERNEL_EMBED, s);
     SD_TRY(launch_rows_embed(dt, ra, s));

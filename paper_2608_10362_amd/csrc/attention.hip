@@ -650,9 +650,8 @@ __global__ __launch_bounds__(64 * kMaxPartWaves) void attn_block_kernel(AttnArgs
 // It polls until every word read carries this launch's tag.  Every block it
 // waits for has a lower index (so it was dispatched no later) and stores all its
 // words before it polls itself, so the wait always ends; a bounded poll count
-// turns a broken invariant into a status.  The tag is the pass count, which the
-// embedding kernel advances, times the layers, plus the layer: no two launches
-// of a handle share one.
+// turns a broken invariant into a status.  The tag comes from the pass count,
+// which the embedding kernel advances, and the layer.
 // Bound: the key and value stream.  16 sequences of 1024 to 8192 keys (1.26 GB
 // per layer of the 7B shape): 255 us in parts sized for 12 blocks per CU
 // (4.9 TB/s), 218 now (5.8 TB/s); 8 sequences of 513 to 2048: 53 us, 44 now.
@@ -683,7 +682,7 @@ __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArg
     const RowDesc last = a.rows[s * rps + rps - 1];
     return last.valid ? min(n_sub, last.pos / kSubKeys + 1) : n_sub;
   };
-  const uint32_t tag = a.pass[0] * (uint32_t)a.n_layers + (uint32_t)a.layer + 1u;
+  const uint32_t tag = attention_tag(a.pass[0], (uint32_t)a.n_layers, (uint32_t)a.layer);
   const int n0 = lane < B ? subs_of(lane) : 0;  // (the first 64 sequences stay in a register)
   int subs = 0;
   for (int c = 0; c < B; c += kWave) {

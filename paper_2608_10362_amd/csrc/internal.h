@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "specdec.h"
+#include "attention_tag.h"
 #include "device_common.h"
 
 namespace specdec {
@@ -157,7 +158,8 @@ struct RowsArgs {
   float* h;               // out [M, d]
   float* xg;              // out [M, d] h * gain
   float* ss;              // out [M] sum of squares of h rows
-  uint32_t* pass;         // or null: the handle's pass count, advanced by one
+  uint32_t* pass;         // or null: the handle's pass count, advanced by one (attention_pass_after)
+  int n_layers;           // of the handle
   uint16_t* xs;           // or null: xg goes out as the stacked operand (put_stacked, stt fragments per k-step) only
   int stt;
 };
@@ -186,8 +188,8 @@ struct AttnArgs {
   // combine kernel adds the parts): one word per (sequence, query tile, kv
   // head), zero between launches; the last block to count combines.  ll (long
   // contexts and batches): [M, h, ll_parts, hd + 2] tagged words: low half the
-  // float (hd O values, then max and sum), high half the launch's tag, pass[0]
-  // * n_layers + layer + 1 (the embedding kernel advances pass[0]).
+  // float (hd O values, then max and sum), high half the launch's tag
+  // (attention_tag of pass[0], which the embedding kernel advances).
   uint32_t* counters;
   uint64_t* ll;
   int ll_parts, n_layers;
