@@ -1093,7 +1093,11 @@ specdec_status specdec_time_kernel(const specdec_model* m, int32_t kind, int32_t
     switch (kind) {
       case SPECDEC_KERNEL_EMBED: return launch_rows_embed(dt, m->rec_embed, s);
       case SPECDEC_KERNEL_ROPE_APPEND: return launch_rope_append(m->rec_attn[(size_t)i % m->rec_attn.size()], s);
-      case SPECDEC_KERNEL_ATTENTION: return launch_attention(m->rec_attn[(size_t)i % m->rec_attn.size()], s);
+      case SPECDEC_KERNEL_ATTENTION: {  // (each round over the layers a pass of its own to the partial words' tags)
+        AttnArgs a = m->rec_attn[(size_t)i % m->rec_attn.size()];
+        a.pass_ahead = (uint32_t)((size_t)i / m->rec_attn.size()) + 1u;
+        return launch_attention(a, s);
+      }
       default: {
         const std::vector<GemmArgs>& v = m->rec_gemm[kind];
         return gemm_rows(dt, v[(size_t)i % v.size()], m->rec_rows[kind], s);
@@ -1110,6 +1114,10 @@ specdec_status specdec_time_kernel(const specdec_model* m, int32_t kind, int32_t
   if (err == hipSuccess) err = hipEventRecord(e0, s);
   for (int i = 1; i <= reps && err == hipSuccess; ++i) err = launch(i);
   if (err == hipSuccess) err = hipEventRecord(e1, s);
+  if (kind == SPECDEC_KERNEL_ATTENTION && m->attn_pass) {  // the next pass starts after the tags used here
+    const hipError_t e = launch_advance_pass(m->attn_pass, (uint32_t)((size_t)reps / m->rec_attn.size()) + 1u, m->n_layers, s);
+    if (err == hipSuccess) err = e;
+  }
   if (err == hipSuccess) err = hipEventSynchronize(e1);
   float ms = 0.f;
   if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);

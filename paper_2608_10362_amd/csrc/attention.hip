@@ -651,7 +651,9 @@ __global__ __launch_bounds__(64 * kMaxPartWaves) void attn_block_kernel(AttnArgs
 // waits for has a lower index (so it was dispatched no later) and stores all its
 // words before it polls itself, so the wait always ends; a bounded poll count
 // turns a broken invariant into a status.  The tag comes from the pass count,
-// which the embedding kernel advances, and the layer.
+// which the embedding kernel advances, and the layer; launches repeated without
+// an embedding (specdec_time_kernel) count passes of their own, so no launch
+// finds its tag in the words of an earlier one.
 // Bound: the key and value stream.  16 sequences of 1024 to 8192 keys (1.26 GB
 // per layer of the 7B shape): 255 us in parts sized for 12 blocks per CU
 // (4.9 TB/s), 218 now (5.8 TB/s); 8 sequences of 513 to 2048: 53 us, 44 now.
@@ -682,7 +684,9 @@ __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArg
     const RowDesc last = a.rows[s * rps + rps - 1];
     return last.valid ? min(n_sub, last.pos / kSubKeys + 1) : n_sub;
   };
-  const uint32_t tag = attention_tag(a.pass[0], (uint32_t)a.n_layers, (uint32_t)a.layer);
+  const uint32_t n_layers = (uint32_t)a.n_layers, pass0 = a.pass[0];
+  const uint32_t pass = a.pass_ahead ? attention_pass_after(pass0, a.pass_ahead, n_layers) : pass0;
+  const uint32_t tag = attention_tag(pass, n_layers, (uint32_t)a.layer);
   const int n0 = lane < B ? subs_of(lane) : 0;  // (the first 64 sequences stay in a register)
   int subs = 0;
   for (int c = 0; c < B; c += kWave) {
@@ -1433,6 +1437,15 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n, v);
+  return hipGetLastError();
+}
+
+__global__ void advance_pass_kernel(uint32_t* pass, uint32_t n, uint32_t n_layers) {
+  *pass = attention_pass_after(*pass, n, n_layers);
+}
+
+hipError_t launch_advance_pass(uint32_t* pass, uint32_t n, int n_layers, hipStream_t s) {
+  hipLaunchKernelGGL(advance_pass_kernel, dim3(1), dim3(1), 0, s, pass, n, (uint32_t)n_layers);
   return hipGetLastError();
 }
 

@@ -189,11 +189,13 @@ struct AttnArgs {
   // head), zero between launches; the last block to count combines.  ll (long
   // contexts and batches): [M, h, ll_parts, hd + 2] tagged words: low half the
   // float (hd O values, then max and sum), high half the launch's tag
-  // (attention_tag of pass[0], which the embedding kernel advances).
+  // (attention_tag of the pass pass_ahead after pass[0]; the embedding kernel
+  // advances pass[0], a launch repeated outside a pass counts on in pass_ahead).
   uint32_t* counters;
   uint64_t* ll;
   int ll_parts, n_layers;
   const uint32_t* pass;
+  uint32_t pass_ahead;
   // Or null: the weights the next launch streams (the O projection's image,
   // next_w_bytes long).  With the in-kernel combine, every block that does not
   // combine reads up to kNextWeightsPerBlock bytes of its share of them after
@@ -209,6 +211,8 @@ size_t attention_counter_count(int n_heads, int n_kv_heads, int max_rows);
 // Flagged partial words (uint64) of the in-kernel combine for max_rows rows.
 size_t attention_ll_words(int n_heads, int head_dim, int max_rows, int n_split_max);
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s);
+// Takes the pass count of a handle n passes on.
+hipError_t launch_advance_pass(uint32_t* pass, uint32_t n, int n_layers, hipStream_t s);
 int attention_chunk(int dtype, int head_dim);  // keys per split of the attention kernel
 int device_compute_units();                    // CUs of the current device (cached)
 hipError_t launch_rope_append(const AttnArgs& a, hipStream_t s);
