@@ -928,7 +928,7 @@ __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArg
           own[HD] = M;
           own[HD + 1] = L;
         }
-      } else if (M != -INFINITY) {
+      } else {  // (every row: scores that are all NaN leave the maximum -inf too, and the combine waits for the words)
         uint64_t* w = a.ll + (((size_t)qrow * H + head) * a.ll_parts + part) * (HD + 2);
 #pragma unroll
         for (int j = 0; j < DPL; ++j)

@@ -13,7 +13,7 @@ from oracle import model as om
 from oracle import sampling
 from oracle.specdec import greedy_decode
 from paper_2608_10362_amd import binding, synth
-from tests.gpu_util import (SOFTMAX_REL_ERR, accept_explained, f32, i32, install_context, log, oracle_caches,
+from tests.gpu_util import (SOFTMAX_REL_ERR, accept_explained, f32, i32, install_context, kv_to_device, log, oracle_caches,
                             torch_cuda, u32_tensor)
 
 pytestmark = pytest.mark.gpu
@@ -418,6 +418,37 @@ def test_bf16_7b_shape_attention_combine_modes_alternate_on_one_handle():
         for ci in (0, 1, 0):
             got = verify(ci)
             assert np.array_equal(got, first[ci]), (rep, ci)
+
+
+def test_bf16_1b_shape_long_context_with_nan_keys():
+    # Scores that are all NaN leave a part's maximum at -inf.  Such a part must
+    # still hand over its words: the pass ends without a status, the sequence's
+    # logits are NaN (its accept then reports them), the other's do not change.
+    torch = torch_cuda()
+    shape, lengths, g = synth.LLAMA_1B, [6000, 6111], 4
+    B, cap = len(lengths), 6144
+    W = synth.make_weights(shape, n_layers=1)
+    dw = binding.DeviceWeights(shape, W)
+    target = binding.Model(dw, 1, max_rows=B * (g + 1), max_ctx=cap)
+    ctx = synth.make_kv_context(shape, 1, lengths, seed=44)
+    kv = binding.KVCache(target, B, cap)
+    install_context(kv, ctx, lengths, 1, shape.dtype)
+    pend = synth.make_prompt(1, shape.vocab, batch=B, seed=45)[:, 0]
+    drafts = i32(synth.make_prompt(g, shape.vocab, batch=B, seed=46))
+    out = []
+    for nan in (False, True):
+        if nan:
+            k = np.array(ctx[0][0]["k"])
+            k[:, 1] = 0x7FC0  # bf16 NaN in every key of one kv head of the first sequence
+            kv.write_context(0, 0, 0, kv_to_device(k, shape.dtype), kv_to_device(ctx[0][0]["v"], shape.dtype))
+        kv.set_state(np.asarray(lengths, np.int32), np.stack([np.zeros(B, np.int32), pend], 1), np.ones(B, np.int32))
+        logits = torch.empty((B, g + 1, shape.vocab), dtype=torch.float32, device="cuda")
+        binding.specdec_verify(target, kv, g, drafts, g, logits)
+        out.append(logits.cpu().numpy())
+        assert kv.read_state()["status"] == 0
+    assert np.isfinite(out[0]).all()
+    assert np.isnan(out[1][0]).all()
+    assert np.array_equal(out[1][1], out[0][1])
 
 
 def test_bf16_7b_shape_long_context_workload_launch_and_accept():
