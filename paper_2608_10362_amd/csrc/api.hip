@@ -40,11 +40,8 @@ struct specdec_model {
   uint16_t* xs_f = nullptr;  // bf16: the stacked attention output (the O projection's x), then SwiGLU output
   float* ypart = nullptr;  // split-K partials (passes of more than 16 rows)
   size_t ypart_floats = 0;
-  uint32_t* attn_pass = nullptr;          // bf16: forward passes run (tags of the attention's partial words)
   uint32_t* attn_cnt = nullptr;           // bf16: the one-round attention combine's arrival counters
-  uint64_t* attn_ll = nullptr;            // bf16: the attention combine's tagged partial words
-  size_t attn_ll_words = 0;
-  mutable bool attn_ready = false;        // set once all three have been zeroed on a stream
+  mutable bool attn_ready = false;        // set once they have been zeroed on a stream
   int chunk, n_split_max;
   // per-layer launches of the last forward pass, for specdec_time_kernel
   // (entry l: layer l; the head and the embedding have one)
@@ -103,7 +100,7 @@ int elem_bytes(int dtype) { return dtype == SPECDEC_BF16 ? 2 : 4; }
 
 // Workspace layout (in order); shared by specdec_workspace_bytes and create.
 struct WsLayout {
-  size_t rows, rope, h, xg, ss, qkv, qr, o_part, ml_part, o, u, logits, samp, xs_d, xs_f, ypart, ctr, cnt, ll, total;
+  size_t rows, rope, h, xg, ss, qkv, qr, o_part, ml_part, o, u, logits, samp, xs_d, xs_f, ypart, cnt, total;
   int ss_parts, chunk, n_split;
   size_t ypart_floats;
 };
@@ -145,9 +142,7 @@ WsLayout ws_layout(const specdec_model_desc* d, int max_rows, int max_ctx) {
                                ? (size_t)kRowsSplitMax * std::min(max_rows, kMaxGemmRows) * d->d_model : 0;
   w.ypart_floats = std::max(rows_part, wide ? tile_ypart_floats(d->d_model) : 0);
   w.ypart = take(w.ypart_floats * 4);
-  w.ctr = take(d->dtype == SPECDEC_BF16 ? 4 : 0);
   w.cnt = take(d->dtype == SPECDEC_BF16 ? attention_counter_count(H, G, max_rows) * 4 : 0);
-  w.ll = take(d->dtype == SPECDEC_BF16 ? attention_ll_words(H, hd, max_rows, w.n_split) * 8 : 0);
   w.total = off;
   return w;
 }
@@ -326,14 +321,10 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   const bool head_stk = q4 && M <= kSkinnyRows;  // (INT4 layers convert float32 x themselves; the bf16 LM head does not)
   ra.xs = stk ? m->xs_d : nullptr;
   ra.stt = stt_d;
-  if (m->attn_pass && !m->attn_ready) {  // (fill kernels: a capturing caller may record them)
-    SD_TRY(launch_fill_u32(m->attn_pass, 1, 0u, s));
+  if (m->attn_cnt && !m->attn_ready) {  // (a fill kernel: a capturing caller may record it)
     SD_TRY(launch_fill_u32(m->attn_cnt, attention_counter_count(H, G, m->max_rows), 0u, s));
-    SD_TRY(launch_fill_u32((uint32_t*)m->attn_ll, 2 * m->attn_ll_words, 0u, s));
     m->attn_ready = true;
   }
-  ra.pass = m->attn_pass;
-  ra.n_layers = m->n_layers;
   {
     Timed t(SPECDEC_KERNEL_EMBED, s);
     SD_TRY(launch_rows_embed(dt, ra, s));
@@ -377,10 +368,6 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   at.status = kv_status(kv);
   at.seq_bound = M / ra.rps > 1;
   at.counters = m->attn_cnt;
-  at.ll = m->attn_ll;
-  at.ll_parts = std::min(kLlMaxParts, m->n_split_max);
-  at.n_layers = m->n_layers;
-  at.pass = m->attn_pass;
   at.xs = stk ? m->xs_f : nullptr;
   at.stt = stt_f;
 
@@ -656,10 +643,7 @@ specdec_status specdec_model_create_fmt(const specdec_model_desc* desc, const sp
   m->xs_f = desc->dtype == SPECDEC_BF16 ? (uint16_t*)(base + L.xs_f) : nullptr;
   m->ypart_floats = L.ypart_floats;
   m->ypart = bf16 && max_rows > kSkinnyRows ? (float*)(base + L.ypart) : nullptr;
-  m->attn_pass = desc->dtype == SPECDEC_BF16 ? (uint32_t*)(base + L.ctr) : nullptr;
   m->attn_cnt = desc->dtype == SPECDEC_BF16 ? (uint32_t*)(base + L.cnt) : nullptr;
-  m->attn_ll = desc->dtype == SPECDEC_BF16 ? (uint64_t*)(base + L.ll) : nullptr;
-  m->attn_ll_words = desc->dtype == SPECDEC_BF16 ? attention_ll_words(desc->n_heads, desc->head_dim, max_rows, L.n_split) : 0;
   m->chunk = L.chunk;
   m->n_split_max = L.n_split;
   *out = m;
@@ -1093,11 +1077,7 @@ specdec_status specdec_time_kernel(const specdec_model* m, int32_t kind, int32_t
     switch (kind) {
       case SPECDEC_KERNEL_EMBED: return launch_rows_embed(dt, m->rec_embed, s);
       case SPECDEC_KERNEL_ROPE_APPEND: return launch_rope_append(m->rec_attn[(size_t)i % m->rec_attn.size()], s);
-      case SPECDEC_KERNEL_ATTENTION: {  // (each round over the layers a pass of its own to the partial words' tags)
-        AttnArgs a = m->rec_attn[(size_t)i % m->rec_attn.size()];
-        a.pass_ahead = (uint32_t)((size_t)i / m->rec_attn.size()) + 1u;
-        return launch_attention(a, s);
-      }
+      case SPECDEC_KERNEL_ATTENTION: return launch_attention(m->rec_attn[(size_t)i % m->rec_attn.size()], s);
       default: {
         const std::vector<GemmArgs>& v = m->rec_gemm[kind];
         return gemm_rows(dt, v[(size_t)i % v.size()], m->rec_rows[kind], s);
@@ -1114,10 +1094,6 @@ specdec_status specdec_time_kernel(const specdec_model* m, int32_t kind, int32_t
   if (err == hipSuccess) err = hipEventRecord(e0, s);
   for (int i = 1; i <= reps && err == hipSuccess; ++i) err = launch(i);
   if (err == hipSuccess) err = hipEventRecord(e1, s);
-  if (kind == SPECDEC_KERNEL_ATTENTION && m->attn_pass) {  // the next pass starts after the tags used here
-    const hipError_t e = launch_advance_pass(m->attn_pass, (uint32_t)((size_t)reps / m->rec_attn.size()) + 1u, m->n_layers, s);
-    if (err == hipSuccess) err = e;
-  }
   if (err == hipSuccess) err = hipEventSynchronize(e1);
   float ms = 0.f;
   if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);

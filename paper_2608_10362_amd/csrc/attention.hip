@@ -221,20 +221,6 @@ __device__ __forceinline__ u32x4 load_kv(const uint16_t* p) {
   else return *(const u32x4*)p;
 }
 
-// Flagged partial words of the in-kernel combine: the float in the low half,
-// the launch's tag in the high half, written and read as single 64-bit
-// agent-scope accesses (a reader sees a whole word, old or new).
-__device__ __forceinline__ void ll_put(uint64_t* p, float v, uint32_t tag) {
-  __hip_atomic_store(p, ((uint64_t)tag << 32) | (uint64_t)__float_as_uint(v), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
-}
-// Cache-policy bits of a load served by the coherent level (sc1), not by a
-// possibly stale line of this XCD's L2.
-constexpr int kCoherentLoad = 16;
-// Polls of the combining block before it gives up (each takes a memory round
-// trip, about a microsecond: a quarter of a second or so in all).
-constexpr int kLlMaxPolls = 1 << 18;
-
 constexpr int kMaxPartWaves = 12;  // 3 waves per SIMD: up to 170 VGPRs per lane
 
 template <int HD>
@@ -645,22 +631,32 @@ __global__ __launch_bounds__(64 * kMaxPartWaves) void attn_block_kernel(AttnArgs
 // a block pays for its start and its merge once or twice instead of per part.
 // Within a unit's segment wave w takes sub-chunks w, w + 4, ... with an online
 // softmax, then the waves merge in LDS.  A unit inside one block is finished
-// there; of a unit that spans blocks, the block that ends it combines, last of
-// all its work: the others store their part as tagged words (ll_put) and go on.
-// It polls until every word read carries this launch's tag.  Every block it
-// waits for has a lower index (so it was dispatched no later) and stores all its
-// words before it polls itself, so the wait always ends; a bounded poll count
-// turns a broken invariant into a status.  The tag comes from the pass count,
-// which the embedding kernel advances, and the layer; launches repeated without
-// an embedding (specdec_time_kernel) count passes of their own, so no launch
-// finds its tag in the words of an earlier one.
+// there; of a unit that spans blocks every block stores its part, and
+// attn_stream_combine_kernel adds the parts.  (Combined by the block that ends
+// the unit, which waits for the other parts, instead: at 16 query rows over 30
+// and more parts that one block reads 300 KB and more, 25 to 35 us per layer;
+// the launch takes 4 to 5.  1.1B shape, 5 rows of one sequence of 8192 keys, two
+// layers: 181 us, 137 now; 7B, 4096 keys: 271, 258; no difference where units
+// are many and few span blocks, 8 or 16 sequences of the 7B shape.)
 // Bound: the key and value stream.  16 sequences of 1024 to 8192 keys (1.26 GB
-// per layer of the 7B shape): 255 us in parts sized for 12 blocks per CU
-// (4.9 TB/s), 218 now (5.8 TB/s); 8 sequences of 513 to 2048: 53 us, 44 now.
+// per layer of the 7B shape): 250 us in parts sized for 12 blocks per CU (5.0
+// TB/s), 216 now with the combine (5.8 TB/s); 8 sequences of 513 to 2048: 54 us,
+// 40 now.
 constexpr int kLoopWaves = 4;
+// Sub-chunks of sequence s: up to its last row's position (the host's count
+// where that row is invalid).
+__device__ __forceinline__ int stream_subs(const AttnArgs& a, int s, int n_sub) {
+  const RowDesc last = a.rows[s * a.rps + a.rps - 1];
+  return last.valid ? min(n_sub, last.pos / kSubKeys + 1) : n_sub;
+}
+// Sub-chunks per block of `nblk` over `tot` in all: a unit spans at most
+// kMaxParts blocks, every wave gets a sub-chunk.
+__device__ __forceinline__ int stream_per_block(int tot, int nblk, int n_sub) {
+  return max(max((tot + nblk - 1) / nblk, (n_sub + kMaxParts - 3) / (kMaxParts - 2)), kLoopWaves);
+}
 __host__ __device__ inline size_t attn_stream_lds(int RS, int HD) {
   const size_t p = (size_t)kLoopWaves * 16 * (kSubKeys + 4), m = (size_t)kLoopWaves * RS * (HD + 6);
-  return ((p > m ? p : m) + (size_t)RS * (HD + 2)) * sizeof(float);
+  return (p > m ? p : m) * sizeof(float);
 }
 template <int HD, bool ONCE>
 __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArgs a, int n_sub, int n_mt) {
@@ -676,17 +672,8 @@ __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArg
   float* const pbuf = smem + (size_t)wave * 16 * (kSubKeys + 4);
   float* const so = smem;                                   // [NW][RS][OS] (P's place, once every wave is past P V)
   float* const sml = smem + (size_t)NW * RSM * OS;          // [NW][RS][2]
-  float* const sown = (float*)((char*)smem + attn_stream_lds(RSM, HD)) - (size_t)RSM * (HD + 2);
 
-  // Sub-chunks of sequence s: up to its last row's position (a batch's own
-  // count where that row is invalid).
-  auto subs_of = [&](int s) {
-    const RowDesc last = a.rows[s * rps + rps - 1];
-    return last.valid ? min(n_sub, last.pos / kSubKeys + 1) : n_sub;
-  };
-  const uint32_t n_layers = (uint32_t)a.n_layers, pass0 = a.pass[0];
-  const uint32_t pass = a.pass_ahead ? attention_pass_after(pass0, a.pass_ahead, n_layers) : pass0;
-  const uint32_t tag = attention_tag(pass, n_layers, (uint32_t)a.layer);
+  auto subs_of = [&](int s) { return stream_subs(a, s, n_sub); };
   const int n0 = lane < B ? subs_of(lane) : 0;  // (the first 64 sequences stay in a register)
   int subs = 0;
   for (int c = 0; c < B; c += kWave) {
@@ -697,8 +684,7 @@ __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArg
   }
   subs = __builtin_amdgcn_readfirstlane(subs);
   const int tot = subs * U, nblk = (int)gridDim.x, blk = (int)blockIdx.x;
-  // (a unit spans at most kLlMaxParts blocks; every wave gets a sub-chunk)
-  const int per = max(max((tot + nblk - 1) / nblk, (n_sub + kLlMaxParts - 3) / (kLlMaxParts - 2)), NW);
+  const int per = stream_per_block(tot, nblk, n_sub);
   int x = blk * per;
   const int hi = min(tot, x + per);
   if (x >= tot) return;
@@ -724,8 +710,6 @@ __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArg
   b = __builtin_amdgcn_readfirstlane(b);
   before = __builtin_amdgcn_readfirstlane(before);
 
-  // the unit this block ends and others began (combined last): part count, its place, its first block
-  int c_parts = 0, c_b = 0, c_u = 0, c_x0 = 0;
   const float scale = 1.0f / sqrtf((float)HD);
 
   while (x < hi) {  // (block-uniform)
@@ -885,7 +869,7 @@ __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArg
       }
     }
     __syncthreads();
-    const bool whole = j0 == 0 && j1 == n_b, ends = j1 == n_b;
+    const bool whole = j0 == 0 && j1 == n_b;
     const int part = blk - x0 / per;
     for (int row = wave; row < RS; row += NW) {  // (wave-uniform) one wave per query row
       const int qc = mt * 16 + row;
@@ -919,31 +903,16 @@ __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArg
 #pragma unroll
         for (int j = 0; j < DPL; ++j)
           if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, valid ? O[j] * inv : 0.f);
-      } else if (ends) {  // (kept in LDS for this block's combine)
-        float* own = sown + (size_t)row * (HD + 2);
+      } else {  // (every row, also one that sees no key here or whose scores are all NaN: the combine weighs them by M)
+        const size_t slot = ((size_t)qrow * H + head) * a.n_split + part;
 #pragma unroll
         for (int j = 0; j < DPL; ++j)
-          if (lane + 64 * j < HD) own[lane + 64 * j] = O[j];
+          if (lane + 64 * j < HD) a.o_part[slot * HD + lane + 64 * j] = O[j];
         if (lane == 0) {
-          own[HD] = M;
-          own[HD + 1] = L;
-        }
-      } else {  // (every row: scores that are all NaN leave the maximum -inf too, and the combine waits for the words)
-        uint64_t* w = a.ll + (((size_t)qrow * H + head) * a.ll_parts + part) * (HD + 2);
-#pragma unroll
-        for (int j = 0; j < DPL; ++j)
-          if (lane + 64 * j < HD) ll_put(w + lane + 64 * j, O[j], tag);
-        if (lane == 0) {
-          ll_put(w + HD, M, tag);
-          ll_put(w + HD + 1, L, tag);
+          a.ml_part[2 * slot] = M;
+          a.ml_part[2 * slot + 1] = L;
         }
       }
-    }
-    if (ends && !whole) {
-      c_parts = part + 1;
-      c_b = b;
-      c_u = u;
-      c_x0 = x0;
     }
     x += j1 - j0;
     if (x == (before + n_b) * U) {
@@ -952,114 +921,72 @@ __global__ __launch_bounds__(64 * kLoopWaves, 2) void attn_stream_kernel(AttnArg
     }
     __syncthreads();  // (the merge buffers are P's again)
   }
+}
 
-  if (c_parts == 0) return;
-  // Combine: one wave per query row.  This block's part (the last) comes from
-  // LDS; the other parts' words are polled until every one read carries the tag
-  // (each write and read is a whole 64-bit word), in batches of PB parts, and
-  // added in part order.
-  const int g = c_u / n_mt, mt = c_u % n_mt, r0 = c_b * rps, RS = min(16, nq - mt * 16), p_first = c_x0 / per;
-  for (int row = wave; row < RS; row += NW) {  // (wave-uniform)
-    const int qc = mt * 16 + row;
-    const int qrow = r0 + qc / group, head = g * group + qc % group;
-    const RowDesc rd = a.rows[qrow];
-    float* o = a.o + ((size_t)qrow * H + head) * HD;
-    if (!rd.valid) {
+// Adds the parts of attn_stream_kernel: one wave per (head, row), lane p = part
+// p.  It finds the unit's place in the line of sub-chunks as the blocks did; a
+// unit that one block held whole is finished already.
+template <int HD>
+__global__ __launch_bounds__(64) void attn_stream_combine_kernel(AttnArgs a, int n_sub, int n_mt, int nblk) {
+  constexpr int DPL = HD >= 64 ? HD / 64 : 1, PB = 16;
+  const int head = blockIdx.x, r = blockIdx.y, lane = threadIdx.x, H = a.n_heads;
+  const int group = H / a.n_kv_heads, U = a.n_kv_heads * n_mt, B = a.M / a.rps, b = r / a.rps;
+  const RowDesc rd = a.rows[r];
+  const int n_b = stream_subs(a, b, n_sub);
+  int subs = 0, before = 0;
+  for (int s = lane; s < B; s += kWave) {
+    const int n = stream_subs(a, s, n_sub);
+    subs += n;
+    before += s < b ? n : 0;
+  }
 #pragma unroll
-      for (int j = 0; j < DPL; ++j)
-        if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, 0.f);
-      continue;
-    }
-    if (rd.pos + 1 > a.max_ctx && lane == 0) set_status(a.status, kStatusKvCapacity);  // the host's bound was wrong
-    // parts whose first sub-chunk holds a key <= pos
-    const int nch = min((c_x0 + rd.pos / kSubKeys) / per - p_first + 1, c_parts);
-    const bool own_row = nch == c_parts;
-    const int npoll = own_row ? c_parts - 1 : nch;  // (>= 1: a unit combined here began in another block)
-    const float* own = sown + (size_t)row * (HD + 2);
-    const uint64_t* w = a.ll + ((size_t)qrow * H + head) * a.ll_parts * (HD + 2);
-    constexpr int PB = 8;
-    // lane p < nch: part p's (max, sum)
-    float mp = -INFINITY, lp = 0.f;
-    if (lane == c_parts - 1 && own_row) {
-      mp = own[HD];
-      lp = own[HD + 1];
-    }
-    float acc[DPL];
-#pragma unroll
-    for (int j = 0; j < DPL; ++j) acc[j] = 0.f;
-    float M = 0.f, wgt = 0.f;
-    bool expired = false;
-    const int pl = min(lane, npoll - 1);  // (clamped: every load below reads a polled slot)
-    for (int p0 = 0; p0 < nch; p0 += PB) {  // (wave-uniform)
-      float ov[PB][DPL];
-      for (int poll = 0;; ++poll) {  // (wave-uniform)
-        // Every load first (branch-free, addresses clamped to polled slots),
-        // then the tag tests and the selection of own and absent parts.
-        uint64_t wm = 0, wl = 0, wo[PB][DPL];
-        if (p0 == 0) {
-          wm = __hip_atomic_load(const_cast<uint64_t*>(w) + (size_t)pl * (HD + 2) + HD, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
-          wl = __hip_atomic_load(const_cast<uint64_t*>(w) + (size_t)pl * (HD + 2) + HD + 1, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
-        }
-#pragma unroll
-        for (int pp = 0; pp < PB; ++pp) {
-          const int pc = min(p0 + pp, npoll - 1);
-#pragma unroll
-          for (int j = 0; j < DPL; ++j)
-            wo[pp][j] = __hip_atomic_load(const_cast<uint64_t*>(w) + (size_t)pc * (HD + 2) + min(lane + 64 * j, HD - 1),
-                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        bool ok = true;
-        if (p0 == 0 && lane < npoll) {
-          ok = (uint32_t)(wm >> 32) == tag && (uint32_t)(wl >> 32) == tag;
-          mp = __uint_as_float((uint32_t)wm);
-          lp = __uint_as_float((uint32_t)wl);
-        }
-#pragma unroll
-        for (int pp = 0; pp < PB; ++pp) {
-          const int p = p0 + pp;
-#pragma unroll
-          for (int j = 0; j < DPL; ++j) {
-            const int dd = lane + 64 * j;
-            const bool polled = p < npoll && dd < HD;
-            ok = ok && (!polled || (uint32_t)(wo[pp][j] >> 32) == tag);
-            ov[pp][j] = polled ? __uint_as_float((uint32_t)wo[pp][j])
-                               : (p < nch && dd < HD ? own[min(dd, HD - 1)] : 0.f);
-          }
-        }
-        if (__all(ok)) break;
-        if (poll >= kLlMaxPolls) {
-          expired = true;
-          break;
-        }
-      }
-      if (expired) break;
-      if (p0 == 0) {
-        M = wave_max(lane < nch ? mp : -INFINITY);
-        wgt = lane < nch ? expf(mp - M) : 0.f;
-      }
-#pragma unroll
-      for (int pp = 0; pp < PB; ++pp) {
-        const float wp = __shfl(wgt, (p0 + pp) & 63, kWave);
-        const float wv = p0 + pp < nch ? wp : 0.f;
-#pragma unroll
-        for (int j = 0; j < DPL; ++j) acc[j] += wv * ov[pp][j];
-      }
-    }
-    if (expired) {  // (a part never arrived: report it, write zeros)
-      if (lane == 0) set_status(a.status, kStatusWaitExpired);
-#pragma unroll
-      for (int j = 0; j < DPL; ++j)
-        if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, 0.f);
-      continue;
-    }
-    const float L = wave_sum(wgt * lp);
-    const float inv = 1.0f / L;
+  for (int o = 32; o > 0; o >>= 1) {
+    subs += __shfl_xor(subs, o, kWave);
+    before += __shfl_xor(before, o, kWave);
+  }
+  const int per = stream_per_block(subs * U, nblk, n_sub);
+  const int u = head / group * n_mt + ((r - b * a.rps) * group + head % group) / 16;
+  const int x0 = before * U + u * n_b, p_first = x0 / per, parts = (x0 + n_b - 1) / per - p_first + 1;
+  if (parts == 1) return;
+  float* o = a.o + ((size_t)r * H + head) * HD;
+  if (!rd.valid) {
 #pragma unroll
     for (int j = 0; j < DPL; ++j)
-      if (lane + 64 * j < HD) put_o(a, o, qrow, head, lane + 64 * j, acc[j] * inv);
+      if (lane + 64 * j < HD) put_o(a, o, r, head, lane + 64 * j, 0.f);
+    return;
   }
+  if (rd.pos + 1 > a.max_ctx && lane == 0) set_status(a.status, kStatusKvCapacity);  // the host's bound was wrong
+  // parts whose first sub-chunk holds a key <= pos
+  const int nch = min((x0 + rd.pos / kSubKeys) / per - p_first + 1, parts);
+  const size_t base = ((size_t)r * H + head) * a.n_split;
+  const int pl = min(lane, nch - 1);
+  const float mp = a.ml_part[2 * (base + pl)], lp = a.ml_part[2 * (base + pl) + 1];
+  float acc[DPL], wgt = 0.f;
+#pragma unroll
+  for (int j = 0; j < DPL; ++j) acc[j] = 0.f;
+  for (int p0 = 0; p0 < nch; p0 += PB) {
+    float ov[PB][DPL];
+#pragma unroll
+    for (int pp = 0; pp < PB; ++pp)
+#pragma unroll
+      for (int j = 0; j < DPL; ++j)
+        ov[pp][j] = a.o_part[(base + min(p0 + pp, nch - 1)) * HD + min(lane + 64 * j, HD - 1)];
+    if (p0 == 0) {
+      const float M = wave_max(lane < nch ? mp : -INFINITY);
+      wgt = lane < nch ? expf(mp - M) : 0.f;
+    }
+#pragma unroll
+    for (int pp = 0; pp < PB; ++pp) {
+      const float w = __shfl(wgt, (p0 + pp) & 63, kWave);
+      const float wv = p0 + pp < nch ? w : 0.f;
+#pragma unroll
+      for (int j = 0; j < DPL; ++j) acc[j] += wv * ov[pp][j];
+    }
+  }
+  const float inv = 1.0f / wave_sum(wgt * lp);
+#pragma unroll
+  for (int j = 0; j < DPL; ++j)
+    if (lane + 64 * j < HD) put_o(a, o, r, head, lane + 64 * j, acc[j] * inv);
 }
 
 // ---------------------------------------------------------------- many query rows (bf16 cache)
@@ -1440,26 +1367,10 @@ hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ void advance_pass_kernel(uint32_t* pass, uint32_t n, uint32_t n_layers) {
-  *pass = attention_pass_after(*pass, n, n_layers);
-}
-
-hipError_t launch_advance_pass(uint32_t* pass, uint32_t n, int n_layers, hipStream_t s) {
-  hipLaunchKernelGGL(advance_pass_kernel, dim3(1), dim3(1), 0, s, pass, n, (uint32_t)n_layers);
-  return hipGetLastError();
-}
-
 size_t attention_counter_count(int n_heads, int n_kv_heads, int max_rows) {
   // sequences x query tiles <= max_rows * group / 16 + max_rows
   const size_t group = (size_t)(n_heads / n_kv_heads);
   return (size_t)n_kv_heads * ((size_t)max_rows * group / 16 + (size_t)max_rows + 1);
-}
-
-size_t attention_ll_words(int n_heads, int head_dim, int max_rows, int n_split_max) {
-  // slots (row, head, part) for up to min(kLlMaxParts, n_split_max) parts: a
-  // launch's parts never outnumber its sub-chunks, ceil(max_ctx / 32)
-  const size_t parts = (size_t)std::min(kLlMaxParts, n_split_max);
-  return (size_t)max_rows * n_heads * parts * (head_dim + 2);
 }
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
@@ -1500,12 +1411,12 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
       }
     } else {
       // Long contexts and batches: the persistent kernel over the sub-chunks themselves.
-      if (!a.ll || !a.pass) return hipErrorInvalidValue;
-      const dim3 sgrid(2 * cus);
+      const dim3 sgrid(2 * cus), sblock(64 * kLoopWaves), cgrid(a.n_heads, a.M);
       const size_t slds = attn_stream_lds(RS, a.head_dim);
-#define SD_STREAM(HDV)                                                                                            \
-  if (n_mt == 1) hipLaunchKernelGGL((attn_stream_kernel<HDV, true>), sgrid, dim3(64 * kLoopWaves), slds, s, a, n_sub, 1); \
-  else hipLaunchKernelGGL((attn_stream_kernel<HDV, false>), sgrid, dim3(64 * kLoopWaves), slds, s, a, n_sub, n_mt);
+#define SD_STREAM(HDV)                                                                                             \
+  if (n_mt == 1) hipLaunchKernelGGL((attn_stream_kernel<HDV, true>), sgrid, sblock, slds, s, a, n_sub, 1);         \
+  else hipLaunchKernelGGL((attn_stream_kernel<HDV, false>), sgrid, sblock, slds, s, a, n_sub, n_mt);               \
+  hipLaunchKernelGGL((attn_stream_combine_kernel<HDV>), cgrid, dim3(64), 0, s, a, n_sub, n_mt, 2 * cus);
       switch (a.head_dim) {
         case 32: SD_STREAM(32) break;
         case 64: SD_STREAM(64) break;
@@ -1521,7 +1432,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
     // In-kernel combine: one part per lane, at most two query rows per wave of
     // the combining block (its rows go one after another); otherwise the
     // separate combine kernel (one wave per row and head).
-    if (n_part > kLlMaxParts || (RS + NW - 1) / NW > 2) ab.counters = nullptr;
+    if (n_part > kMaxParts || (RS + NW - 1) / NW > 2) ab.counters = nullptr;
     const dim3 grid(n_part * n_mt, a.n_kv_heads, B);
     const size_t lds = attn_block_lds(NW, RS, a.head_dim);
 #define SD_ATTN(HDV) hipLaunchKernelGGL((attn_block_kernel<HDV>), grid, dim3(64 * NW), lds, s, ab, S, n_sub, NW);

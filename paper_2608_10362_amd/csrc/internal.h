@@ -6,7 +6,6 @@
 #include <stdint.h>
 
 #include "specdec.h"
-#include "attention_tag.h"
 #include "device_common.h"
 
 namespace specdec {
@@ -158,8 +157,6 @@ struct RowsArgs {
   float* h;               // out [M, d]
   float* xg;              // out [M, d] h * gain
   float* ss;              // out [M] sum of squares of h rows
-  uint32_t* pass;         // or null: the handle's pass count, advanced by one (attention_pass_after)
-  int n_layers;           // of the handle
   uint16_t* xs;           // or null: xg goes out as the stacked operand (put_stacked, stt fragments per k-step) only
   int stt;
 };
@@ -184,18 +181,10 @@ struct AttnArgs {
   int stt;
   int32_t* status;
   int seq_bound;         // 1: bound each sequence's keys by its own last row (batches of several sequences)
-  // bf16 in-kernel combines.  counters (one-round launches; null: a separate
-  // combine kernel adds the parts): one word per (sequence, query tile, kv
-  // head), zero between launches; the last block to count combines.  ll (long
-  // contexts and batches): [M, h, ll_parts, hd + 2] tagged words: low half the
-  // float (hd O values, then max and sum), high half the launch's tag
-  // (attention_tag of the pass pass_ahead after pass[0]; the embedding kernel
-  // advances pass[0], a launch repeated outside a pass counts on in pass_ahead).
+  // The in-kernel combine of one-round bf16 launches (null: a separate combine
+  // kernel adds the parts): one word per (sequence, query tile, kv head), zero
+  // between launches; the last block to count combines.
   uint32_t* counters;
-  uint64_t* ll;
-  int ll_parts, n_layers;
-  const uint32_t* pass;
-  uint32_t pass_ahead;
   // Or null: the weights the next launch streams (the O projection's image,
   // next_w_bytes long).  With the in-kernel combine, every block that does not
   // combine reads up to kNextWeightsPerBlock bytes of its share of them after
@@ -205,14 +194,10 @@ struct AttnArgs {
   uint32_t next_w_bytes;
 };
 constexpr uint32_t kNextWeightsPerBlock = 48u << 10;
-constexpr int kLlMaxParts = 64;  // parts of one head the in-kernel combine takes (one per lane)
+constexpr int kMaxParts = 64;  // parts of one head that the one-round in-kernel and the long-context combine take (one per lane)
 // Counter words a model workspace holds for the one-round in-kernel combine.
 size_t attention_counter_count(int n_heads, int n_kv_heads, int max_rows);
-// Flagged partial words (uint64) of the in-kernel combine for max_rows rows.
-size_t attention_ll_words(int n_heads, int head_dim, int max_rows, int n_split_max);
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s);
-// Takes the pass count of a handle n passes on.
-hipError_t launch_advance_pass(uint32_t* pass, uint32_t n, int n_layers, hipStream_t s);
 int attention_chunk(int dtype, int head_dim);  // keys per split of the attention kernel
 int device_compute_units();                    // CUs of the current device (cached)
 hipError_t launch_rope_append(const AttnArgs& a, hipStream_t s);

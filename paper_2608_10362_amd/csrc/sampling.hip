@@ -160,7 +160,6 @@ __global__ __launch_bounds__(256) void rows_embed_kernel(RowsArgs a) {
   }
   if (first) {
     a.rows[r] = RowDesc{b, pos, tok, valid};
-    if (r == 0 && a.pass) *a.pass = attention_pass_after(*a.pass, 1u, (uint32_t)a.n_layers);
   }
   const ET* e = (const ET*)a.embed + (size_t)tok * a.d_model;
   const ET* gn = (const ET*)a.gain;

@@ -4,6 +4,7 @@ Logits must agree within max-abs 1e-4 (float32 model) / 2e-2 (bf16 model),
 under teacher forcing: both sides get the same weights, resident context and
 drafted tokens.
 """
+import ctypes
 import dataclasses
 
 import numpy as np
@@ -420,10 +421,47 @@ def test_bf16_7b_shape_attention_combine_modes_alternate_on_one_handle():
             assert np.array_equal(got, first[ci]), (rep, ci)
 
 
+def test_bf16_1b_shape_long_context_handles_sharing_a_workspace():
+    # Two handles of 3 layers and 1 over one workspace, their calls one after
+    # another: what a pass leaves there (partial sums of keys split over blocks
+    # among it) must not reach the passes of the other handle.
+    torch = torch_cuda()
+    shape, lengths, g = synth.LLAMA_1B, [6000, 6111], 4
+    B, cap = len(lengths), 6144
+    dw = binding.DeviceWeights(shape, synth.make_weights(shape, n_layers=3))
+    models = [binding.Model(dw, n, max_rows=B * (g + 1), max_ctx=cap) for n in (3, 1)]
+    ctx = synth.make_kv_context(shape, 3, lengths, seed=47)
+    pend = synth.make_prompt(1, shape.vocab, batch=B, seed=48)[:, 0]
+    drafts = i32(synth.make_prompt(g, shape.vocab, batch=B, seed=49))
+    kvs = []
+    for m in models:
+        kvs.append(binding.KVCache(m, B, cap))
+        install_context(kvs[-1], ctx, lengths, m.n_layers, shape.dtype)
+
+    def verify(i):
+        kvs[i].set_state(np.asarray(lengths, np.int32), np.stack([np.zeros(B, np.int32), pend], 1), np.ones(B, np.int32))
+        logits = torch.empty((B, g + 1, shape.vocab), dtype=torch.float32, device="cuda")
+        binding.specdec_verify(models[i], kvs[i], g, drafts, g, logits)
+        assert kvs[i].read_state()["status"] == 0
+        return logits.cpu().numpy()
+
+    alone = [verify(0), verify(1)]
+    ws, h = models[0].workspace, ctypes.c_void_p()
+    w, arrays = dw.c_struct(1)
+    binding._check(binding.lib().specdec_model_create(ctypes.byref(models[1].desc), ctypes.byref(w), 1,
+                                                      dw.packed.data_ptr(), dw.packed.numel(), B * (g + 1), cap,
+                                                      ws.data_ptr(), ws.numel(), ctypes.byref(h)), "specdec_model_create")
+    own, models[1].handle = models[1].handle, h
+    binding.lib().specdec_model_destroy(own)
+    for _ in range(2):
+        for i in [0] + [1] * 9:
+            assert np.array_equal(verify(i), alone[i]), i
+
+
 def test_bf16_1b_shape_long_context_with_nan_keys():
-    # Scores that are all NaN leave a part's maximum at -inf.  Such a part must
-    # still hand over its words: the pass ends without a status, the sequence's
-    # logits are NaN (its accept then reports them), the other's do not change.
+    # Scores that are all NaN leave a part's maximum at -inf: the pass must still
+    # end without a status, the sequence's logits are NaN (its accept then
+    # reports them), the other's do not change.
     torch = torch_cuda()
     shape, lengths, g = synth.LLAMA_1B, [6000, 6111], 4
     B, cap = len(lengths), 6144

@@ -54,50 +54,6 @@ def test_time_kernel_cycles_layers_and_keeps_the_context():
     assert np.array_equal(before, after)
 
 
-def test_time_kernel_tags_every_repeat_of_the_long_context_attention():
-    """The long-context attention hands partial sums from block to block as words
-    that carry the launch's tag (their high half; at the end of the workspace).
-    A repeat that found its own tag in the words of the launch before would not
-    wait for the other blocks: each repeat must leave a newer tag, the next pass
-    a newer one still, and timing must not change that pass's logits."""
-    torch = torch_cuda()
-    shape, n_layers, lengths, g = synth.LLAMA_1B, 2, [6000, 6100], 4
-    B, cap = len(lengths), 6144
-    W = synth.make_weights(shape, n_layers=n_layers)
-    dw = binding.DeviceWeights(shape, W)
-    target = binding.Model(dw, n_layers, max_rows=B * (g + 1), max_ctx=cap)
-    kv = binding.KVCache(target, B, cap)
-    install_context(kv, synth.make_kv_context(shape, n_layers, lengths), lengths, n_layers, shape.dtype)
-    pend = synth.make_prompt(1, shape.vocab, batch=B, seed=41)[:, 0]
-    drafts = i32(synth.make_prompt(g, shape.vocab, batch=B, seed=42))
-    logits = torch.empty((B, g + 1, shape.vocab), dtype=torch.float32, device="cuda")
-    n_words = B * (g + 1) * shape.n_heads * 64 * (shape.head_dim + 2)  # (row, head, part <= 64, hd + 2)
-
-    def verify():
-        kv.set_state(np.asarray(lengths, np.int32), np.stack([np.zeros(B, np.int32), pend], 1), np.ones(B, np.int32))
-        binding.specdec_verify(target, kv, g, drafts, g, logits)
-        assert kv.read_state()["status"] == 0
-        return logits.cpu().numpy()
-
-    def last_tag():
-        pad = (-n_words * 8) % 256
-        words = target.workspace[-(n_words * 8 + pad):].view(torch.int64)[:n_words]
-        return int((words >> 32).max().item())
-
-    before = verify()
-    t0 = last_tag()
-    assert t0 == n_layers + n_layers  # pass 1, last layer
-    for reps in (n_layers, 2 * n_layers + 1):
-        assert binding.specdec_time_kernel(target, "attention", reps=reps) > 0.0
-        t1 = last_tag()
-        log(f"{reps + 1} repeats: last tag {t0} -> {t1}")
-        assert t1 >= t0 + reps  # (a pass's worth of tags per round over the layers)
-        t0 = t1
-    after = verify()
-    assert last_tag() > t0
-    assert np.array_equal(before, after)
-
-
 def test_stream_read_reads_and_writes_nothing():
     """The streaming-read ceiling probe over a buffer whose size is not a whole
     number of its chunks: it runs, and it never writes its sink for real data."""
