@@ -314,13 +314,10 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   // rows which each would convert again.
   const bool q4 = m->wfmt == SPECDEC_WEIGHTS_INT4;
   const bool stk = dt == SPECDEC_BF16 && (!q4 || M > kSkinnyRows);
-  // x of the Q|K|V, gate|up and LM head GEMMs: hi and lo fragments per 16 rows;
-  // of the O and down GEMMs (attention and SwiGLU output): over at most 8 rows
-  // both parts in one.
-  const int stt_d = 2 * ((M + 15) / 16), stt_f = M <= 8 ? 1 : stt_d;
+  const int stt = stacked_fragments(M);
   const bool head_stk = q4 && M <= kSkinnyRows;  // (INT4 layers convert float32 x themselves; the bf16 LM head does not)
   ra.xs = stk ? m->xs_d : nullptr;
-  ra.stt = stt_d;
+  ra.stt = stt;
   if (m->attn_cnt && !m->attn_ready) {  // (a fill kernel: a capturing caller may record it)
     SD_TRY(launch_fill_u32(m->attn_cnt, attention_counter_count(H, G, m->max_rows), 0u, s));
     m->attn_ready = true;
@@ -369,7 +366,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   at.seq_bound = M / ra.rps > 1;
   at.counters = m->attn_cnt;
   at.xs = stk ? m->xs_f : nullptr;
-  at.stt = stt_f;
+  at.stt = stt;
 
   for (int l = 0; l < m->n_layers; ++l) {
     const bool last_kv = kv_only && l + 1 == m->n_layers;
@@ -385,7 +382,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
       q.n_heads = H; q.n_kv_heads = G; q.head_dim = hd;
     }
     if (q4) { q.q4 = 1; q.wscale[0] = m->sq[l]; q.wscale[1] = m->sk[l]; q.wscale[2] = m->sv[l]; }
-    if (stk) { q.xs = m->xs_d; q.stt = stt_d; }
+    if (stk) { q.xs = m->xs_d; q.stt = stt; }
     {
       Timed t(SPECDEC_KERNEL_QKV, s);
       GemmArgs run = q;
@@ -422,7 +419,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
     o.w[0] = m->wo[l]; o.n_seg[0] = d.d_model; o.n_rows = d.d_model; o.kind = EPI_RESID;
     o.out = m->h; o.ldo = d.d_model; o.ss_out = m->ss; o.xg_out = m->xg; o.gain_out = m->ffn_norm[l];
     if (q4) { o.q4 = 1; o.wscale[0] = m->so[l]; }
-    if (stk) { o.xs = m->xs_f; o.stt = stt_f; o.xs_out = m->xs_d; o.stt_out = stt_d; }
+    if (stk) { o.xs = m->xs_f; o.stt = stt; o.xs_out = m->xs_d; o.stt_out = stt; }
     if (!last_kv) {
       Timed t(SPECDEC_KERNEL_O_PROJ, s);
       SD_TRY(gemm_rows(dt, o, M, s));
@@ -436,7 +433,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
     gu.w[0] = m->w_gate[l]; gu.w[1] = m->w_up[l]; gu.n_seg[0] = d.ffn_dim; gu.n_seg[1] = d.ffn_dim;
     gu.n_rows = d.ffn_dim; gu.kind = EPI_SWIGLU; gu.out = m->u; gu.ldo = d.ffn_dim;
     if (q4) { gu.q4 = 1; gu.wscale[0] = m->sg[l]; gu.wscale[1] = m->su[l]; }
-    if (stk) { gu.xs = m->xs_d; gu.stt = stt_d; gu.xs_out = m->xs_f; gu.stt_out = stt_f; }
+    if (stk) { gu.xs = m->xs_d; gu.stt = stt; gu.xs_out = m->xs_f; gu.stt_out = stt; }
     if (!last_kv) {
       Timed t(SPECDEC_KERNEL_GATE_UP, s);
       SD_TRY(gemm_rows(dt, gu, M, s));
@@ -449,8 +446,8 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
     dn.out = m->h; dn.ldo = d.d_model; dn.ss_out = m->ss; dn.xg_out = m->xg;
     dn.gain_out = l + 1 < m->n_layers ? m->attn_norm[l + 1] : m->final_norm;
     if (q4) { dn.q4 = 1; dn.wscale[0] = m->sd[l]; }
-    if (stk) { dn.xs = m->xs_f; dn.stt = stt_f; }
-    if (stk || (head_stk && l + 1 == m->n_layers)) { dn.xs_out = m->xs_d; dn.stt_out = stt_d; }
+    if (stk) { dn.xs = m->xs_f; dn.stt = stt; }
+    if (stk || (head_stk && l + 1 == m->n_layers)) { dn.xs_out = m->xs_d; dn.stt_out = stt; }
     if (!last_kv) {
       Timed t(SPECDEC_KERNEL_DOWN, s);
       SD_TRY(gemm_rows(dt, dn, M, s));
@@ -462,7 +459,7 @@ specdec_status forward(const specdec_model* m, specdec_kv* kv, RowsArgs ra, int 
   hd_.x = m->xg; hd_.ldx = d.d_model; hd_.ss_in = m->ss; hd_.n_ss = n_ss;
   hd_.K = d.d_model; hd_.w[0] = m->lm_head; hd_.n_seg[0] = d.vocab; hd_.n_rows = d.vocab;
   hd_.kind = EPI_STORE; hd_.out = logits; hd_.ldo = d.vocab;
-  if (stk || head_stk) { hd_.xs = m->xs_d; hd_.stt = stt_d; }
+  if (stk || head_stk) { hd_.xs = m->xs_d; hd_.stt = stt; }
   if (!kv_only) {
     Timed t(SPECDEC_KERNEL_LM_HEAD, s);
     SD_TRY(gemm_rows(dt, hd_, M, s));

@@ -46,9 +46,15 @@ __device__ __forceinline__ bf16x8 q4_operand24(uint32_t w) {
 // is fed to the products as the bf16 value 24 + q (q4_operand24), the bias is
 // cancelled by the product of the same x with -24, shared by the unit's tiles,
 // and a group's sum is multiplied by the row's group scale in float32.
-template <int T, int MT, int NW, int UB, int KIND, bool Q4 = false>
+// Over at most 16 rows (MT = 1) the hi and lo parts are summed apart and added
+// once per unit and wave: XF = 1 (at most 8 rows) has both in one fragment, hi
+// in x rows 0-7 and lo in rows 8-15 of one product, XF = 2 in two; the sums are
+// the same either way, so a block of rows equals its rows run one by one.
+template <int T, int MT, int NW, int UB, int KIND, bool Q4, int XF, bool PEEL>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_units, int n_split, int ks_per_split) {
-  constexpr int NTH = 64 * NW, NC = 16 * T, MP = 16 * MT, NF = T * MT, XF = 2 * MT;
+  constexpr int NC = 16 * T, MP = 16 * MT;
+  constexpr int MA = MT == 1 ? XF : MT;  // accumulator tiles per weight tile
+  static_assert(XF == 2 * MT || (MT == 1 && XF == 1), "fragments of x per k-step");
   constexpr bool SCALE = KIND != EPI_RESID, SWIGLU = KIND == EPI_SWIGLU;
   // fragments per reduction round (a SwiGLU round holds whole gate / up pairs)
   constexpr int RMAX = 128 / NW;
@@ -66,9 +72,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
   const int my_units = (n_units - u0 + us - 1) / us;
   const int total = my_units * nbat;
 
-  floatx4 acc[MT][T];
+  floatx4 acc[MA][T];
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+  for (int mt = 0; mt < MA; ++mt)
 #pragma unroll
     for (int t = 0; t < T; ++t) acc[mt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
   constexpr int WB = Q4 ? 1 : UB;  // weight pieces per tile and batch
@@ -76,7 +82,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
   u32x2 sA[Q4 ? T : 1], sB[Q4 ? T : 1];  // Q4: bf16 scales of the lane's four weight rows
 
   // (the lanes of rows past M read nothing and hold zeros)
-  const uint32_t xlast = (uint32_t)(16 * (MT - 1) + (lane & 15) >= M) << 31;
+  const uint32_t xlast = (uint32_t)(16 * (MT - 1) + (lane & (XF == 1 ? 7 : 15)) >= M) << 31;
   const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.xs, (uint32_t)KS * XF * 1024u);
   int lu = u0, lb = 0;  // load cursor: unit, batch
   auto load = [&](u32x4 (&wv)[WB][T], u32x4 (&xv)[UB][XF], u32x2 (&sv)[Q4 ? T : 1]) {
@@ -167,13 +173,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
 #pragma unroll
       for (int u = 0; u < UB; ++u)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < XF / MA; ++h)
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
+          for (int mt = 0; mt < MA; ++mt)
 #pragma unroll
             for (int t = 0; t < T; ++t)
               acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv[u][t]),
-                                                                   __builtin_bit_cast(bf16x8, xv[u][2 * mt + h]),
+                                                                   __builtin_bit_cast(bf16x8, xv[u][XF / MA * mt + h]),
                                                                    acc[mt][t], 0, 0, 0);
     }
   };
@@ -207,6 +213,15 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
     }
   };
   auto finish = [&](int unit) {
+    if constexpr (MT == 1) {  // hi + lo (XF = 1: of row m in lanes of rows m and 8 + m)
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        if constexpr (XF == 2) acc[0][t] += acc[1][t];
+        else
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[0][t][r] += __shfl_xor(acc[0][t][r], 8, kWave);
+      }
+    }
 #pragma unroll
     for (int m0 = 0; m0 < MT; m0 += RT) {
 #pragma unroll
@@ -233,7 +248,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
       __syncthreads();
     }
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MA; ++mt)
 #pragma unroll
       for (int t = 0; t < T; ++t) acc[mt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
   };
@@ -255,7 +270,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
       }
   }
   load(wA, xA, sA);
-  constexpr bool PEEL = MT > 1 || T == 3 || T == 6;
   if (PEEL || total > 1) load(wB, xB, sB);  // (PEEL, past the last batch: weights out of range)
   if constexpr (SCALE) {
     // s_m = 1/sqrt(sum_p ss[p][m] / K + eps): partial p in lane p % 64, in p order, fixed shuffle tree
@@ -320,21 +334,29 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
   }
 }
 
-template <int T, int MT, int NW, int UB, int KIND, bool Q4>
+template <int T, int MT, int NW, int UB, int KIND, bool Q4, int XF, bool PEEL>
 void launch_mt(const GemmArgs& a, int n_split, int per_split, hipStream_t s) {
   constexpr int NU = KIND == EPI_SWIGLU ? 8 * T : 16 * T;  // output columns per unit
   const int units = (a.n_rows + NU - 1) / NU;
   const int grid = std::min(units, std::max(1, device_compute_units() / n_split)) * n_split;
-  hipLaunchKernelGGL((gemm_bf16_rows<T, MT, NW, UB, KIND, Q4>), dim3(grid), dim3(64 * NW), 0, s, a, units, n_split,
-                     per_split);
+  hipLaunchKernelGGL((gemm_bf16_rows<T, MT, NW, UB, KIND, Q4, XF, PEEL>), dim3(grid), dim3(64 * NW), 0, s, a, units,
+                     n_split, per_split);
 }
-template <int T, int NW, int UB, int KIND, bool Q4 = false, bool MT1 = false>
+// 17 to 64 rows.
+template <int T, int NW, int UB, int KIND, bool Q4 = false>
 void launch_t(const GemmArgs& a, int n_split, int per_split, hipStream_t s) {
   const int MT = (a.M + 15) / 16;
-  if constexpr (MT1) launch_mt<T, 1, NW, UB, KIND, Q4>(a, n_split, per_split, s);
-  else if (MT == 2) launch_mt<T, 2, NW, UB, KIND, Q4>(a, n_split, per_split, s);
-  else if (MT == 3) launch_mt<T, 3, NW, UB, KIND, Q4>(a, n_split, per_split, s);
-  else launch_mt<T, 4, NW, UB, KIND, Q4>(a, n_split, per_split, s);
+  if (MT == 2) launch_mt<T, 2, NW, UB, KIND, Q4, 4, true>(a, n_split, per_split, s);
+  else if (MT == 3) launch_mt<T, 3, NW, UB, KIND, Q4, 6, true>(a, n_split, per_split, s);
+  else launch_mt<T, 4, NW, UB, KIND, Q4, 8, true>(a, n_split, per_split, s);
+}
+// At most 16 rows, whole K.
+template <int T, int NW, int UB, int KIND>
+void launch_t1(const GemmArgs& a, hipStream_t s) {
+  constexpr bool PEEL = T == 3 || T == 6;
+  const int KS = a.K / 32;
+  if (a.M <= 8) launch_mt<T, 1, NW, UB, KIND, false, 1, PEEL>(a, 1, KS, s);
+  else launch_mt<T, 1, NW, UB, KIND, false, 2, PEEL>(a, 1, KS, s);
 }
 
 // Rounds of the persistent grid that units of T tiles take, in tiles (plus
@@ -345,10 +367,13 @@ int unit_cost(int n_tiles, int T) {
 }
 
 // Passes of at most 16 rows, bf16 weights: Q|K|V, gate|up and the LM head (the
-// residual GEMMs run gemm_bf16_mfma).  The unit sizes do not depend on the row
-// count, so a verify block equals its rows run one by one bit for bit.  A row
-// tile costs one register set here, so units hold two to four k-steps per
-// buffer.
+// residual GEMMs run gemm_bf16_mfma).  Neither the waves nor the unit sizes
+// depend on the row count, so a verify block equals its rows run one by one bit
+// for bit.  A row tile costs one register set here, so units hold two to four
+// k-steps per buffer (one or four more over at most 8 rows: 2994 and 3100 us
+// instead of 2973 for the 7B verify of 5 rows).  Over at most 8 rows x comes in
+// one fragment per k-step: a load takes its slot in the texture unit whether its
+// lanes are in range or not (7B LM head over 5 rows 42.6 us in two, 42.1 in one).
 hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
   const int KS = a.K / 32, tiles = a.n_rows / 16;
   if (a.q4) return hipErrorInvalidValue;
@@ -356,19 +381,19 @@ hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
     case EPI_STORE:
       // (a wave keeps at least 16 k-steps of a unit: fewer waves where K is
       // short; K = 2048, 32000 rows: 22.2 us on 4 waves, 27.7 on 8)
-      if (KS >= 128) launch_t<4, 8, 2, EPI_STORE, false, true>(a, 1, KS, s);
-      else launch_t<4, 4, 4, EPI_STORE, false, true>(a, 1, KS, s);
+      if (KS >= 128) launch_t1<4, 8, 2, EPI_STORE>(a, s);
+      else launch_t1<4, 4, 4, EPI_STORE>(a, s);
       break;
     case EPI_QKV: {
       const int c1 = unit_cost(tiles, 1), c2 = unit_cost(tiles, 2), c3 = unit_cost(tiles, 3);
-      if (c3 <= c2 && c3 <= c1) launch_t<3, 8, 2, EPI_QKV, false, true>(a, 1, KS, s);
-      else if (c2 <= c1) launch_t<2, 8, 4, EPI_QKV, false, true>(a, 1, KS, s);
-      else launch_t<1, 8, 4, EPI_QKV, false, true>(a, 1, KS, s);
+      if (c3 <= c2 && c3 <= c1) launch_t1<3, 8, 2, EPI_QKV>(a, s);
+      else if (c2 <= c1) launch_t1<2, 8, 4, EPI_QKV>(a, s);
+      else launch_t1<1, 8, 4, EPI_QKV>(a, s);
       break;
     }
     case EPI_SWIGLU:
-      if (unit_cost(2 * tiles, 6) <= unit_cost(2 * tiles, 4)) launch_t<6, 8, 2, EPI_SWIGLU, false, true>(a, 1, KS, s);
-      else launch_t<4, 8, 2, EPI_SWIGLU, false, true>(a, 1, KS, s);
+      if (unit_cost(2 * tiles, 6) <= unit_cost(2 * tiles, 4)) launch_t1<6, 8, 2, EPI_SWIGLU>(a, s);
+      else launch_t1<4, 8, 2, EPI_SWIGLU>(a, s);
       break;
     default: return hipErrorInvalidValue;
   }
@@ -412,7 +437,7 @@ hipError_t launch_q4(const GemmArgs& a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
-  if (a.M <= 0 || a.M > kMaxGemmRows || !a.xs || a.stt != 2 * ((a.M + 15) / 16) || a.K % 32 || a.n_rows % 16)
+  if (a.M <= 0 || a.M > kMaxGemmRows || !a.xs || a.stt != stacked_fragments(a.M) || a.K % 32 || a.n_rows % 16)
     return hipErrorInvalidValue;
   if (a.kind == EPI_QKV && (a.kv.dtype != SPECDEC_BF16 || a.head_dim % 16 || a.n_seg[0] % a.head_dim ||
                             a.n_seg[1] % a.head_dim))

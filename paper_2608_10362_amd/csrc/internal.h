@@ -59,6 +59,8 @@ template <> struct KvIndex<uint16_t> {
 enum EpiKind { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
 constexpr int kMaxGemmRows = 64;  // rows of x per launch of the skinny kernels (callers split larger M)
 constexpr int kSkinnyRows = 16;   // passes of more rows (to kMaxGemmRows) run launch_gemm_rows throughout
+// 1 KB fragments per k-step of the stacked operand of a pass of M rows (put_stacked).
+constexpr int stacked_fragments(int M) { return M <= 8 ? 1 : 2 * ((M + 15) / 16); }
 constexpr int kRowsSplitMax = 8;  // K splits of its residual GEMMs (partials in ypart: kRowsSplitMax * M * n_rows)
 // Passes of more than kMaxGemmRows bf16 rows run launch_gemm_tile in launches
 // of up to kTileLaunchRows rows; GEMMs that split K over the grid there need

@@ -5,8 +5,8 @@ and at the 7B widths that take the large units."""
 import numpy as np
 import pytest
 
-from paper_2608_10362_amd import synth
-from tests.gpu_util import log
+from paper_2608_10362_amd import binding, synth
+from tests.gpu_util import i32, install_context, log, torch_cuda
 from tests.test_gpu_int4 import _int4_case
 from tests.test_gpu_model import _bf16_case, test_bf16_prefill_in_large_chunks as _prefill_case
 
@@ -37,6 +37,34 @@ def test_odd_shape_rows(B, g):
 @pytest.mark.parametrize("B,g", [(1, 0), (1, 7), (3, 2), (4, 3), (5, 3), (5, 7), (7, 7)])
 def test_uneven_k_rows(B, g):
     _rows_case(UNEVEN, 1, [1 + (37 * b) % 90 for b in range(B)], g, seed=B)
+
+
+@pytest.mark.parametrize("shape,B,g", [(UNEVEN, 3, 3), (UNEVEN, 5, 2), (synth.LLAMA_1B, 3, 2), (synth.LLAMA_1B, 2, 7)])
+def test_rows_equal_their_sequences_alone(shape, B, g):
+    """9 to 16 rows (two fragments of x per k-step) against each sequence in a
+    pass of its own (at most 8 rows, one fragment): the same logits bit for bit.
+    Contexts of one 32-key sub-chunk, so the attention is cut the same way."""
+    torch = torch_cuda()
+    lengths = [7 + 5 * b for b in range(B)]
+    dw = binding.DeviceWeights(shape, synth.make_weights(shape, n_layers=1))
+    ctx = synth.make_kv_context(shape, 1, lengths, seed=70)
+    pend = synth.make_prompt(1, shape.vocab, batch=B, seed=71)[:, 0]
+    drafts = synth.make_prompt(g, shape.vocab, batch=B, seed=72)
+
+    def verify(seqs):
+        n = len(seqs)
+        m = binding.Model(dw, 1, max_rows=n * (g + 1), max_ctx=64)
+        kv = binding.KVCache(m, n, 64)
+        install_context(kv, [[ctx[0][b] for b in seqs]], [lengths[b] for b in seqs], 1, shape.dtype)
+        kv.set_state([lengths[b] for b in seqs], [[0, int(pend[b])] for b in seqs], [1] * n)
+        logits = torch.empty((n, g + 1, shape.vocab), dtype=torch.float32, device="cuda")
+        binding.specdec_verify(m, kv, g, i32(drafts[seqs]), g, logits)
+        assert kv.read_state()["status"] == 0
+        return logits.cpu().numpy()
+
+    block = verify(list(range(B)))
+    for b in range(B):
+        assert np.array_equal(verify([b])[0], block[b]), b
 
 
 # (the tile kernel: more than 64 rows, row tiles of 96, 128 and 256 with remainders, launches of 1024 rows)
