@@ -294,9 +294,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
   // Refills without a branch, the last batches peeled off (PEEL): with a branch
   // around a refill the compiler waits for both buffers before the first
   // product of either (40 rows, 7B: Q|K|V 28.0 -> 26.8 us, O and down 33.8 ->
-  // 32.0 together, LM head 57 -> 50; 5 rows: Q|K|V 18.5 -> 18.0).  Not in the
-  // units of 1, 2 or 4 tiles over at most 16 rows: their k loops are a few
-  // batches (K = 2048), and the longer code costs more (1.1B draft 804 -> 808).
+  // 32.0 together, LM head 57 -> 50; at most 16 rows: launch_t1).
   int cu = u0, cb = 0, left = total;  // compute cursor, batches left
   auto done = [&]() {
     if (++cb == nbat) { finish(cu); cb = 0; cu += us; }
@@ -350,13 +348,22 @@ void launch_t(const GemmArgs& a, int n_split, int per_split, hipStream_t s) {
   else if (MT == 3) launch_mt<T, 3, NW, UB, KIND, Q4, 6, true>(a, n_split, per_split, s);
   else launch_mt<T, 4, NW, UB, KIND, Q4, 8, true>(a, n_split, per_split, s);
 }
-// At most 16 rows, whole K.
+// At most 16 rows, whole K.  Refills without a branch (PEEL) from four batches
+// per unit and wave: 7B verify of 5 rows 2973 us (8 batches in all three GEMMs;
+// 3004 with the branch everywhere), 1.1B LM head over 16 rows 22.5 (4 batches;
+// 23.2); the 2 batches of the 1.1B Q|K|V units gain nothing from the longer code
+// (draft of four slots 799 us, 801 with it).
 template <int T, int NW, int UB, int KIND>
 void launch_t1(const GemmArgs& a, hipStream_t s) {
-  constexpr bool PEEL = T == 3 || T == 6;
   const int KS = a.K / 32;
-  if (a.M <= 8) launch_mt<T, 1, NW, UB, KIND, false, 1, PEEL>(a, 1, KS, s);
-  else launch_mt<T, 1, NW, UB, KIND, false, 2, PEEL>(a, 1, KS, s);
+  const bool peel = (KS + NW * UB - 1) / (NW * UB) >= 4;
+  if (a.M <= 8) {
+    if (peel) launch_mt<T, 1, NW, UB, KIND, false, 1, true>(a, 1, KS, s);
+    else launch_mt<T, 1, NW, UB, KIND, false, 1, false>(a, 1, KS, s);
+  } else {
+    if (peel) launch_mt<T, 1, NW, UB, KIND, false, 2, true>(a, 1, KS, s);
+    else launch_mt<T, 1, NW, UB, KIND, false, 2, false>(a, 1, KS, s);
+  }
 }
 
 // Rounds of the persistent grid that units of T tiles take, in tiles (plus
