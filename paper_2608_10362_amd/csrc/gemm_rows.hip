@@ -29,6 +29,11 @@ __device__ __forceinline__ bf16x8 q4_operand24(uint32_t w) {
   return __builtin_bit_cast(bf16x8, v);
 }
 
+// The value of lane ^ 8 (a rotation by 8 within each row of 16 lanes; no LDS round trip).
+__device__ __forceinline__ float row_half_swap(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, false));
+}
+
 // Block = NW waves, a work unit = T tiles of 16 weight rows over a range of
 // k-steps; the unit's k-steps are dealt out to the waves (wave w: w, w + NW,
 // ...) and every wave holds the whole unit's T x MT accumulator tiles in
@@ -219,7 +224,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
         if constexpr (XF == 2) acc[0][t] += acc[1][t];
         else
 #pragma unroll
-          for (int r = 0; r < 4; ++r) acc[0][t][r] += __shfl_xor(acc[0][t][r], 8, kWave);
+          for (int r = 0; r < 4; ++r) acc[0][t][r] += row_half_swap(acc[0][t][r]);
       }
     }
 #pragma unroll
@@ -348,18 +353,19 @@ void launch_t(const GemmArgs& a, int n_split, int per_split, hipStream_t s) {
   else if (MT == 3) launch_mt<T, 3, NW, UB, KIND, Q4, 6, true>(a, n_split, per_split, s);
   else launch_mt<T, 4, NW, UB, KIND, Q4, 8, true>(a, n_split, per_split, s);
 }
-// At most 16 rows, whole K.  Refills without a branch (PEEL) from four batches
-// per unit and wave: 7B verify of 5 rows 2973 us (8 batches in all three GEMMs;
-// 3004 with the branch everywhere), 1.1B LM head over 16 rows 22.5 (4 batches;
-// 23.2); the 2 batches of the 1.1B Q|K|V units gain nothing from the longer code
-// (draft of four slots 799 us, 801 with it).
-template <int T, int NW, int UB, int KIND>
+// At most 16 rows, whole K; UB1: k-steps per buffer over at most 8 rows.
+// Refills without a branch (PEEL) from four batches per unit and wave: 7B verify
+// of 5 rows 2973 us (8 batches in all three GEMMs; 3004 with the branch
+// everywhere), 1.1B LM head over 16 rows 22.5 (4 batches; 23.2); the 2 batches
+// of the 1.1B Q|K|V units gain nothing from the longer code (draft of four slots
+// 799 us, 801 with it).
+template <int T, int NW, int UB, int KIND, int UB1 = UB>
 void launch_t1(const GemmArgs& a, hipStream_t s) {
-  const int KS = a.K / 32;
-  const bool peel = (KS + NW * UB - 1) / (NW * UB) >= 4;
+  const int KS = a.K / 32, per_batch = NW * (a.M <= 8 ? UB1 : UB);
+  const bool peel = (KS + per_batch - 1) / per_batch >= 4;
   if (a.M <= 8) {
-    if (peel) launch_mt<T, 1, NW, UB, KIND, false, 1, true>(a, 1, KS, s);
-    else launch_mt<T, 1, NW, UB, KIND, false, 1, false>(a, 1, KS, s);
+    if (peel) launch_mt<T, 1, NW, UB1, KIND, false, 1, true>(a, 1, KS, s);
+    else launch_mt<T, 1, NW, UB1, KIND, false, 1, false>(a, 1, KS, s);
   } else {
     if (peel) launch_mt<T, 1, NW, UB, KIND, false, 2, true>(a, 1, KS, s);
     else launch_mt<T, 1, NW, UB, KIND, false, 2, false>(a, 1, KS, s);
@@ -377,10 +383,14 @@ int unit_cost(int n_tiles, int T) {
 // residual GEMMs run gemm_bf16_mfma).  Neither the waves nor the unit sizes
 // depend on the row count, so a verify block equals its rows run one by one bit
 // for bit.  A row tile costs one register set here, so units hold two to four
-// k-steps per buffer (one or four more over at most 8 rows: 2994 and 3100 us
-// instead of 2973 for the 7B verify of 5 rows).  Over at most 8 rows x comes in
-// one fragment per k-step: a load takes its slot in the texture unit whether its
-// lanes are in range or not (7B LM head over 5 rows 42.6 us in two, 42.1 in one).
+// k-steps per buffer (over at most 8 rows one or two to four more: 2994 and 3100
+// us instead of 2973 for the 7B verify of 5 rows; half in Q|K|V or gate|up: 2973,
+// 2982).  Over at most 8 rows x comes in one fragment per k-step: a load takes its
+// slot in the texture unit whether its lanes are in range or not.  The 7B LM head
+// over 5 rows, among the other launches of a pass: 45.5 us with two fragments,
+// 44.5 to 45 with one, 44.0 to 44.8 in buffers of one k-step (43.6 on the
+// residual GEMMs' kernel, x held in LDS, but 68 instead of 45 over 9 to 16 rows,
+// and the two would add in different orders).
 hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
   const int KS = a.K / 32, tiles = a.n_rows / 16;
   if (a.q4) return hipErrorInvalidValue;
@@ -388,7 +398,7 @@ hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
     case EPI_STORE:
       // (a wave keeps at least 16 k-steps of a unit: fewer waves where K is
       // short; K = 2048, 32000 rows: 22.2 us on 4 waves, 27.7 on 8)
-      if (KS >= 128) launch_t1<4, 8, 2, EPI_STORE>(a, s);
+      if (KS >= 128) launch_t1<4, 8, 2, EPI_STORE, 1>(a, s);
       else launch_t1<4, 4, 4, EPI_STORE>(a, s);
       break;
     case EPI_QKV: {
