@@ -123,16 +123,6 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
   return v;
 }
-// (value, index) max with the lowest index on ties
-__device__ __forceinline__ void wave_argmax(float& v, int& i) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    float ov = __shfl_xor(v, o, kWave);
-    int oi = __shfl_xor(i, o, kWave);
-    if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
-  }
-}
-
 // Block-wide sum / max of float (blockDim.x a multiple of 64, <= 1024).
 // `red` is __shared__ float[16]; the result is returned to every thread.
 __device__ __forceinline__ float block_sum(float v, float* red) {
@@ -154,16 +144,6 @@ __device__ __forceinline__ float block_max(float v, float* red) {
   float t = red[0];
   for (int i = 1; i < nw; ++i) t = fmaxf(t, red[i]);
   return t;
-}
-__device__ __forceinline__ void block_argmax(float& v, int& idx, float* redv, int* redi) {
-  wave_argmax(v, idx);
-  int w = threadIdx.x / kWave, l = threadIdx.x % kWave, nw = blockDim.x / kWave;
-  __syncthreads();
-  if (l == 0) { redv[w] = v; redi[w] = idx; }
-  __syncthreads();
-  v = redv[0]; idx = redi[0];
-  for (int i = 1; i < nw; ++i)
-    if (redv[i] > v || (redv[i] == v && redi[i] < idx)) { v = redv[i]; idx = redi[i]; }
 }
 
 // ------------------------------------------------------------------ row descriptors

@@ -31,29 +31,8 @@ __device__ __forceinline__ void load_lds16(uint32_t dst, uint32_t off, __amdgpu_
                : "memory", "m0");
 }
 
-// Base of the packed 16-row tile `t` (t < NC/16) of block `blk`.  Packed
-// matrices are sequences of 16-row tiles of ceil(K/32) 1 KB fragments.
-__device__ __forceinline__ const uint16_t* weight_tile(const GemmArgs& a, int kind, int blk, int NC, int t,
-                                                       int KS, bool& ok) {
-  int seg, n;
-  if (kind == EPI_SWIGLU) {
-    const int H = NC / 2;
-    seg = 16 * t >= H;
-    n = blk * H + 16 * t - seg * H;
-    ok = n < a.n_rows;
-    if (!ok) n = 0;
-  } else {
-    n = blk * NC + 16 * t;
-    ok = n < a.n_rows;
-    if (!ok) n = 0;
-    const int b1 = a.n_seg[0], b2 = b1 + a.n_seg[1];
-    seg = n < b1 ? 0 : (n < b2 ? 1 : 2);
-    n -= seg == 0 ? 0 : (seg == 1 ? b1 : b2);
-  }
-  return (const uint16_t*)a.w[seg] + (size_t)(n / 16) * KS * 512;
-}
-
-// Segment and local row of row tile t of block blk (as weight_tile).
+// Segment and local row of row tile t (t < NC/16) of block blk.  A SwiGLU block
+// pairs NC/2 gate rows (segment 0) with the up rows of the same columns (1).
 __device__ __forceinline__ void tile_segment(const GemmArgs& a, int kind, int blk, int NC, int t, int& seg, int& n,
                                              bool& ok) {
   if (kind == EPI_SWIGLU) {
@@ -70,6 +49,14 @@ __device__ __forceinline__ void tile_segment(const GemmArgs& a, int kind, int bl
     seg = n < b1 ? 0 : (n < b2 ? 1 : 2);
     n -= seg == 0 ? 0 : (seg == 1 ? b1 : b2);
   }
+}
+// Base of that tile in the packed bf16 image: sequences of 16-row tiles of
+// ceil(K/32) 1 KB fragments.
+__device__ __forceinline__ const uint16_t* weight_tile(const GemmArgs& a, int kind, int blk, int NC, int t,
+                                                       int KS, bool& ok) {
+  int seg, n;
+  tile_segment(a, kind, blk, NC, t, seg, n, ok);
+  return (const uint16_t*)a.w[seg] + (size_t)(n / 16) * KS * 512;
 }
 
 // Four consecutive columns n .. n+3 (n % 4 == 0) of row m of the Q|K|V

@@ -345,13 +345,13 @@ void launch_mt(const GemmArgs& a, int n_split, int per_split, hipStream_t s) {
   hipLaunchKernelGGL((gemm_bf16_rows<T, MT, NW, UB, KIND, Q4, XF, PEEL>), dim3(grid), dim3(64 * NW), 0, s, a, units,
                      n_split, per_split);
 }
-// 17 to 64 rows.
-template <int T, int NW, int UB, int KIND, bool Q4 = false>
+// 17 to 64 rows (to 16 MT_MAX).
+template <int T, int NW, int UB, int KIND, bool Q4 = false, int MT_MAX = 4>
 void launch_t(const GemmArgs& a, int n_split, int per_split, hipStream_t s) {
   const int MT = (a.M + 15) / 16;
   if (MT == 2) launch_mt<T, 2, NW, UB, KIND, Q4, 4, true>(a, n_split, per_split, s);
   else if (MT == 3) launch_mt<T, 3, NW, UB, KIND, Q4, 6, true>(a, n_split, per_split, s);
-  else launch_mt<T, 4, NW, UB, KIND, Q4, 8, true>(a, n_split, per_split, s);
+  else if constexpr (MT_MAX == 4) launch_mt<T, 4, NW, UB, KIND, Q4, 8, true>(a, n_split, per_split, s);
 }
 // At most 16 rows, whole K; UB1: k-steps per buffer over at most 8 rows.
 // Refills without a branch (PEEL) from four batches per unit and wave: 7B verify
@@ -430,7 +430,7 @@ hipError_t launch_q4(const GemmArgs& a, hipStream_t s) {
     case EPI_SWIGLU:
       // (6 tiles over more than 48 rows spill: 101 us against 65 for the 7B shape over 64 rows)
       if (a.M <= 48 && unit_cost(2 * tiles, 6) <= unit_cost(2 * tiles, 4))
-        launch_t<6, 4, 4, EPI_SWIGLU, true>(a, 1, KG, s);
+        launch_t<6, 4, 4, EPI_SWIGLU, true, 3>(a, 1, KG, s);
       else launch_t<4, 4, 4, EPI_SWIGLU, true>(a, 1, KG, s);
       break;
     case EPI_RESID: {

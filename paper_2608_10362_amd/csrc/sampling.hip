@@ -690,8 +690,7 @@ hipError_t launch_rows_embed(int dtype, const RowsArgs& a, hipStream_t s) {
 
 size_t sampling_scratch_bytes(int B, int rows, int V) {
   const int NC = n_chunks(V);
-  return align256(sizeof(StatPart) * (size_t)B * rows * NC) + align256(sizeof(DrawPart) * (size_t)B * NC) +
-         align256(sizeof(uint32_t) * (size_t)B);
+  return align256(sizeof(StatPart) * (size_t)B * rows * NC) + align256(sizeof(DrawPart) * (size_t)B * NC);
 }
 
 // Two launches: the chunk statistics, then decide-and-draw.
