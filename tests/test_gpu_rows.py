@@ -89,6 +89,49 @@ def test_int4_7b_width_rows(B, g):
     _int4_case(synth.LLAMA_7B, 1, [40 + 13 * b for b in range(B)], g, seed=B)
 
 
+# The long-context attention (more 32-key sub-chunks times (sequence, kv head, 16-query tile) units than 12 per CU): 32-dim
+# heads with one and with two query tiles per unit, more sequences than a wave has lanes, few units over many blocks (one
+# sequence: 2 units of 1600 sub-chunks, 62 parts) and units that end at, before and after a block's border
+@pytest.mark.parametrize("B,g,lo,hi", [(130, 3, 340, 460), (97, 7, 300, 420), (70, 0, 700, 1100), (1, 4, 51100, 51100),
+                                       (3, 7, 8000, 11000)])
+def test_odd_shape_long_contexts(B, g, lo, hi):
+    lengths = [lo + (hi - lo) * ((7 * b + 3) % B) // max(B - 1, 1) for b in range(B)]
+    n_mt, cus = -(-(g + 1) * 3 // 16), torch_cuda().cuda.get_device_properties(0).multi_processor_count
+    assert -(-(max(lengths) + g + 1) // 32) * B * 2 * n_mt > 12 * cus  # (the rule of the dispatch)
+    _rows_case(ODD, 1, lengths, g, seed=B)
+
+
+def test_long_contexts_with_an_invalid_last_row():
+    """A drafted token out of range in the last row of some sequences: their keys
+    are counted by the pass's bound then.  The status says so; all other rows
+    keep their logits (another cut into blocks: to float32 rounding)."""
+    torch = torch_cuda()
+    B, g, bad = 130, 3, (0, 63, 64, 101, 129)
+    lengths = [340 + (37 * b) % 120 for b in range(B)]
+    cap = 512
+    dw = binding.DeviceWeights(ODD, synth.make_weights(ODD, n_layers=1))
+    m = binding.Model(dw, 1, max_rows=B * (g + 1), max_ctx=cap)
+    kv = binding.KVCache(m, B, cap)
+    install_context(kv, synth.make_kv_context(ODD, 1, lengths, seed=73), lengths, 1, ODD.dtype)
+    pend = synth.make_prompt(1, ODD.vocab, batch=B, seed=74)[:, 0]
+    drafts = synth.make_prompt(g, ODD.vocab, batch=B, seed=75).copy()
+    out, status = [], []
+    for invalid in (False, True):
+        if invalid:
+            drafts[list(bad), g - 1] = ODD.vocab
+        kv.set_state(lengths, np.stack([np.zeros(B, np.int32), pend], 1), np.ones(B, np.int32))
+        logits = torch.empty((B, g + 1, ODD.vocab), dtype=torch.float32, device="cuda")
+        binding.specdec_verify(m, kv, g, i32(drafts), g, logits)
+        out.append(logits.cpu().numpy())
+        status.append(kv.read_state()["status"])
+    assert status == [0, -7]
+    keep = np.ones((B, g + 1), bool)
+    keep[list(bad), g] = False
+    rel = float(np.linalg.norm(out[1][keep] - out[0][keep]) / np.linalg.norm(out[0][keep]))
+    log(f"invalid last rows: relative difference of the others {rel:.3g}")
+    assert rel < REL
+
+
 # (one pass of 1500 rows, two launches of the tile kernel; the shared-K/V attention with 32-dim heads, 3 query heads per
 # kv head: 900 query rows in 15 blocks of 64, the last of them ragged; then ragged chunks of it)
 @pytest.mark.parametrize("B,rows,n", [(5, 1500, 301), (7, 1470, 380)])
