@@ -115,7 +115,7 @@ def test_int4_7b_shape_verify(g):
 
 @pytest.mark.parametrize("lengths,g", [([1, 64, 300, 129], 4), ([1, 64, 300, 129], 3), ([517], 4)])
 def test_int4_1b_shape_verify(lengths, g):
-    # 20 rows: the skinny kernel's INT4 path; 16 rows: one group per wave and
+    # 20 rows: the row-block GEMM's INT4 form; 16 rows: one group per wave and
     # window; one sequence: two SwiGLU units per block, 6 groups per wave of
     # the 5632-column down projection
     _int4_case(synth.LLAMA_1B, 2, lengths, g=g, seed=1)

@@ -334,24 +334,25 @@ def test_bf16_7b_shape_verify_block_vs_steps_across_an_attention_partition_chang
 
 
 def test_bf16_7b_shape_multi_request_ragged():
-    # 16 sequences, ragged contexts, gamma 6: 112 rows (one launch of the wide GEMMs)
+    # 16 sequences, ragged contexts, gamma 6: 112 rows (the tile GEMM, one launch of it per
+    # matrix, and the reductions of its K splits)
     lengths = synth.make_ragged_lengths(16, 40, 400)
     _bf16_case(synth.LLAMA_7B, 1, list(lengths), g=6, seed=2)
 
 
 @pytest.mark.parametrize("B,g", [(2, 3), (2, 7), (3, 4)])
 def test_bf16_1b_shape_stacked_operand_row_counts(B, g):
-    # 8, 16 and 15 rows: passes of at most 16 rows hand x between kernels as the
-    # stacked bf16 operand, one fragment (hi and lo rows of one MFMA) up to 8
-    # rows and two fragments above; K = 2048 also takes the LDS-resident form
+    # 8, 16 and 15 rows: the stacked bf16 operand between the kernels, one
+    # fragment (hi and lo rows of one MFMA) up to 8 rows and two above; over 8
+    # rows the O projection (K = 2048) holds it in LDS
     lengths = synth.make_ragged_lengths(B, 50, 300, seed=7)
     _bf16_case(synth.LLAMA_1B, 2, list(lengths), g=g, seed=6)
 
 
 @pytest.mark.parametrize("B,g", [(7, 4), (8, 7)])
 def test_bf16_1b_shape_skinny_row_tiles(B, g):
-    # 35 and 64 rows: the skinny kernels' four-row-tile variants (float32 x, no
-    # stacked operand), up to the largest pass before the wide kernels (65 rows)
+    # 35 and 64 rows: three and four row tiles of the row-block GEMM, up to its
+    # largest pass (from 65 rows on the tile GEMM runs)
     lengths = synth.make_ragged_lengths(B, 1, 300, seed=9)
     _bf16_case(synth.LLAMA_1B, 2, list(lengths), g=g, seed=4)
 
@@ -365,20 +366,19 @@ def test_bf16_7b_shape_many_short_sequences():
 
 
 def test_bf16_7b_shape_long_context_looping_attention():
-    # 2 sequences of 4500 and 6100 keys: 188 sub-chunks of 32 keys over 64
-    # (kv head, sequence) units -> parts of 8 sub-chunks on 4-wave blocks, each
-    # wave looping over 2 sub-chunks with the online softmax
+    # 2 sequences of 4500 and 6100 keys: 141 and 191 sub-chunks of 32 keys in 32
+    # (kv head, sequence) units each, more than one round of waves: the persistent
+    # grid, 21 sub-chunks per block, every wave looping with the online softmax,
+    # the up to 11 parts of a unit added by the combine launch
     _bf16_case(synth.LLAMA_7B, 1, [4500, 6100], g=4, seed=4)
 
 
 def test_bf16_7b_shape_attention_combine_modes_alternate_on_one_handle():
-    # One model handle, two caches: 2 sequences of 4500 and 6100 keys (looping
-    # attention: the fixed combining block polls tagged partial words, and the
-    # launch advances the per-(sequence, tile, kv head) epochs) and one of 2048
-    # keys (one-round attention: the last block to count combines).  Verifies
-    # alternate between the two several times; every repeat of a verify from the
-    # same state must give the same logits bit for bit, and the first of each
-    # must match the oracle.
+    # One model handle, two caches: 2 sequences of 4500 and 6100 keys (persistent
+    # grid: parts added by a launch of their own) and one of 2048 keys (one round:
+    # the last block of a head to count combines).  Verifies alternate between the
+    # two several times; every repeat of a verify from the same state must give
+    # the same logits bit for bit, and the first of each must match the oracle.
     torch = torch_cuda()
     shape, n_layers, g = synth.LLAMA_7B, 1, 4
     W = synth.make_weights(shape, n_layers=n_layers)
@@ -492,7 +492,7 @@ def test_bf16_1b_shape_long_context_with_nan_keys():
 def test_bf16_7b_shape_long_context_workload_launch_and_accept():
     # The exact launch of the 16-sequence long-context workload: contexts drawn
     # from U[1024, 8192] with the lengths seed (up to 8022 keys), gamma 6 (112
-    # rows: the wide GEMMs and the looping attention), then the temperature-0.8
+    # rows: the tile GEMMs and the persistent attention), then the temperature-0.8
     # accept on the device's verify logits (LOGITS mode) against the oracle's
     # accept on its own logits, with synthetic draft distributions and words.
     torch = torch_cuda()
@@ -525,8 +525,9 @@ def test_bf16_7b_shape_long_context_workload_launch_and_accept():
 
 @pytest.mark.parametrize("B,g", [(13, 4), (16, 7), (25, 7)])
 def test_bf16_1b_shape_wide_rows(B, g):
-    # 65, 128 and 200 rows (128 + 72 in two launches): the wide GEMM path with
-    # its 4-, 7- and 8-tile row variants, split-K residual GEMMs, head_dim 64 RoPE
+    # 65, 128 and 200 rows: the tile GEMM in blocks of 128 and 256 rows, the last
+    # ones partial, K split over the grid in Q|K|V, O and down (and gate|up to 128
+    # rows) with their ordered reductions, head_dim 64 RoPE
     lengths = synth.make_ragged_lengths(B, 1, 300, seed=5)
     _bf16_case(synth.LLAMA_1B, 2, list(lengths), g=g, seed=3)
 
@@ -538,8 +539,8 @@ def test_bf16_prefill_in_large_chunks(shape_name, B, rows, n):
     """Prefill of n-1 prompt tokens per sequence in chunks of rows/B tokens
     (1.1B: 128-token chunks of 2 sequences = 256-row passes, GQA with 64 query
     tiles per kv head; 7B: 256-token chunks, MHA; 1.1B in one 600-row pass:
-    launches of three 256-row tiles, the last partial), then a verify: the
-    caches and the verify logits against the oracle's prefill."""
+    row tiles of 128, the last partial), then a verify: the caches and the
+    verify logits against the oracle's prefill."""
     torch = torch_cuda()
     shape = getattr(synth, shape_name)
     L, g = 2, 4
