@@ -51,14 +51,21 @@ __device__ __forceinline__ float row_half_swap(float v) {
 // is fed to the products as the bf16 value 24 + q (q4_operand24), the bias is
 // cancelled by the product of the same x with -24, shared by the unit's tiles,
 // and a group's sum is multiplied by the row's group scale in float32.
-// Over at most 16 rows (MT = 1) the hi and lo parts are summed apart and added
-// once per unit and wave: XF = 1 (at most 8 rows) has both in one fragment, hi
-// in x rows 0-7 and lo in rows 8-15 of one product, XF = 2 in two; the sums are
-// the same either way, so a block of rows equals its rows run one by one.
+// Over at most 16 rows, and in Q|K|V, the hi and lo parts are summed apart and
+// added once per unit and wave (APART): in one accumulator every product of the
+// small lo part rounds the large sum once more.  Keys and values of a first
+// layer that fall on the other bf16 side of their 64-bit value, per 1e5, in one
+// accumulator and apart: 8 rows of the 1.1B and the 7B shape 17 and 21, 9 and 16;
+// 24 rows 21 and 23, 12 and 16.  (Above 16 rows the other results are not rounded
+// to bf16, the logits' error is the same either way, and twice the accumulators
+// cost up to 5%.)  XF = 1 (at most 8 rows) has both parts in one fragment, hi in
+// x rows 0-7 and lo in rows 8-15 of one product, XF = 2 in two; the sums are the
+// same, so a block of rows equals its rows run one by one.
 template <int T, int MT, int NW, int UB, int KIND, bool Q4, int XF, bool PEEL>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_units, int n_split, int ks_per_split) {
   constexpr int NC = 16 * T, MP = 16 * MT;
-  constexpr int MA = MT == 1 ? XF : MT;  // accumulator tiles per weight tile
+  constexpr bool APART = MT == 1 || (!Q4 && KIND == EPI_QKV);
+  constexpr int MA = APART ? XF : MT;  // accumulator tiles per weight tile
   static_assert(XF == 2 * MT || (MT == 1 && XF == 1), "fragments of x per k-step");
   constexpr bool SCALE = KIND != EPI_RESID, SWIGLU = KIND == EPI_SWIGLU;
   // fragments per reduction round (a SwiGLU round holds whole gate / up pairs)
@@ -218,13 +225,16 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_rows(GemmArgs a, int n_unit
     }
   };
   auto finish = [&](int unit) {
-    if constexpr (MT == 1) {  // hi + lo (XF = 1: of row m in lanes of rows m and 8 + m)
+    if constexpr (APART) {  // hi + lo (XF = 1: of row m in lanes of rows m and 8 + m)
 #pragma unroll
       for (int t = 0; t < T; ++t) {
-        if constexpr (XF == 2) acc[0][t] += acc[1][t];
-        else
+        if constexpr (XF == 1) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) acc[0][t][r] += row_half_swap(acc[0][t][r]);
+        } else {
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) acc[mt][t] = acc[2 * mt][t] + acc[2 * mt + 1][t];
+        }
       }
     }
 #pragma unroll

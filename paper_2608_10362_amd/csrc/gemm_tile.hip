@@ -33,7 +33,7 @@ constexpr int kMaxSs = 64;                    // ss partials a reduction sums
 // 45 -> 35, down 105 -> 78, against staging float32 x through registers; 112
 // rows: gate|up 63 -> 50, Q|K|V 40 -> 31, O 21 -> 15, down 37 -> 29, LM head
 // 101 -> 75 (there 3.2 to 3.7 TB/s of weights).
-template <int WM, int WN, int MTW, int NTW, int ST, int KIND>
+template <int WM, int WN, int MTW, int NTW, int ST, int KIND, bool KEYS>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile(GemmArgs a, int n_ctiles, int ks_per_split, int n_split) {
   constexpr int NW = WM * WN, MTB = WM * MTW, NTB = WN * NTW;  // row and weight tiles of the block
   constexpr bool SCALE = KIND != EPI_RESID, SWIGLU = KIND == EPI_SWIGLU;
@@ -104,20 +104,32 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile(GemmArgs a, int n
 #pragma unroll
     for (int j = 0; j < NTW; ++j) r.w[j] = st[XFR + btile(j)][lane];
   };
-  floatx4 acc[MTW][NTW];
+  // KEYS (the Q|K|V projections, whose results are rounded to bf16): blocks of at
+  // most 128 rows sum hi and lo products apart.  In one accumulator every product
+  // of the small lo part rounds the large sum once more (keys and values of a
+  // first layer, 120 rows of the 7B shape, that fall on the other bf16 side of
+  // their 64-bit value, per 1e5: 37 in one, 27 apart).  Blocks of 256 rows have no
+  // registers for it.
+  constexpr int HL = KEYS && 16 * MTB <= 128 ? 2 : 1;
+  floatx4 acc[MTW][NTW], acl[HL == 2 ? MTW : 1][HL == 2 ? NTW : 1];
 #pragma unroll
   for (int m = 0; m < MTW; ++m)
 #pragma unroll
-    for (int j = 0; j < NTW; ++j) acc[m][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NTW; ++j) {
+      acc[m][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (HL == 2) acl[m][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
   auto multiply = [&](const Frags& r) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int m = 0; m < MTW; ++m)
 #pragma unroll
-        for (int j = 0; j < NTW; ++j)
-          acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.w[j]),
-                                                              __builtin_bit_cast(bf16x8, r.x[m][h]), acc[m][j], 0, 0, 0);
+        for (int j = 0; j < NTW; ++j) {
+          floatx4& s = HL == 2 && h == 1 ? acl[HL == 2 ? m : 0][HL == 2 ? j : 0] : acc[m][j];
+          s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, r.w[j]),
+                                                      __builtin_bit_cast(bf16x8, r.x[m][h]), s, 0, 0, 0);
+        }
   };
 
 #pragma unroll
@@ -159,6 +171,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile(GemmArgs a, int n
       }
       __builtin_amdgcn_sched_group_barrier(0x008, NM - NR * PER, 0);
     }
+  }
+  if constexpr (HL == 2) {
+#pragma unroll
+    for (int m = 0; m < MTW; ++m)
+#pragma unroll
+      for (int j = 0; j < NTW; ++j) acc[m][j] += acl[m][j];
   }
   wait_vm<0>();  // (the re-read stages past the range have landed before the block can end)
   __syncthreads();
@@ -363,26 +381,26 @@ TilePlan plan_tile(int M, int n, int KS, bool pairs, bool can_split, bool always
   return best;
 }
 
-template <int WM, int WN, int MTW, int NTW, int ST, int KIND>
+template <int WM, int WN, int MTW, int NTW, int ST, int KIND, bool KEYS>
 void launch_shape(const GemmArgs& a, const TilePlan& p, hipStream_t s) {
   constexpr int BM = 16 * WM * MTW, BN = (KIND == EPI_SWIGLU ? 8 : 16) * WN * NTW;
   const int rt = (a.M + BM - 1) / BM, ct = (a.n_rows + BN - 1) / BN;
-  hipLaunchKernelGGL((gemm_bf16_tile<WM, WN, MTW, NTW, ST, KIND>), dim3(rt * ((ct + 7) / 8 * 8) * p.n_split),
+  hipLaunchKernelGGL((gemm_bf16_tile<WM, WN, MTW, NTW, ST, KIND, KEYS>), dim3(rt * ((ct + 7) / 8 * 8) * p.n_split),
                      dim3(64 * WM * WN), 0, s, a, ct, p.per, p.n_split);
 }
-template <int KIND>
+template <int KIND, bool KEYS = false>
 hipError_t launch_plan(const GemmArgs& a, const TilePlan& p, hipStream_t s) {
   switch (p.shape) {
-    case 0: launch_shape<4, 2, 4, 6, 3, KIND>(a, p, s); break;
-    case 1: launch_shape<4, 2, 4, 4, 3, KIND>(a, p, s); break;
-    case 2: launch_shape<8, 1, 2, 6, 4, KIND>(a, p, s); break;
-    case 3: launch_shape<4, 2, 2, 6, 4, KIND>(a, p, s); break;
-    case 4: launch_shape<2, 4, 4, 2, 4, KIND>(a, p, s); break;
-    case 7: launch_shape<2, 4, 3, 2, 4, KIND>(a, p, s); break;
+    case 0: launch_shape<4, 2, 4, 6, 3, KIND, KEYS>(a, p, s); break;
+    case 1: launch_shape<4, 2, 4, 4, 3, KIND, KEYS>(a, p, s); break;
+    case 2: launch_shape<8, 1, 2, 6, 4, KIND, KEYS>(a, p, s); break;
+    case 3: launch_shape<4, 2, 2, 6, 4, KIND, KEYS>(a, p, s); break;
+    case 4: launch_shape<2, 4, 4, 2, 4, KIND, KEYS>(a, p, s); break;
+    case 7: launch_shape<2, 4, 3, 2, 4, KIND, KEYS>(a, p, s); break;
     default:
       if constexpr (KIND != EPI_SWIGLU) {
-        if (p.shape == 5) launch_shape<4, 2, 2, 3, 4, KIND>(a, p, s);
-        else if (p.shape == 6) launch_shape<2, 4, 3, 3, 4, KIND>(a, p, s);
+        if (p.shape == 5) launch_shape<4, 2, 2, 3, 4, KIND, KEYS>(a, p, s);
+        else if (p.shape == 6) launch_shape<2, 4, 3, 3, 4, KIND, KEYS>(a, p, s);
         else return hipErrorInvalidValue;
         break;
       }
@@ -420,10 +438,10 @@ hipError_t launch_gemm_tile(const GemmArgs& a, hipStream_t s) {
       if (a.kv.dtype != SPECDEC_BF16 || a.head_dim % 16 || a.n_seg[0] % a.head_dim || a.n_seg[1] % a.head_dim)
         return hipErrorInvalidValue;
       const TilePlan p = plan_tile(a.M, a.n_rows, KS, false, true, false, a.ypart_floats);
-      if (p.n_split == 1) return launch_plan<EPI_QKV>(a, p, s);
+      if (p.n_split == 1) return launch_plan<EPI_QKV, true>(a, p, s);
       GemmArgs g = a;
       g.kind = EPI_RESID;
-      const hipError_t e = launch_plan<EPI_RESID>(g, p, s);
+      const hipError_t e = launch_plan<EPI_RESID, true>(g, p, s);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(qkv_reduce_kernel, reduce_grid(a), dim3(256), 0, s, a, p.n_split);
       return hipGetLastError();

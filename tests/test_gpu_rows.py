@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2608_10362_amd import binding, synth
-from tests.gpu_util import i32, install_context, log, torch_cuda
+from tests.gpu_util import i32, install_context, kv_to_device, log, torch_cuda
 from tests.test_gpu_int4 import _int4_case
 from tests.test_gpu_model import _bf16_case, test_bf16_prefill_in_large_chunks as _prefill_case
 
@@ -65,6 +65,42 @@ def test_rows_equal_their_sequences_alone(shape, B, g):
     block = verify(list(range(B)))
     for b in range(B):
         assert np.array_equal(verify([b])[0], block[b]), b
+
+
+@pytest.mark.parametrize("shape,rows,limit", [(synth.LLAMA_1B, 24, 15.5), (synth.LLAMA_1B, 64, 17),
+                                              (synth.LLAMA_7B, 24, 22), (synth.LLAMA_7B, 64, 21), (synth.LLAMA_7B, 120, 25)])
+def test_first_layer_keys_and_values_round_as_in_64_bits(shape, rows, limit):
+    """Keys and values of one prefilled layer against their 64-bit values rounded
+    to bf16: only a value within the float32 sums' error of a tie may differ.
+    `limit` per 1e5 values lies halfway between what hi and lo products summed
+    apart give (11.7, 15.3, 19.6, 17.5, 21.3) and what they give in one
+    accumulator (19.3, 18.8, 24.7, 24.0, 29.5); the sums have a fixed order."""
+    torch = torch_cuda()
+    G, hd, differ, total = shape.n_kv_heads, shape.head_dim, 0, 0
+    W = synth.make_weights(shape, n_layers=1)
+    gain = 1.0 + 0.1 * np.random.default_rng(79).standard_normal(shape.d_model, dtype=np.float32)
+    W["layers"][0]["attn_norm"] = synth.f32_to_bf16_bits(gain)  # (x = embedding times gain: a lo part that is not 0)
+    dw = binding.DeviceWeights(shape, W)
+    up = lambda bits: kv_to_device(np.asarray(bits), "bf16").double()  # noqa: E731
+    lw = {k: up(W["layers"][0][k]) for k in ("attn_norm", "wk", "wv")}
+    m = binding.Model(dw, 1, max_rows=rows, max_ctx=1024)
+    n = max(rows, -(-400000 // (2 * G * hd)) // rows * rows)  # (whole passes; at least 400000 values)
+    half, pos = hd // 2, torch.arange(rows, dtype=torch.float64, device="cuda")
+    inv = shape.rope_base ** (-2.0 * torch.arange(half, dtype=torch.float64, device="cuda") / hd)
+    c, s = torch.cos(pos[:, None] * inv)[:, None], torch.sin(pos[:, None] * inv)[:, None]
+    for i in range(n // rows):
+        kv = binding.KVCache(m, 1, 1024)
+        tok = synth.make_prompt(rows + 1, shape.vocab, batch=1, seed=80 + i)
+        binding.specdec_prefill(m, kv, i32(tok))
+        x = up(np.asarray(W["embed"])[tok[0, :rows]])
+        x = x / torch.sqrt((x * x).mean(-1, keepdim=True) + shape.rms_eps) * lw["attn_norm"]
+        k, v = ((x @ lw[w].t()).reshape(rows, G, hd) for w in ("wk", "wv"))
+        k = torch.cat([k[..., :half] * c - k[..., half:] * s, k[..., half:] * c + k[..., :half] * s], -1)
+        for got, ref in zip(kv.read_context(0, 0, 0, rows), (k, v)):
+            differ += int((got != ref.float().to(torch.bfloat16)).sum())
+            total += ref.numel()
+    log(f"rows {rows}: {differ} of {total} values differ, {1e5 * differ / total:.1f} per 1e5")
+    assert differ <= limit * total / 1e5
 
 
 # (the tile kernel: more than 64 rows, row tiles of 96, 128 and 256 with remainders, launches of 1024 rows)
