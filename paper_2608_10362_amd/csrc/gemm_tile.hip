@@ -29,10 +29,10 @@ constexpr int kMaxSs = 64;                    // ss partials a reduction sums
 // a RoPE partner (column ^ 8) is lane ^ 32.
 // Bound: the matrix units at the clock they hold (1.1 to 1.3 PFLOP/s of
 // products; a large library bf16 product reaches 1.55 on the same card).  7B
-// shapes, 512 rows: gate|up 309 -> 155 us, Q|K|V 158 (+ 13 for RoPE) -> 87, O
-// 45 -> 35, down 105 -> 78, against staging float32 x through registers; 112
-// rows: gate|up 63 -> 50, Q|K|V 40 -> 31, O 21 -> 15, down 37 -> 29, LM head
-// 101 -> 75 (there 3.2 to 3.7 TB/s of weights).
+// shapes, the reductions included, against staging float32 x through registers:
+// 512 rows gate|up 308 -> 153 us, Q|K|V 182 -> 110, O 55 -> 42, down 120 -> 90;
+// 112 rows gate|up 64 -> 55, Q|K|V 45 -> 43, O 29 -> 19.5, down 40 -> 32, LM head
+// 91 -> 70 (there 3.3 to 3.7 TB/s of weights).
 template <int WM, int WN, int MTW, int NTW, int ST, int KIND, bool KEYS>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_tile(GemmArgs a, int n_ctiles, int ks_per_split, int n_split) {
   constexpr int NW = WM * WN, MTB = WM * MTW, NTB = WN * NTW;  // row and weight tiles of the block

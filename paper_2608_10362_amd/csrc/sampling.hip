@@ -103,8 +103,8 @@ __device__ __forceinline__ MaxSum ms_merge(MaxSum a, MaxSum b) {
 // 1) computes its RoPE table (in float64: the angle of position p at float32
 // resolution needs it) with one thread per cosine and one per sine.  Both are
 // latency chains (the table's pow, then cos or sin; the row's state words,
-// then its embedding), so they run side by side: 13.2 us for the two one after
-// the other over 5 rows of the 7B shape, 6.8 now.
+// then its embedding), so they run side by side: 12.8 us for the two one after
+// the other over 5 rows of the 7B shape, 6.2 now (at the head of a pass).
 template <typename ET>
 __global__ __launch_bounds__(256) void rows_embed_kernel(RowsArgs a) {
   __shared__ float red[16];
